@@ -536,33 +536,34 @@ struct TileLds {
 
 // Loads tile `tile` and ranks every element among the elements of its wave
 // with the same digit (stable: wave order, then round, then lane).  After
-// the call wcnt[w][dg] holds wave w's count of digit dg.
-template <bool HAS_VAL>
-__device__ __forceinline__ void tile_rank(TileLds<HAS_VAL>& S, const uint64_t* __restrict__ kin,
-                                          const uint32_t* __restrict__ vin, size_t tile_base,
-                                          size_t tile_end, int shift, int nbits, uint64_t* k_,
-                                          uint32_t* v_, uint32_t* r_) {
+// the call wcnt[w][dg] holds wave w's count of digit dg.  Every key (and
+// value) of the thread is loaded before the first is ranked: the ranking
+// rounds are ordered by wave-level fences, which kept each round's load
+// behind the round before (a pass over 32e6 keys with values 218 -> 161 us;
+// over 160e3 keys, where the chain was the whole time, 12.5 -> 9.9 us).
+template <bool HAS_VAL, int NB>
+__device__ __forceinline__ void tile_rank_n(TileLds<HAS_VAL>& S, size_t wave_base, size_t tile_end,
+                                            int shift, int nbits, const uint64_t* k_,
+                                            uint32_t* r_) {
   const uint32_t lane = lane_id();
   const int w = threadIdx.x >> 6;
   const uint32_t mask = (1u << nbits) - 1u;
-#pragma unroll
-  for (int q = 0; q < kWaves; ++q) S.wcnt[q][threadIdx.x] = 0u;
-  __syncthreads();
-  const size_t wave_base = tile_base + (size_t)w * (kTile / kWaves);
   const uint64_t lt = (1ull << lane) - 1ull;
 #pragma unroll
   for (int q = 0; q < kKeysPerThread; ++q) {
-    const size_t e = wave_base + (size_t)q * 64 + lane;
-    const bool valid = e < tile_end;
-    const uint64_t key = valid ? kin[e] : ~0ull;
-    k_[q] = key;
-    if (HAS_VAL) v_[q] = valid ? vin[e] : 0u;
-    const uint32_t dg = (uint32_t)(key >> shift) & mask;
+    const bool valid = wave_base + (size_t)q * 64 + lane < tile_end;
+    const uint32_t dg = (uint32_t)(k_[q] >> shift) & mask;
     uint64_t peers = ballot(valid);
-    for (int b = 0; b < nbits; ++b) {
+    auto match = [&](int b) {
       const bool bit = (dg >> b) & 1u;
       const uint64_t m = ballot(bit);
       peers &= bit ? m : ~m;
+    };
+    if constexpr (NB > 0) {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) match(b);
+    } else {
+      for (int b = 0; b < nbits; ++b) match(b);
     }
     uint32_t before = 0;
     if (valid) before = S.wcnt[w][dg];
@@ -571,6 +572,28 @@ __device__ __forceinline__ void tile_rank(TileLds<HAS_VAL>& S, const uint64_t* _
     if (valid && (peers & lt) == 0ull) S.wcnt[w][dg] = before + (uint32_t)__popcll(peers);
     wave_lds_sync();
   }
+}
+
+template <bool HAS_VAL>
+__device__ __forceinline__ void tile_rank(TileLds<HAS_VAL>& S, const uint64_t* __restrict__ kin,
+                                          const uint32_t* __restrict__ vin, size_t tile_base,
+                                          size_t tile_end, int shift, int nbits, uint64_t* k_,
+                                          uint32_t* v_, uint32_t* r_) {
+  const uint32_t lane = lane_id();
+  const int w = threadIdx.x >> 6;
+  const size_t wave_base = tile_base + (size_t)w * (kTile / kWaves);
+  // (a tile holds at least one key: elements past its end read its last)
+#pragma unroll
+  for (int q = 0; q < kKeysPerThread; ++q) {
+    const size_t e = min(wave_base + (size_t)q * 64 + lane, tile_end - 1);
+    k_[q] = kin[e];
+    if (HAS_VAL) v_[q] = vin[e];
+  }
+#pragma unroll
+  for (int q = 0; q < kWaves; ++q) S.wcnt[q][threadIdx.x] = 0u;
+  __syncthreads();
+  if (nbits == kRadixBits) tile_rank_n<HAS_VAL, kRadixBits>(S, wave_base, tile_end, shift, nbits, k_, r_);
+  else tile_rank_n<HAS_VAL, 0>(S, wave_base, tile_end, shift, nbits, k_, r_);
   __syncthreads();
 }
 
@@ -693,14 +716,18 @@ __global__ __launch_bounds__(kBlock) void k_radix_hist(const uint64_t* __restric
                                                        uint32_t ntiles,
                                                        const SortTile* __restrict__ tiles) {
   __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0u;
-  __syncthreads();
   const uint32_t mask = (1u << nbits) - 1u;
   const TileSpan t = tile_span(tiles, count, ntiles, blockIdx.x);
-#pragma unroll 4
+  uint64_t k_[kKeysPerThread];  // every load in flight before the first count
+#pragma unroll
+  for (int q = 0; q < kKeysPerThread; ++q)
+    k_[q] = keys[min(t.start + (size_t)q * kBlock + threadIdx.x, t.end - 1)];
+  h[threadIdx.x] = 0u;
+  __syncthreads();
+#pragma unroll
   for (int q = 0; q < kKeysPerThread; ++q) {
-    size_t e = t.start + (size_t)q * kBlock + threadIdx.x;
-    if (e < t.end) atomicAdd(&h[(uint32_t)(keys[e] >> shift) & mask], 1u);
+    const size_t e = t.start + (size_t)q * kBlock + threadIdx.x;
+    if (e < t.end) atomicAdd(&h[(uint32_t)(k_[q] >> shift) & mask], 1u);
   }
   __syncthreads();
   tile_hist[t.slot + (size_t)threadIdx.x * t.stride] = h[threadIdx.x];
@@ -828,24 +855,12 @@ __global__ __launch_bounds__(kBlock) void k_onesweep(
 // ---------------------------------------------------------------------------
 // runs of equal keys (cells with >= 2 points), unique keys.
 
-// Whether element e begins or ends a run of at least two equal keys.  The
-// wave's lanes hold 64 consecutive elements (e = 64-aligned base + lane):
-// each loads its own key, takes its neighbours' from the adjacent lanes, and
-// only the first and last lanes load the keys beyond the wave's ends.
-__device__ __forceinline__ void run_flags(const uint64_t* __restrict__ keys, size_t count, size_t e,
-                                          uint32_t lane, int shift, bool& head, bool& tail) {
-  const bool in = e < count;
-  const uint64_t k = in ? keys[e] >> shift : 0ull;
-  uint64_t kp = __shfl_up(k, 1, 64);
-  uint64_t kn = __shfl_down(k, 1, 64);
-  if (lane == 0 && in && e > 0) kp = keys[e - 1] >> shift;
-  if (lane == 63 && e + 1 < count) kn = keys[e + 1] >> shift;
-  const bool prev_same = in && e > 0 && kp == k;
-  const bool next_same = in && e + 1 < count && kn == k;
-  head = !prev_same && next_same;
-  tail = prev_same && !next_same;
-}
-
+// Run heads and tails: whether an element begins or ends a run of at least
+// two equal keys.  A wave takes 1024 consecutive elements in 16 groups of
+// 64; its keys and the keys beyond its two ends are all loaded first (loads
+// that waited for each group in turn made this kernel a serial chain of 16
+// memory latencies: 17 -> 4.8 us at 160e3 keys, 123 -> 67 us at 32e6), and a
+// group's neighbours come from the adjacent lanes and groups.
 __global__ __launch_bounds__(kBlock) void k_run_count(const uint64_t* __restrict__ keys,
                                                       size_t count, int shift, uint32_t* head_cnt,
                                                       uint32_t* tail_cnt,
@@ -855,11 +870,30 @@ __global__ __launch_bounds__(kBlock) void k_run_count(const uint64_t* __restrict
   const int w = threadIdx.x >> 6;
   const size_t wave_base = (size_t)blockIdx.x * kTile + (size_t)w * (kTile / kWaves);
   const size_t ngroups = (count + 63) / 64;
+  uint64_t k_[kKeysPerThread];
+#pragma unroll
+  for (int q = 0; q < kKeysPerThread; ++q)
+    k_[q] = keys[min(wave_base + (size_t)q * 64 + lane, count - 1)] >> shift;
+  const uint64_t before = keys[min(wave_base ? wave_base - 1 : 0, count - 1)] >> shift;
+  const uint64_t after = keys[min(wave_base + kTile / kWaves, count - 1)] >> shift;
   uint32_t hc = 0, tc = 0;
+#pragma unroll
   for (int q = 0; q < kKeysPerThread; ++q) {
-    bool h, t;
-    run_flags(keys, count, wave_base + (size_t)q * 64 + lane, lane, shift, h, t);
-    const uint64_t hb = ballot(h), tb = ballot(t);
+    const size_t e = wave_base + (size_t)q * 64 + lane;
+    const uint64_t k = k_[q];
+    uint64_t kp = __shfl_up(k, 1, 64);
+    uint64_t kn = __shfl_down(k, 1, 64);
+    const uint64_t last = q ? lane_value((unsigned long long)k_[q ? q - 1 : 0], 63) : before;
+    const uint64_t first =
+        q + 1 < kKeysPerThread
+            ? lane_value((unsigned long long)k_[q + 1 < kKeysPerThread ? q + 1 : 0], 0)
+            : after;
+    if (lane == 0) kp = last;
+    if (lane == 63) kn = first;
+    const bool in = e < count;
+    const bool prev_same = in && e > 0 && kp == k;
+    const bool next_same = in && e + 1 < count && kn == k;
+    const uint64_t hb = ballot(!prev_same && next_same), tb = ballot(prev_same && !next_same);
     hc += (uint32_t)__popcll(hb);
     tc += (uint32_t)__popcll(tb);
     // the writing kernel reads these bits instead of the keys again
@@ -900,18 +934,16 @@ __global__ __launch_bounds__(kBlock) void k_run_write(const uint64_t* __restrict
   const int w = threadIdx.x >> 6;
   const size_t wave_base = (size_t)blockIdx.x * kTile + (size_t)w * (kTile / kWaves);
   const size_t ngroups = (count + 63) / 64;
-  uint32_t hmask = 0, tmask = 0, hc = 0, tc = 0;
+  // lane 2 q / 2 q + 1 holds the head / tail bits of the wave's group q
+  static_assert(2 * kKeysPerThread <= 64, "one mask word per lane");
+  unsigned long long mword = 0;
+  if (lane < 2 * kKeysPerThread && (wave_base >> 6) + lane / 2 < ngroups)
+    mword = masks[2 * (wave_base >> 6) + lane];
+  uint32_t hc = 0, tc = 0;
+#pragma unroll
   for (int q = 0; q < kKeysPerThread; ++q) {
-    const size_t g = (wave_base >> 6) + (size_t)q;
-    uint64_t hb = 0, tb = 0;
-    if (g < ngroups) {
-      hb = masks[2 * g];
-      tb = masks[2 * g + 1];
-    }
-    hmask |= (uint32_t)((hb >> lane) & 1ull) << q;
-    tmask |= (uint32_t)((tb >> lane) & 1ull) << q;
-    hc += (uint32_t)__popcll(hb);
-    tc += (uint32_t)__popcll(tb);
+    hc += (uint32_t)__popcll(lane_value(mword, 2 * q));
+    tc += (uint32_t)__popcll(lane_value(mword, 2 * q + 1));
   }
   if (lane == 0) {
     sh[w] = hc;
@@ -945,10 +977,11 @@ __global__ __launch_bounds__(kBlock) void k_run_write(const uint64_t* __restrict
     hbase += sh[q];
     tbase += st[q];
   }
+#pragma unroll
   for (int q = 0; q < kKeysPerThread; ++q) {
     const size_t e = wave_base + (size_t)q * 64 + lane;
-    const bool h = (hmask >> q) & 1u, t = (tmask >> q) & 1u;
-    const uint64_t hb = ballot(h), tbm = ballot(t);
+    const uint64_t hb = lane_value(mword, 2 * q), tbm = lane_value(mword, 2 * q + 1);
+    const bool h = (hb >> lane) & 1ull, t = (tbm >> lane) & 1ull;
     if (h) start[hbase + rank_below(hb)] = (uint32_t)e;
     if (t) end[tbase + rank_below(tbm)] = (uint32_t)(e + 1);
     hbase += (uint32_t)__popcll(hb);
