@@ -1717,7 +1717,7 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
     auto stretch = [&]() {
       KeysArgs ka{inst_d, m, nblk, d, npts, soa, sa, sb, segs_d, Rd, ud, klo_d, layout_d,
                   keys, vals, err, sig, sig_stride, sig_b, sig_gpw, idx_bits,
-                  P.tb >= S_total ? 1 : 0};
+                  P.tb >= S_total ? 1 : 0, kmax};
       kbegin(RTG_K_KEYS);
       launch_keys(ka, stream);
       kend(RTG_K_KEYS, 4.0 * (double)pass_pts * d + (idx_bits ? 8.0 : 12.0) * (double)N +
@@ -2713,7 +2713,7 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
     void* scr = S.get<char>(radix_scratch_bytes(N, 0, key_bits, (size_t)(sb - sa)));
     if (!keys || !keys_alt || (!idx_bits && (!vals || !vals_alt)) || !scr) return RTG_ENOMEM;
     KeysArgs ka{inst_d, 1, nblk, d, n, soa, sa, sb, segs_d, I.R, I.u, I.klo, I.layout,
-                keys, vals, err, I.sig, I.sig_W, I.sig_b, I.sig_gpw, idx_bits};
+                keys, vals, err, I.sig, I.sig_W, I.sig_b, I.sig_gpw, idx_bits, 0, k};
     launch_keys(ka, stream);
     // several grids in the sort: within grids, on the cell bits only
     const bool segmented = seg_bits > 0 && ctx->defaults.sort_algo == kSortReduceScan;

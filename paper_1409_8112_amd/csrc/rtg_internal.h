@@ -133,6 +133,7 @@ struct KeysArgs {
   int sig_stride, sig_b, sig_gpw;  // sig_stride: words from one point's signature to the next
   int idx_bits;
   int sig_fresh;     // 1: this pass covers every grid, so signature words are stored, not ORed
+  int kmax;          // most grids of an instance
 };
 void launch_keys(const KeysArgs& a, hipStream_t s);
 // kappa [n][d] = floor(y) for one transform (stage check).

@@ -63,6 +63,12 @@ __device__ __forceinline__ unsigned long long lane_value(unsigned long long v, i
   return ((unsigned long long)hi << 32) | lo;
 }
 
+// v of the first active lane, as a scalar.
+template <typename T>
+__device__ __forceinline__ T uniform(T v) {
+  return (T)__builtin_amdgcn_readfirstlane((int)v);
+}
+
 // DPP controls: row_shr:n = 0x110 + n, row_mirror = 0x140,
 // row_half_mirror = 0x141, row_bcast:15 = 0x142, row_bcast:31 = 0x143;
 // quad_perm [1,0,3,2] = 0xB1, [2,3,0,1] = 0x4E.
@@ -339,10 +345,25 @@ __device__ __forceinline__ double cell_y(const double* __restrict__ Rj, const fl
   return z * inv_c + uj;
 }
 
-// One thread per batch point; writes the keys of the point's segments in
-// [sa, sb): key = (segment - sa) << cell_bits | packed cell, at
-// segs[segment].key_off + the point's index in its instance.
-template <int D>
+// Byte j of a KeyLayout array as a scalar (a wave-uniform j): read as words,
+// which the scalar unit can load; bytes go through vector registers.
+__device__ __forceinline__ uint32_t layout_byte(const uint8_t* __restrict__ bytes, int j) {
+  const uint32_t v = reinterpret_cast<const uint32_t*>(bytes)[j >> 2];
+  return (v >> (8 * (j & 3))) & 0xFFu;
+}
+
+// Writes the keys of the points' segments in [sa, sb): key = (segment - sa)
+// << cell_bits | packed cell, at segs[segment].key_off + the point's index in
+// its instance.  The work is one FP64 dot product per axis and the packing of
+// its floor; packed in 32 bits when cell and signature group fit (fields are
+// taken modulo their width, at most 32 bits, so 32-bit differences are exact):
+// 61 -> 51 us for 8e6 keys at d = 6, 537 -> 507 us for 32e6 at d = 12.
+// SPLIT = false: one thread per batch point, all of its grids.  SPLIT = true:
+// a block takes 64 points, its four waves every fourth grid of a signature
+// word, whose parts meet in LDS; blockIdx.y takes words_per_slice words.
+// Four waves per point fill the chip where the points alone do not (see
+// launch_keys).
+template <int D, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ inst, uint32_t m,
                                                  int d_rt, int64_t npts,
                                                  const float* __restrict__ soa, int sa, int sb,
@@ -355,69 +376,97 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
                                                  uint32_t* __restrict__ vals, uint32_t* err,
                                                  uint64_t* __restrict__ sig, int sig_stride,
                                                  int sig_b, int sig_gpw, int idx_bits,
-                                                 int sig_fresh) {
+                                                 int sig_fresh, int words_per_slice) {
+  __shared__ uint64_t part[SPLIT ? kWaves : 1][SPLIT ? 64 : 1];
   const int d = D > 0 ? D : d_rt;
-  const uint32_t q = block_instance(inst, m, blockIdx.x);
-  const int64_t i = (int64_t)(blockIdx.x - (uint32_t)inst[q].blk_first) * kBlock + threadIdx.x;
-  if (i >= inst[q].n) return;
-  const int64_t g = inst[q].pt_off + i;
+  const uint32_t blk = SPLIT ? blockIdx.x / kWaves : blockIdx.x;
+  const uint32_t lane = lane_id();
+  const int w = uniform((int)(threadIdx.x >> 6));
+  const uint32_t q = uniform(block_instance(inst, m, blk));
+  const int64_t n = inst[q].n;
+  const int64_t i0 = (int64_t)(blk - (uint32_t)inst[q].blk_first) * kBlock +
+                     (SPLIT ? (int64_t)(blockIdx.x % kWaves) * 64 : 0);
+  const int64_t i = i0 + (SPLIT ? lane : threadIdx.x);
+  if (SPLIT ? i0 >= n : i >= n) return;  // (SPLIT: the whole block)
+  const bool live = i < n;
+  const int64_t g = inst[q].pt_off + (live ? i : n - 1);
   const int seg_first = inst[q].seg_first;
   const int t_lo = max(0, sa - seg_first), t_hi = min(inst[q].k, sb - seg_first);
+  if (t_lo >= t_hi) return;
   const double inv_c = inst[q].inv_c;
+  const int tr_off = inst[q].tr_off;
   float p[D > 0 ? D : 1];
   if (D > 0) {
 #pragma unroll
     for (int l = 0; l < (D > 0 ? D : 1); ++l) p[l] = soa[(int64_t)l * npts + g];
   }
   const int cell_bits = layout->cell_bits;
-  const uint64_t bmask = (1ull << sig_b) - 1ull;
+  const uint32_t bmask = (uint32_t)((1ull << sig_b) - 1ull);
   const int gbits = d * sig_b;
-  uint64_t sword = 0;  // signature word being filled
-  int sw = -1;         // its index
   bool bad = false;
-  for (int t = t_lo; t < t_hi; ++t) {
+  // one grid's key (stored) and signature group (returned)
+  auto grid = [&](int t, auto zero) -> uint64_t {
+    using C = decltype(zero);
     const int s = seg_first + t;
-    const int tr = inst[q].tr_off + t;
+    const int tr = tr_off + t;
     const double* Rt = R + (size_t)tr * d * d;
     const double* ut = u + (size_t)tr * d;
     const int64_t* kl = klo + (size_t)tr * d;
-    uint64_t cell = 0, grp = 0;
+    C cell = 0, grp = 0;
     for (int j = 0; j < d; ++j) {
-      double y = cell_y<D>(Rt + (size_t)j * d, p, soa, npts, g, d, inv_c, ut[j]);
-      bool ok = fabs(y) < 2147483648.0;
+      const double y = cell_y<D>(Rt + (size_t)j * d, p, soa, npts, g, d, inv_c, ut[j]);
+      const bool ok = fabs(y) < 2147483648.0;
       bad |= !ok;
       // |y| < 2^31: the floor fits 32 bits, and one native conversion takes it
-      int64_t kap = ok ? (int64_t)(int32_t)floor(y) : 0;
-      uint64_t mask = (1ull << layout->bits[j]) - 1ull;
-      cell |= ((uint64_t)(kap - kl[j]) & mask) << layout->shift[j];
-      grp |= ((uint64_t)(kap - kl[j]) & bmask) << (j * sig_b);
+      const uint32_t f = (uint32_t)(ok ? (int32_t)floor(y) : 0) - (uint32_t)kl[j];
+      const uint32_t mask = (uint32_t)((1ull << layout_byte(layout->bits, j)) - 1ull);
+      cell |= (C)(f & mask) << layout_byte(layout->shift, j);
+      grp |= (C)(f & bmask) << (j * sig_b);
     }
-    if (sig) {
-      // the point owns its row: earlier passes' bits are read back and kept
-      const int w = t / sig_gpw;
-      if (w != sw) {
-        if (sw >= 0) {
-          uint64_t* dst = sig + (size_t)g * sig_stride + sw;
-          *dst = sig_fresh ? sword : (*dst | sword);
-        }
-        sword = 0;
-        sw = w;
-      }
-      sword |= grp << ((t - w * sig_gpw) * gbits);
-    }
-    const uint64_t key = (cell_bits < 64) ? (((uint64_t)(s - sa) << cell_bits) | cell) : cell;
+    const uint64_t key =
+        (cell_bits < 64) ? (((uint64_t)(s - sa) << cell_bits) | (uint64_t)cell) : (uint64_t)cell;
     const int64_t pos = segs[s].key_off + i;
-    if (idx_bits) {
-      keys[pos] = (key << idx_bits) | (uint64_t)g;
-    } else {
-      keys[pos] = key;
-      vals[pos] = (uint32_t)g;
+    if (live) {
+      if (idx_bits) {
+        keys[pos] = (key << idx_bits) | (uint64_t)g;
+      } else {
+        keys[pos] = key;
+        vals[pos] = (uint32_t)g;
+      }
     }
-  }
-  if (sig && sw >= 0) {
-    uint64_t* dst = sig + (size_t)g * sig_stride + sw;
-    *dst = sig_fresh ? sword : (*dst | sword);
-  }
+    return (uint64_t)grp;
+  };
+  auto words = [&](auto zero) {
+    const int w_lo = t_lo / sig_gpw + (SPLIT ? (int)blockIdx.y * words_per_slice : 0);
+    const int w_end = (t_hi + sig_gpw - 1) / sig_gpw;
+    const int w_hi = SPLIT ? min(w_end, w_lo + words_per_slice) : w_end;
+    for (int x = w_lo; x < w_hi; ++x) {
+      const int ta = max(t_lo, x * sig_gpw), tb = min(t_hi, (x + 1) * sig_gpw);
+      uint64_t word = 0;
+      for (int t = ta + (SPLIT ? w : 0); t < tb; t += SPLIT ? kWaves : 1) {
+        const uint64_t grp = grid(t, zero);
+        if (sig) word |= grp << ((t - x * sig_gpw) * gbits);
+      }
+      if (sig) {
+        // the point owns its row: earlier passes' bits are read back and kept
+        uint64_t* dst = sig + (size_t)g * sig_stride + x;
+        if constexpr (SPLIT) {
+          part[w][lane] = word;
+          __syncthreads();
+          if (w == (x & (kWaves - 1)) && live) {
+#pragma unroll
+            for (int o = 0; o < kWaves; ++o) word |= part[o][lane];
+            *dst = sig_fresh ? word : (*dst | word);
+          }
+          __syncthreads();  // part is rewritten by the next word
+        } else {
+          *dst = sig_fresh ? word : (*dst | word);
+        }
+      }
+    }
+  };
+  if (cell_bits <= 32 && gbits <= 32) words(uint32_t{0});
+  else words(uint64_t{0});
   if (bad) atomicOr(err, 1u);
 }
 
@@ -1181,11 +1230,6 @@ __device__ __forceinline__ bool shared_earlier_cell(const uint64_t* aq, const ui
 // keys carry it, else the separate index array.
 __device__ __forceinline__ uint32_t point_at(const PairsArgs& P, uint32_t p) {
   return P.idx_bits ? (uint32_t)(P.skeys[p] & ((1ull << P.idx_bits) - 1ull)) : P.sidx[p];
-}
-
-template <typename T>
-__device__ __forceinline__ T uniform(T v) {
-  return (T)__builtin_amdgcn_readfirstlane((int)v);
 }
 
 // One tile's data for this lane (lane < n): coordinates, point index and the
@@ -1961,7 +2005,8 @@ __global__ __launch_bounds__(kBlock) void k_query_keys(const QueryArgs A) {
       // last vector register of the wave's allocation reads it as 0 now and
       // then (seen at d = 6 with more than one wave per SIMD), and the loads
       // of these bytes go through vector registers.
-      const int bits = uniform((int)A.layout->bits[j]), shift = uniform((int)A.layout->shift[j]);
+      const uint32_t bits = uniform(layout_byte(A.layout->bits, j));
+      const uint32_t shift = uniform(layout_byte(A.layout->shift, j));
       const uint64_t mask = (1ull << bits) - 1ull;
       cell |= ((uint64_t)(kap - kl[j]) & mask) << shift;
       grp |= ((uint64_t)(kap - kl[j]) & bmask) << (j * A.sig_b);
@@ -3382,11 +3427,34 @@ void launch_stage(const InstDesc* inst, uint32_t m, uint32_t nblocks, int d, int
   hipLaunchKernelGGL(k_bbox_reduce, dim3(m, gy), dim3(kBlock), 0, s, inst, d, part, bbox);
 }
 
+// Point blocks below which the key kernel splits a point's grids over waves.
+// A wave that loops over the grids keeps its point, but too few of them leave
+// the SIMDs idle: 46 -> 8.7 us at 25 blocks (k = 25, d = 6), 81 -> 42 us at
+// 400 (k = 25, d = 9), 19 us either way at 782 (k = 8, d = 6); above, the
+// split's repeated loads show: 10.7 -> 14.0 us at 1172 (k = 6, d = 2),
+// 51 -> 67 us at 3907 (k = 8, d = 6).
+constexpr uint32_t kKeysSplitBlocks = 768;
+
 template <int D>
 static void keys_dispatch(const KeysArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(k_keys<D>, dim3(a.nblocks), dim3(kBlock), 0, s, a.inst, a.m, a.d, a.npts,
-                     a.soa, a.sa, a.sb, a.segs, a.R, a.u, a.klo, a.layout, a.keys, a.vals, a.err,
-                     a.sig, a.sig_stride, a.sig_b, a.sig_gpw, a.idx_bits, a.sig_fresh);
+  // without signatures the "words" only deal grids to the blocks
+  const int gpw = a.sig ? a.sig_gpw : 2 * kWaves;
+  if (a.nblocks < kKeysSplitBlocks) {
+    // words an instance has in this pass at most (one more where the pass
+    // may begin inside a word), over as many slices as fill the chip
+    const int grids = std::min(a.kmax, a.sb - a.sa);
+    const int words = (grids + gpw - 1) / gpw + (a.sig_fresh ? 0 : 1);
+    const int slices = std::min(words, (int)(kKeysSplitBlocks / a.nblocks) + 1);
+    const int per = (words + slices - 1) / slices;
+    hipLaunchKernelGGL((k_keys<D, true>), dim3(a.nblocks * kWaves, slices), dim3(kBlock), 0, s,
+                       a.inst, a.m, a.d, a.npts, a.soa, a.sa, a.sb, a.segs, a.R, a.u, a.klo,
+                       a.layout, a.keys, a.vals, a.err, a.sig, a.sig_stride, a.sig_b, gpw,
+                       a.idx_bits, a.sig_fresh, per);
+    return;
+  }
+  hipLaunchKernelGGL((k_keys<D, false>), dim3(a.nblocks), dim3(kBlock), 0, s, a.inst, a.m, a.d,
+                     a.npts, a.soa, a.sa, a.sb, a.segs, a.R, a.u, a.klo, a.layout, a.keys, a.vals,
+                     a.err, a.sig, a.sig_stride, a.sig_b, gpw, a.idx_bits, a.sig_fresh, 0);
 }
 
 void launch_keys(const KeysArgs& a, hipStream_t s) {

@@ -42,3 +42,18 @@ def test_runs_over_group_and_tile_ends(ctx, n, k):
     cross at every place of the 64-key groups, the waves and the tiles."""
     pts = workloads.uniform_points(n, 2, seed=n)
     _check(ctx, pts, float(np.sqrt(10.0 / n)), k, 2.0, n)
+
+
+@pytest.mark.parametrize("d,alpha", [(2, 2.0), (6, 1.25), (9, 0.9), (20, 2.0), (40, 3.0)])
+@pytest.mark.parametrize("k", [1, 4, 5, 23])
+def test_grids_split_over_waves(ctx, d, alpha, k):
+    """Signature words that end inside, at and past the grids the four waves
+    share, in 32 and 64 bits; a last group of one point."""
+    pts = workloads.uniform_points(321, d, seed=d)
+    _check(ctx, pts, 0.35 * np.sqrt(d / 2.0), k, alpha, d + k)
+
+
+@pytest.mark.parametrize("n", [768 * 256 - 256, 768 * 256 - 255])
+def test_keys_either_side_of_the_split(ctx, n):
+    pts = workloads.uniform_points(n, 3, seed=3)
+    _check(ctx, pts, 0.02, 2, 2.0, 1)
