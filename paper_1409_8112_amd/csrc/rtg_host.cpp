@@ -953,6 +953,11 @@ int alloc_result(Lane& c, int64_t n, size_t nnz, void** res, int64_t** row_ptr, 
   return RTG_OK;
 }
 
+// Buckets of few entries: the per-bucket kernel keeps two blocks on each of
+// 256 CUs, and its fixed steps cost about what 1024 entries do (282e3 entries:
+// 27 buckets of 2^14 took 43 us, 400 smaller ones 12).
+constexpr double kCsrResident = 512.0, kMinBucketEntries = 1024.0;
+
 // Neighbour lists by row buckets (see the bucket kernels): partition the
 // directed entries of the unique pairs into buckets of 2^rb rows, then put
 // each bucket in (row, col) order in LDS and write col and row_ptr; buckets
@@ -972,9 +977,12 @@ int csr_by_buckets(Lane& c, Scratch& S, const Tuning& T, const PairSource& pairs
   // per-bucket blocks more entries per fixed step
   int rb = std::max(0, ceil_log2((uint64_t)n) - 14);
   if ((1 << rb) > kBucketMaxRows) return RTG_ENOMEM;  // callers keep n <= 2^22
+  // (and, of few entries, as large as still gives the chip's CUs two each)
   const double per_row = (double)E / (double)n;
+  const double target = std::min((double)T.bucket_entries,
+                                 std::max(kMinBucketEntries, (double)E / kCsrResident));
   while ((2 << rb) <= kBucketMaxRows && rb + 1 + pb <= 32 &&
-         per_row * (double)(1u << (rb + 1)) <= (double)T.bucket_entries)
+         per_row * (double)(1u << (rb + 1)) <= target)
     ++rb;
   const uint32_t nbuckets = (uint32_t)((n + ((int64_t)1 << rb) - 1) >> rb);
   uint32_t nblocks = (uint32_t)std::max<size_t>(

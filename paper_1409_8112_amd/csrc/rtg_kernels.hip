@@ -2515,19 +2515,30 @@ __device__ __forceinline__ void bucket_range(const uint32_t* __restrict__ offs, 
   cnt = stop - start;
 }
 
-// One block per bucket: put the bucket's entries in row order and write
-// them out as the bucket's part of col and row_ptr.  The input pairs are
+// One block per bucket: put the bucket's entries in (row, column) order and
+// write them out as the bucket's part of col and row_ptr.  The input pairs are
 // unique, so every entry is kept, the bucket's start in the entry array is
 // its start in col, and the columns of a row are distinct.  The block's
-// 1024 threads load the whole bucket into registers at once, count rows
-// (LDS histogram) and scatter the entries by row into LDS.  An entry of a
-// row of at most kShortRow entries takes its place in the row as the number
-// of smaller columns; a longer row is sorted in place by one wave.  Buckets
-// larger than cap or with a row longer than kLongRow are listed in
-// oversized for the caller.
+// 1024 threads load the whole bucket into registers at once and count rows
+// (LDS histogram).  Rows of at most kShortRow entries: the entries are
+// scattered by row into LDS and each takes its place in the row as the number
+// of smaller columns.  Buckets with longer rows go by bins: each row has
+// about a quarter as many bins as entries, each an equal share of the
+// bucket's column range, the entries are scattered in bin order, and an
+// entry's place is its bin's start plus the number of smaller columns in the
+// bin, about four reads whatever the row's length (sorting each long row by a
+// wave's bitonic network took 402 us for 20e6 entries in rows of 190 and 1510
+// for 107e6 in clustered d12, bins 111-120 and 550; for rows of about 20 both
+// ways measure 104 us per 19e6, bound by the LDS, and with few entries per
+// bucket the extra steps cost 36 against 25 us).  A quarter bin per entry,
+// 16 bits each, keeps two blocks on a CU.  Where a bin holds more than
+// kMaxBin entries (long rows whose columns lie together), the short rows are
+// ranked by counting and the longer ones sorted in place by one wave.
+// Buckets larger than cap, and those with such bins and a row longer than
+// kLongRow, are listed in oversized for the caller.
 constexpr uint32_t kLongRow = 1024;
 constexpr uint32_t kShortRow = 64;
-constexpr uint32_t kMaxLongRows = 512;  // long rows per bucket handled in LDS
+constexpr uint32_t kMaxBin = 128;
 
 // Ascending sort of v[0..len) in LDS by one wave (len <= 1024): a bitonic
 // network in its flip form, where every compare-exchange puts the smaller
@@ -2588,17 +2599,26 @@ __device__ __forceinline__ uint32_t csr_block_exclusive_scan(uint32_t v, uint32_
   return before + inc - v;
 }
 
-__global__ __launch_bounds__(kCsrThreads) void k_bucket_csr(
+// Bins of the rows before row r whose entries start at start: every row has
+// at least one.
+__device__ __forceinline__ uint32_t csr_bin_base(uint32_t start, uint32_t r) {
+  return (start >> 2) + r;
+}
+constexpr uint32_t kCsrBins = kBucketMaxEntries / 4 + kBucketMaxRows + 1;
+constexpr int kCsrBinsPer = (int)((kCsrBins + 2 * kCsrThreads - 1) / (2 * kCsrThreads)) * 2;
+
+__global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
     const uint32_t* __restrict__ entries, const uint32_t* __restrict__ offs, uint32_t nbuckets,
     uint32_t nblocks, const uint32_t* __restrict__ total_p, uint32_t* __restrict__ oversized,
     uint32_t* __restrict__ n_oversized, uint32_t cap, int pb, int rb, int64_t n, int64_t nnz,
     int64_t* __restrict__ row_ptr, int32_t* __restrict__ col) {
   __shared__ uint32_t s[kBucketMaxEntries];
-  __shared__ uint32_t rstart[kBucketMaxRows], rcur[kBucketMaxRows];
+  __shared__ uint32_t rstart[kBucketMaxRows + 1];
+  __shared__ uint32_t bins[(kCsrBins + 1) / 2];  // two 16-bit counters a word
   __shared__ uint32_t wsum[kCsrWaves];
-  __shared__ uint32_t s_long, s_nlong;
-  __shared__ uint32_t s_longrows[kMaxLongRows];
+  __shared__ uint32_t s_min, s_max, s_bin, s_long;
   const uint32_t b = blockIdx.x;
+  const uint32_t lane = lane_id();
   if (b == 0 && threadIdx.x == 0) row_ptr[n] = nnz;
   uint32_t start, cnt;
   bucket_range(offs, b, nbuckets, nblocks, *total_p, start, cnt);
@@ -2614,79 +2634,158 @@ __global__ __launch_bounds__(kCsrThreads) void k_bucket_csr(
     const uint32_t i = threadIdx.x + (uint32_t)q * kCsrThreads;
     e_[q] = i < cnt ? entries[start + i] : 0u;
   }
-  for (uint32_t r = threadIdx.x; r < nrows; r += kCsrThreads) rcur[r] = 0u;
+  if (threadIdx.x < nrows) rstart[threadIdx.x] = 0u;
   if (threadIdx.x == 0) {
+    s_min = 0xFFFFFFFFu;
+    s_max = 0u;
+    s_bin = 0u;
     s_long = 0u;
-    s_nlong = 0u;
   }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kCsrItems; ++q)
-    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) atomicAdd(&rcur[e_[q] >> pb], 1u);
+    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) atomicAdd(&rstart[e_[q] >> pb], 1u);
   __syncthreads();
-  // row starts: each thread scans a contiguous run of rows
-  const uint32_t per = (nrows + kCsrThreads - 1) / kCsrThreads;
-  const uint32_t r0 = threadIdx.x * per;
-  uint32_t mine = 0;
-  for (uint32_t r = r0; r < r0 + per && r < nrows; ++r) {
-    mine += rcur[r];
-    if (rcur[r] > kLongRow) s_long = 1u;
-    if (rcur[r] > kShortRow) {
-      const uint32_t q = atomicAdd(&s_nlong, 1u);
-      if (q < kMaxLongRows) s_longrows[q] = r;
-      else s_long = 1u;  // too many long rows: the caller sorts the bucket
+  // row starts (at most one row per thread)
+  static_assert(kBucketMaxRows <= kCsrThreads, "one row per thread");
+  const uint32_t mine = threadIdx.x < nrows ? rstart[threadIdx.x] : 0u;
+  if (mine > kShortRow) atomicOr(&s_long, mine > kLongRow ? 3u : 1u);
+  uint32_t all;
+  const uint32_t run = csr_block_exclusive_scan(mine, wsum, all);
+  if (threadIdx.x < nrows) {
+    rstart[threadIdx.x] = run;
+    bins[threadIdx.x] = run;  // the rows' cursors, when there are no long rows
+    const int64_t row = ((int64_t)b << rb) + threadIdx.x;
+    if (row < n) row_ptr[row] = (int64_t)start + run;
+  }
+  if (threadIdx.x == 0) rstart[nrows] = cnt;
+  __syncthreads();
+  const uint32_t long_rows = s_long;
+  // Each short row's entries, at positions t, t + 1024, ... of the row-ordered
+  // array for thread t: the lanes of a wave cover a few whole rows and read
+  // the same row element at each step (broadcast reads, no bank conflicts).
+  // An entry's place is the number of smaller columns in its row (the row
+  // bits are equal, so whole entries compare as columns).
+  auto rank_short_rows = [&]() {
+#pragma unroll
+    for (int q = 0; q < kCsrItems; ++q) {
+      const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
+      if (x < cnt) {
+        const uint32_t e = s[x];
+        const uint32_t r = e >> pb;
+        const uint32_t lo = rstart[r], hi = rstart[r + 1];
+        if (hi - lo <= kShortRow) {
+          uint32_t rank = lo, y = lo;
+          for (; y + 4 <= hi; y += 4)
+            rank += (s[y] < e ? 1u : 0u) + (s[y + 1] < e ? 1u : 0u) + (s[y + 2] < e ? 1u : 0u) +
+                    (s[y + 3] < e ? 1u : 0u);
+          for (; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
+          col[(size_t)start + rank] = (int32_t)(e & cmask);
+        }
+      }
+    }
+  };
+  if (!long_rows) {
+#pragma unroll
+    for (int q = 0; q < kCsrItems; ++q)
+      if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt)
+        s[atomicAdd(&bins[e_[q] >> pb], 1u)] = e_[q];
+    __syncthreads();
+    rank_short_rows();
+    return;
+  }
+  // Long rows: bins.
+  const uint32_t nbins = csr_bin_base(cnt, nrows);
+  for (uint32_t x = threadIdx.x; x < (nbins + 1) / 2; x += kCsrThreads) bins[x] = 0u;
+  uint32_t cmin = 0xFFFFFFFFu, cmax = 0u;
+#pragma unroll
+  for (int q = 0; q < kCsrItems; ++q)
+    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) {
+      cmin = min(cmin, e_[q] & cmask);
+      cmax = max(cmax, e_[q] & cmask);
+    }
+  wave_minmax_u32(cmin, cmax);
+  if (lane == 0 && cmin <= cmax) {
+    atomicMin(&s_min, cmin);
+    atomicMax(&s_max, cmax);
+  }
+  __syncthreads();
+  // bin of an entry: its column's share of the range, over its row's bins
+  const uint32_t c0 = s_min;
+  const uint32_t scale = 0xFFFFFFFFu / (s_max - c0 + 1u);
+  auto bin_of = [&](uint32_t e) -> uint32_t {
+    const uint32_t r = e >> pb;
+    const uint32_t b0 = csr_bin_base(rstart[r], r), b1 = csr_bin_base(rstart[r + 1], r + 1);
+    return b0 + __umulhi(((e & cmask) - c0) * scale, b1 - b0);
+  };
+#pragma unroll
+  for (int q = 0; q < kCsrItems; ++q)
+    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) {
+      const uint32_t x = bin_of(e_[q]);
+      atomicAdd(&bins[x >> 1], 1u << (16 * (x & 1u)));
+    }
+  __syncthreads();
+  {
+    // bin starts: each thread scans a contiguous run of bins
+    uint32_t v[kCsrBinsPer / 2], sum = 0, most = 0;
+#pragma unroll
+    for (int x = 0; x < kCsrBinsPer / 2; ++x) {
+      const uint32_t at = threadIdx.x * (kCsrBinsPer / 2) + (uint32_t)x;
+      v[x] = 2 * at < nbins ? bins[at] : 0u;
+      const uint32_t a0 = v[x] & 0xFFFFu, a1 = v[x] >> 16;
+      sum += a0 + a1;
+      most = max(most, max(a0, a1));
+    }
+    uint32_t none = 0;
+    wave_minmax_u32(none, most);
+    if (lane == 0 && most > kMaxBin) s_bin = 1u;
+    uint32_t at0 = csr_block_exclusive_scan(sum, wsum, all);
+#pragma unroll
+    for (int x = 0; x < kCsrBinsPer / 2; ++x) {
+      const uint32_t at = threadIdx.x * (kCsrBinsPer / 2) + (uint32_t)x;
+      const uint32_t a0 = v[x] & 0xFFFFu, a1 = v[x] >> 16;
+      if (2 * at < nbins) bins[at] = at0 | ((at0 + a0) << 16);
+      at0 += a0 + a1;
     }
   }
-  uint32_t all;
-  uint32_t run = csr_block_exclusive_scan(mine, wsum, all);
-  for (uint32_t r = r0; r < r0 + per && r < nrows; ++r) {
-    rstart[r] = run;
-    const int64_t row = ((int64_t)b << rb) + r;
-    if (row < n) row_ptr[row] = (int64_t)start + run;
-    run += rcur[r];
-  }
   __syncthreads();
-  if (s_long) {
+  if (s_bin && (long_rows & 2u)) {
     if (threadIdx.x == 0) oversized[atomicAdd(n_oversized, 1u)] = b;
     return;
   }
-  for (uint32_t r = threadIdx.x; r < nrows; r += kCsrThreads) rcur[r] = rstart[r];
-  __syncthreads();
 #pragma unroll
   for (int q = 0; q < kCsrItems; ++q)
-    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) s[atomicAdd(&rcur[e_[q] >> pb], 1u)] = e_[q];
+    if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt) {
+      const uint32_t x = bin_of(e_[q]);
+      const uint32_t old = atomicAdd(&bins[x >> 1], 1u << (16 * (x & 1u)));
+      s[(old >> (16 * (x & 1u))) & 0xFFFFu] = e_[q];
+    }
   __syncthreads();
-  // Short rows: thread t takes the entries at positions t, t + 1024, ... of
-  // the row-ordered array, so the lanes of a wave cover a few whole rows and
-  // read the same row element at each step (broadcast reads, no bank
-  // conflicts).  Each entry's place is the number of smaller columns in its
-  // row (the row bits are equal, so whole entries compare as columns).
+  if (!s_bin) {
+    // A bin's cursor now stands at its end, and so at the next bin's start.
 #pragma unroll
-  for (int q = 0; q < kCsrItems; ++q) {
-    const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
-    if (x < cnt) {
-      const uint32_t e = s[x];
-      const uint32_t r = e >> pb;
-      const uint32_t lo = rstart[r], hi = rcur[r];
-      if (hi - lo <= kShortRow) {
-        uint32_t rank = 0, y = lo;
-        for (; y + 4 <= hi; y += 4)
-          rank += (s[y] < e ? 1u : 0u) + (s[y + 1] < e ? 1u : 0u) + (s[y + 2] < e ? 1u : 0u) +
-                  (s[y + 3] < e ? 1u : 0u);
-        for (; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
-        col[(size_t)start + lo + rank] = (int32_t)(e & cmask);
+    for (int q = 0; q < kCsrItems; ++q) {
+      const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
+      if (x < cnt) {
+        const uint32_t e = s[x];
+        const uint32_t z = bin_of(e);
+        const uint32_t hi = (bins[z >> 1] >> (16 * (z & 1u))) & 0xFFFFu;
+        const uint32_t lo = z ? (bins[(z - 1) >> 1] >> (16 * ((z - 1) & 1u))) & 0xFFFFu : 0u;
+        uint32_t rank = lo;
+        for (uint32_t y = lo; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
+        col[(size_t)start + rank] = (int32_t)(e & cmask);
       }
     }
+    return;
   }
-  // long rows: one wave sorts each in place (the row bits are equal, so the
-  // whole entries order as the columns)
-  const uint32_t nlong = s_nlong;
-  const uint32_t lane = lane_id();
-  for (uint32_t q = threadIdx.x >> 6; q < nlong; q += kCsrWaves) {
-    const uint32_t r = s_longrows[q];
-    const uint32_t lo = rstart[r], len = rcur[r] - lo;
+  rank_short_rows();
+  __syncthreads();  // (the sorts below rewrite only long rows)
+  for (uint32_t r = threadIdx.x >> 6; r < nrows; r += kCsrWaves) {
+    const uint32_t lo = rstart[r], len = rstart[r + 1] - lo;
+    if (len <= kShortRow) continue;
     wave_sort_lds(s + lo, len, lane);
-    for (uint32_t x = lane; x < len; x += 64) col[(size_t)start + lo + x] = (int32_t)(s[lo + x] & cmask);
+    for (uint32_t x = lane; x < len; x += 64)
+      col[(size_t)start + lo + x] = (int32_t)(s[lo + x] & cmask);
   }
 }
 

@@ -57,3 +57,34 @@ def test_grids_split_over_waves(ctx, d, alpha, k):
 def test_keys_either_side_of_the_split(ctx, n):
     pts = workloads.uniform_points(n, 3, seed=3)
     _check(ctx, pts, 0.02, 2, 2.0, 1)
+
+
+def _stars(spokes, contiguous, n=9000, d=8, r=0.1, hubs=3):
+    """Hubs with `spokes` points on the sphere around each, just within r (in
+    d = 8 most of them are farther than r from one another), among far-away
+    points; the spokes' indices together or spread over all."""
+    rng = np.random.default_rng(spokes)
+    pts = rng.random((n, d)) + 10.0
+    at = np.arange(n) if contiguous else rng.permutation(n)
+    for h in range(hubs):
+        ids = at[h * (spokes + 1):(h + 1) * (spokes + 1)]
+        g = rng.standard_normal((spokes, d))
+        g *= 0.999 * r / np.linalg.norm(g, axis=1, keepdims=True)
+        centre = rng.random(d)
+        pts[ids[0]] = centre
+        pts[ids[1:]] = centre + g
+    return pts.astype(np.float32)
+
+
+@pytest.mark.parametrize("spokes", [63, 64, 65, 66, 127, 129, 160, 1023, 1025, 1300])
+@pytest.mark.parametrize("contiguous", [True, False])
+def test_long_rows_in_bins(ctx, spokes, contiguous):
+    """Rows either side of the short-row limit, of a crowded bin and of the
+    longest row a crowded bucket sorts itself."""
+    _check(ctx, _stars(spokes, contiguous), 0.1, 3, 6.0, spokes)
+
+
+@pytest.mark.parametrize("n", [600, 3000, 40000])
+def test_few_entries_in_many_buckets(ctx, n):
+    pts = workloads.uniform_points(n, 4, seed=n)
+    _check(ctx, pts, (6.0 / n) ** 0.25, 4, 2.0, 2)
