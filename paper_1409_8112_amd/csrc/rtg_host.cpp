@@ -472,7 +472,27 @@ int Ctx::hip_fail(hipError_t e, const char* what) {
 
 void* Ctx::dalloc(size_t bytes) {
   std::lock_guard<std::mutex> lk(amu);
-  return arena->alloc(bytes);
+  void* p = arena->alloc(bytes);
+  if (!p && drop_index_extras()) p = arena->alloc(bytes);
+  return p;
+}
+
+// What indexes keep only for speed goes back, except from an index that a
+// query is reading (their kernels have ended: a query waits for its own).
+bool Ctx::drop_index_extras() {
+  bool any = false;
+  for (auto& ix : indexes) {
+    Index& I = *ix.second;
+    if (I.in_use) continue;
+    for (void* p : {(void*)I.rows, (void*)I.tab})
+      if (p) {
+        arena->release(p);
+        any = true;
+      }
+    I.rows = nullptr;
+    I.tab = nullptr;
+  }
+  return any;
 }
 
 void* Ctx::dalloc_noalloc(size_t bytes) {
@@ -544,6 +564,8 @@ int Ctx::release_many(const uint64_t* handles, int32_t count) {
         continue;
       }
       for (void* p : ix->second->blocks) arena->release(p);
+      for (void* p : {(void*)ix->second->rows, (void*)ix->second->tab})
+        if (p) arena->release(p);
       indexes.erase(ix);
       any = true;
     }
@@ -2760,6 +2782,19 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
                            (uint64_t)(t - sa), idx_bits, 0};
   }
   if ((rc = upload(I.grids, grids.data(), sizeof(QueryGrid) * grids.size()))) return rc;
+  // About four keys per table entry, and the coordinates in grid order: a
+  // query reads its cells' members in runs (pairs of 1e6 queries, n = 1e6,
+  // d = 3: 1.0 ms, 2.0 by point index; the copy takes 0.12 ms here).  Neither
+  // is needed, so they take at most a sixteenth of what is free.
+  const size_t spare = ctx->largest_free() / 16;
+  I.tab_bits = std::min(I.P.layout.cell_bits, std::max(1, pair_bits - 2));
+  const size_t tab_bytes = sizeof(uint32_t) * (size_t)k * (((size_t)1 << I.tab_bits) + 1);
+  const size_t row_bytes = sizeof(float) * (size_t)k * n * d;
+  if (I.tab_bits > 0 && tab_bytes <= spare) I.tab = static_cast<uint32_t*>(dalloc(tab_bytes));
+  if (I.tab) launch_query_table(I.grids, k, n, I.P.layout.cell_bits, I.tab_bits, I.tab, stream);
+  if (query_rows_fit(d) && row_bytes + tab_bytes <= spare)
+    I.rows = static_cast<float*>(dalloc(row_bytes));
+  if (I.rows) launch_query_rows(I.grids, k, n, d, I.pts, I.rows, stream);
   uint32_t errh = 0;
   if ((rc = read_back(err, sizeof(errh), &errh))) return rc;
   if (errh & 1u) return RTG_ERANGE;
@@ -2767,8 +2802,19 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
   return RTG_OK;
 }
 
+// Queries from which a call orders them by place (their cell under grid 0, on
+// up to 24 bits: three sort passes).  The order costs about 45 us; without
+// it every cell's keys and coordinates come from HBM for each query.  At
+// 65536 queries both ways measure the same (258 against 256 us at n = 1e6,
+// d = 3; 633 against 778 at d = 6; 181 / 175 and 494 / 501 us at n = 5e4),
+// below it the order loses (158 / 117 us at 16384), at 1e6 queries of 1e6
+// points, d = 3, pairs and search take 4.2 ms without and 1.04 with it (1.17
+// on 16 bits).
+constexpr int64_t kQueryOrderMin = 65536;
+constexpr int kQueryOrderBits = 24;
+
 int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats& st,
-                      rtg_csr* out) {
+                      rtg_csr* out, bool extras) {
   int rc;
   if (m == 0 || I.n == 0) return make_empty_result(m, out, 0);
   kstats = &st;
@@ -2783,11 +2829,16 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
   Scratch S(*this);
   const int k = I.k, d = I.d;
   uint64_t* qkey = S.get<uint64_t>((size_t)m * k);
+  uint32_t* qlo = S.get<uint32_t>((size_t)m * k);
   uint64_t* qsig = S.get<uint64_t>((size_t)m * I.sig_W);
-  uint32_t* err = S.get<uint32_t>(2);
-  unsigned long long* counter = S.get<unsigned long long>(1);
-  if (!qkey || !qsig || !err || !counter) return RTG_ENOMEM;
-  launch_fill_u32(err, 0u, 2, stream);
+  // the output segments' counts, then a filter's count and the error bits
+  // ([0] the queries', [1] the list build's)
+  constexpr uint32_t kWords = kCandSegments + 2;
+  unsigned long long* counts = S.get<unsigned long long>(kWords);
+  if (!qkey || !qlo || !qsig || !counts) return RTG_ENOMEM;
+  unsigned long long* counter = counts + kCandSegments;
+  uint32_t* err = reinterpret_cast<uint32_t*>(counter + 1);
+  launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kWords, stream);
   QueryArgs A{};
   A.queries = queries;
   A.m = m;
@@ -2803,6 +2854,9 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
   A.grids = I.grids;
   A.n = I.n;
   A.pts = I.pts;
+  A.rows = extras ? I.rows : nullptr;
+  A.tab = extras ? I.tab : nullptr;
+  A.tab_bits = I.tab_bits;
   A.sig = I.sig;
   A.W = I.sig_W;
   A.sig_b = I.sig_b;
@@ -2811,36 +2865,86 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
   A.lows = I.lows;
   A.highs = I.highs;
   A.qkey = qkey;
+  A.qlo = qlo;
   A.qsig = qsig;
   A.err = err;
   A.pb = std::max(1, ceil_log2((uint64_t)std::max<int64_t>(I.n, m)));
-  launch_query_keys(A, stream);
-  uint32_t errh = 0;
-  if ((rc = read_back(err, sizeof(errh), &errh))) return rc;
-  if (errh & 2u) return RTG_EINVAL;
-  if (errh & 1u) return RTG_ERANGE;
+  const PairTest pt = make_pair_test(A.r2, A.pb, d, I.alpha * I.r);
+  A.lo = pt.lo;
+  A.hi = pt.hi;
+  A.cand_count = counts;
+  // Queries in the order of their place: those that read the same cells run
+  // side by side, so the cells come from the caches.  (Without room the
+  // queries run as given.)
+  if (m >= kQueryOrderMin) {
+    const int bits = std::min(A.cell_bits, kQueryOrderBits);
+    uint64_t* o1 = S.get<uint64_t>((size_t)m);
+    uint64_t* o2 = o1 ? S.get<uint64_t>((size_t)m) : nullptr;
+    void* scr = o2 ? S.get<char>(radix_scratch_bytes((size_t)m, 32, 32 + bits)) : nullptr;
+    if (scr) {
+      launch_query_order(A, bits, o1, stream);
+      A.order = radix_sort(o1, nullptr, o2, nullptr, (size_t)m, 32, 32 + bits, scr, err, stream,
+                           nullptr, 0, 0, kSortReduceScan)
+                    ? o2
+                    : o1;
+    }
+  }
+  launch_query_find(A, stream);
 
-  // pairs (query, point); room from a guess, the exact count on overflow
-  uint64_t cap = std::max<uint64_t>(1u << 20, (uint64_t)m * 32);
-  uint64_t* cand = nullptr;
-  uint64_t C = 0;
-  for (int attempt = 0; attempt < 2; ++attempt) {
-    if (cand) S.drop(cand);
-    cand = S.get<uint64_t>(cap);
-    if (!cand) return RTG_ENOMEM;
-    launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 0ull, 1, stream);
+  // pairs (query, point) in output segments; room from a guess, the exact
+  // counts on overflow (one segment where that is all that fits)
+  const int pb = A.pb;
+  const bool bucket_rows = pb <= 24 && ceil_log2((uint64_t)m) <= 22 &&
+                           ceil_log2((uint64_t)m) - 14 + pb <= 32;
+  const uint64_t guess = std::max<uint64_t>(1u << 20, (uint64_t)m * 32);
+  A.nseg = kCandSegments;
+  A.cap = guess / A.nseg + guess / (4 * A.nseg) + 1024;
+  uint64_t* cand = S.get<uint64_t>(A.nseg * A.cap);
+  if (!cand) {
+    A.cap = guess / A.nseg;
+    cand = S.get<uint64_t>(A.nseg * A.cap);
+  }
+  if (!cand) return RTG_ENOMEM;
+  uint64_t C = 0, most = 0;
+  for (int attempt = 0;; ++attempt) {
     A.cand = cand;
-    A.cap = cap;
-    A.cand_count = counter;
     kbegin(RTG_K_PAIRS);
     launch_query_pairs(A, stream);
     kend(RTG_K_PAIRS, 0.0);
-    unsigned long long cnt = 0;
-    if ((rc = read_back(counter, sizeof(cnt), &cnt))) return rc;
-    C = cnt;
-    if (C <= cap) break;
-    if (attempt == 1) return RTG_ENOMEM;
-    cap = C;
+    unsigned long long got[kWords];
+    if ((rc = read_back(counts, sizeof(got), got))) return rc;
+    const uint32_t errh = (uint32_t)got[kWords - 1];
+    if (errh & 2u) return RTG_EINVAL;
+    if (errh & 1u) return RTG_ERANGE;
+    C = most = 0;
+    for (uint32_t g = 0; g < A.nseg; ++g) {
+      C += got[g];
+      most = std::max<uint64_t>(most, got[g]);
+    }
+    if (most <= A.cap) break;
+    if (attempt == 2) return RTG_ENOMEM;
+    S.drop(cand);
+    A.cap = most;
+    cand = S.get<uint64_t>(A.nseg * A.cap);
+    if (!cand) {
+      A.nseg = 1;
+      A.cap = C;
+      cand = S.get<uint64_t>(C);
+    }
+    if (!cand) return RTG_ENOMEM;
+    launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kCandSegments, stream);
+  }
+  // The row-bucket lists read the segments as they are; the filter and the
+  // sorted build take one array.
+  const bool segments = A.nseg > 1 && !I.sub && bucket_rows && C < (1ull << 32) && C > 0;
+  if (!segments && A.nseg > 1 && C > 0) {
+    uint64_t* flat = S.get<uint64_t>(C);
+    if (!flat) return RTG_ENOMEM;
+    kbegin(RTG_K_COMPACT);
+    launch_seg_compact(cand, A.cap, counts, A.nseg, most, flat, stream);
+    kend(RTG_K_COMPACT, 16.0 * (double)C);
+    S.drop(cand);
+    cand = flat;
   }
   if (I.sub && C > 0) {
     // MR-metric: keep the Euclidean candidates within r under the MR-metric
@@ -2849,7 +2953,6 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
     uint64_t* kept = S.get<uint64_t>(C);
     if (!mi_d || !kept) return RTG_ENOMEM;
     if ((rc = upload(mi_d, &mi, sizeof(mi)))) return rc;
-    launch_fill_u64(reinterpret_cast<uint64_t*>(counter), 0ull, 1, stream);
     MrFilterArgs fa{cand, C, A.pb, d, queries, I.pts, mi_d, 1, kept, counter};
     kbegin(RTG_K_COMPACT);
     launch_mr_filter(fa, stream);
@@ -2870,21 +2973,20 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
   int64_t* row_ptr = nullptr;
   int32_t* col = nullptr;
   size_t nnz = 0;
-  const int pb = A.pb;
-  const bool bucket_ok = pb <= 24 && ceil_log2((uint64_t)m) <= 22 &&
-                         ceil_log2((uint64_t)m) - 14 + pb <= 32 && C < (1ull << 32);
+  const bool bucket_ok = bucket_rows && C < (1ull << 32);
+  bool drained = false;  // the list build's read-back came after its last kernel
   if (C == 0) {
     if ((rc = alloc_result(*this, m, 0, &res, &row_ptr, &col))) return rc;
     launch_fill_u64(reinterpret_cast<uint64_t*>(row_ptr), 0ull, (size_t)(m + 1), stream);
   } else if (bucket_ok) {
-    if ((rc = csr_by_buckets(*this, S, ctx->defaults, PairSource{cand}, C, m, pb, false, err + 1,
-                             nullptr, &res, &row_ptr, &col, &nnz)))
+    const PairSource src = segments ? PairSource{cand, counts, A.cap, A.nseg} : PairSource{cand};
+    if ((rc = csr_by_buckets(*this, S, ctx->defaults, src, C, m, pb, false, err + 1, nullptr, &res,
+                             &row_ptr, &col, &nnz, nullptr, &drained)))
       return rc;
   } else {
     uint64_t* alt = S.get<uint64_t>(C);
     void* scr = S.get<char>(radix_scratch_bytes(C, 0, 2 * pb));
     if (!alt || !scr) return RTG_ENOMEM;
-    launch_fill_u32(err + 1, 0u, 1, stream);
     const int where = radix_sort(cand, nullptr, alt, nullptr, C, 0, 2 * pb, scr, err + 1, stream,
                                  nullptr, 0, 0, ctx->defaults.sort_algo);
     nnz = C;
@@ -2895,10 +2997,11 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
       return rc;
     }
   }
-  if ((rc = sync())) {
+  if (!drained && (rc = sync())) {
     dfree(res);
     return rc;
   }
+  S.drained = drained;
   out->n = m;
   out->nnz = (int64_t)nnz;
   out->row_ptr = row_ptr;
@@ -3024,6 +3127,8 @@ int rtg_index_build(rtg_ctx* ctx, const float* points, int64_t n, int32_t d, dou
   if (rc) {
     (void)hipStreamSynchronize(c->main.stream);
     for (void* p : I->blocks) c->dfree(p);
+    for (void* p : {(void*)I->rows, (void*)I->tab})
+      if (p) c->dfree(p);
     return rc;
   }
   const uint64_t h = c->new_handle();
@@ -3041,7 +3146,7 @@ int rtg_index_query(rtg_ctx* ctx, uint64_t index, const float* queries, int64_t 
   Ctx* c = reinterpret_cast<Ctx*>(ctx);
   std::lock_guard<std::mutex> lk(c->mu);
   if (c->poisoned) return RTG_EDEVICE;
-  const rtg::Index* I = nullptr;
+  rtg::Index* I = nullptr;
   {
     std::lock_guard<std::mutex> alk(c->amu);
     auto it = c->indexes.find(index);
@@ -3056,7 +3161,22 @@ int rtg_index_query(rtg_ctx* ctx, uint64_t index, const float* queries, int64_t 
   st.n = m;
   st.d = I->d;
   st.k = I->k;
-  const int rc = c->main.query_index(*I, queries, m, st, out);
+  auto in_use = [&](bool v) {
+    std::lock_guard<std::mutex> alk(c->amu);
+    I->in_use = v;
+  };
+  in_use(true);
+  int rc = c->main.query_index(*I, queries, m, st, out, true);
+  in_use(false);
+  // out of memory beside what the index keeps for speed: once more without it
+  if (rc == RTG_ENOMEM && (I->rows || I->tab)) {
+    (void)hipStreamSynchronize(c->main.stream);
+    {
+      std::lock_guard<std::mutex> alk(c->amu);
+      c->drop_index_extras();
+    }
+    rc = c->main.query_index(*I, queries, m, st, out, false);
+  }
   if (!rc) c->stats = st;
   return rc;
 }

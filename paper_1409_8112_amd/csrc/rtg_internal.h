@@ -365,19 +365,37 @@ struct QueryArgs {
   const QueryGrid* grids;   // [k]
   int64_t n;                // indexed points
   const float* pts;         // [n][d] indexed points
-  const uint64_t* sig;      // [n][W] their signatures (null: no first-owner rule)
+  const float* rows;        // [k][n][d] their coordinates by grid position (null: by index)
+  const uint32_t* tab;      // [k][2^tab_bits + 1] first positions by top cell bits (null: none)
+  int tab_bits;
+  const uint64_t* sig;      // [n][W] their signatures
   int W, sig_b, g, gpw;
   uint64_t lows, highs;
+  float lo, hi;             // the FP32 screen of r2 (see PairTest)
+  const uint64_t* order;    // [m] queries by place, the index in the low 32 bits (null: as given)
+  // by place in the order:
   uint64_t* qkey;           // [m][k] cell prefix of each query under each grid
+  uint32_t* qlo;            // [m][k] and the cell's first position
   uint64_t* qsig;           // [m][W] signature words of each query
   uint32_t* err;            // bit 0: a cell coordinate out of range, bit 1: not finite
   int pb;                   // bits of an index in a packed (query, point) pair
-  uint64_t* cand;
+  uint32_t lanes;           // lanes per query (set by launch_query_pairs)
+  uint64_t* cand;           // nseg output segments of cap pairs each (see PairsArgs)
   uint64_t cap;
+  uint32_t nseg;
   unsigned long long* cand_count;
 };
-void launch_query_keys(const QueryArgs& a, hipStream_t s);
+// order[q] = the top bits (at most 32) of query q's cell under grid 0, above q.
+void launch_query_order(const QueryArgs& a, int bits, uint64_t* order, hipStream_t s);
+void launch_query_find(const QueryArgs& a, hipStream_t s);
 void launch_query_pairs(const QueryArgs& a, hipStream_t s);
+// What an index keeps beside its keys where memory allows: rows (dimensions
+// query_rows_fit takes) and tab of QueryArgs.
+bool query_rows_fit(int d);
+void launch_query_rows(const QueryGrid* grids, int k, int64_t n, int d, const float* pts,
+                       float* rows, hipStream_t s);
+void launch_query_table(const QueryGrid* grids, int k, int64_t n, int cell_bits, int tab_bits,
+                        uint32_t* tab, hipStream_t s);
 
 // spts / ssig for the positions of every unit, from the batch rows and the
 // per-point signatures sig [npts][W] (ssig untouched when sig is null).

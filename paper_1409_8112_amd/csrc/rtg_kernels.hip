@@ -352,11 +352,38 @@ __device__ __forceinline__ uint32_t layout_byte(const uint8_t* __restrict__ byte
   return (v >> (8 * (j & 3))) & 0xFFu;
 }
 
+// The packed cell fields and signature group of one point under one transform
+// (rows Rt, shifts ut, field origins kl); false if a cell coordinate is out of
+// range.  The point is p (D > 0) or soa[l n + i], l < d.  C holds both results
+// (fields are taken modulo their width, at most 32 bits, so 32-bit differences
+// are exact).
+template <int D, typename C>
+__device__ __forceinline__ bool pack_cell(const double* __restrict__ Rt,
+                                          const double* __restrict__ ut,
+                                          const int64_t* __restrict__ kl,
+                                          const KeyLayout* __restrict__ layout, const float* p,
+                                          const float* __restrict__ soa, int64_t n, int64_t i,
+                                          int d, double inv_c, int sig_b, C& cell, C& grp) {
+  const uint32_t bmask = (uint32_t)((1ull << sig_b) - 1ull);
+  bool all_ok = true;
+  cell = grp = 0;
+  for (int j = 0; j < d; ++j) {
+    const double y = cell_y<D>(Rt + (size_t)j * d, p, soa, n, i, d, inv_c, ut[j]);
+    const bool ok = fabs(y) < 2147483648.0;
+    all_ok = all_ok && ok;
+    // |y| < 2^31: the floor fits 32 bits, and one native conversion takes it
+    const uint32_t f = (uint32_t)(ok ? (int32_t)floor(y) : 0) - (uint32_t)kl[j];
+    const uint32_t mask = (uint32_t)((1ull << layout_byte(layout->bits, j)) - 1ull);
+    cell |= (C)(f & mask) << layout_byte(layout->shift, j);
+    grp |= (C)(f & bmask) << (j * sig_b);
+  }
+  return all_ok;
+}
+
 // Writes the keys of the points' segments in [sa, sb): key = (segment - sa)
 // << cell_bits | packed cell, at segs[segment].key_off + the point's index in
 // its instance.  The work is one FP64 dot product per axis and the packing of
-// its floor; packed in 32 bits when cell and signature group fit (fields are
-// taken modulo their width, at most 32 bits, so 32-bit differences are exact):
+// its floor; packed in 32 bits when cell and signature group fit:
 // 61 -> 51 us for 8e6 keys at d = 6, 537 -> 507 us for 32e6 at d = 12.
 // SPLIT = false: one thread per batch point, all of its grids.  SPLIT = true:
 // a block takes 64 points, its four waves every fourth grid of a signature
@@ -401,7 +428,6 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
     for (int l = 0; l < (D > 0 ? D : 1); ++l) p[l] = soa[(int64_t)l * npts + g];
   }
   const int cell_bits = layout->cell_bits;
-  const uint32_t bmask = (uint32_t)((1ull << sig_b) - 1ull);
   const int gbits = d * sig_b;
   bool bad = false;
   // one grid's key (stored) and signature group (returned)
@@ -413,16 +439,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
     const double* ut = u + (size_t)tr * d;
     const int64_t* kl = klo + (size_t)tr * d;
     C cell = 0, grp = 0;
-    for (int j = 0; j < d; ++j) {
-      const double y = cell_y<D>(Rt + (size_t)j * d, p, soa, npts, g, d, inv_c, ut[j]);
-      const bool ok = fabs(y) < 2147483648.0;
-      bad |= !ok;
-      // |y| < 2^31: the floor fits 32 bits, and one native conversion takes it
-      const uint32_t f = (uint32_t)(ok ? (int32_t)floor(y) : 0) - (uint32_t)kl[j];
-      const uint32_t mask = (uint32_t)((1ull << layout_byte(layout->bits, j)) - 1ull);
-      cell |= (C)(f & mask) << layout_byte(layout->shift, j);
-      grp |= (C)(f & bmask) << (j * sig_b);
-    }
+    bad |= !pack_cell<D>(Rt, ut, kl, layout, p, soa, npts, g, d, inv_c, sig_b, cell, grp);
     const uint64_t key =
         (cell_bits < 64) ? (((uint64_t)(s - sa) << cell_bits) | (uint64_t)cell) : (uint64_t)cell;
     const int64_t pos = segs[s].key_off + i;
@@ -1960,77 +1977,10 @@ k_cell_pairs_gram(
 // with the indexed points of that cell within r, once (first-owner rule with
 // the query's own signature).
 
-// Cell prefix (segment and packed cell fields) of every query under every
-// grid, and the query's signature words.  One thread per query.
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_query_keys(const QueryArgs A) {
-  const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (q >= A.m) return;
-  const int d = D > 0 ? D : A.d;
-  float p[D > 0 ? D : 1];
-  bool finite = true;
-  if (D > 0) {
-#pragma unroll
-    for (int l = 0; l < (D > 0 ? D : 1); ++l) p[l] = A.queries[q * d + l];
-  }
-  for (int l = 0; l < d; ++l) finite = finite && isfinite(A.queries[q * d + l]);
-  if (!finite) {
-    atomicOr(A.err, 2u);
-    return;
-  }
-  const uint64_t bmask = (1ull << A.sig_b) - 1ull;
-  uint64_t sword = 0;
-  int sw = -1;
-  bool bad = false;
-  for (int t = 0; t < A.k; ++t) {
-    const double* Rt = A.R + (size_t)t * d * d;
-    const double* ut = A.u + (size_t)t * d;
-    const int64_t* kl = A.klo + (size_t)t * d;
-    uint64_t cell = 0, grp = 0;
-    for (int j = 0; j < d; ++j) {
-      // same operation order as the points' keys (the key kernel)
-      double z;
-      if (D > 0) {
-        z = Rt[(size_t)j * d] * (double)p[0];
-        for (int l = 1; l < d; ++l) z = z + Rt[(size_t)j * d + l] * (double)p[l];
-      } else {
-        z = Rt[(size_t)j * d] * (double)A.queries[q * d];
-        for (int l = 1; l < d; ++l) z = z + Rt[(size_t)j * d + l] * (double)A.queries[q * d + l];
-      }
-      const double y = z * A.inv_c + ut[j];
-      const bool ok = fabs(y) < 2147483648.0;
-      bad |= !ok;
-      const int64_t kap = ok ? (int64_t)(int32_t)floor(y) : 0;
-      // Widths and offsets as scalars: a 64-bit shift whose amount lies in the
-      // last vector register of the wave's allocation reads it as 0 now and
-      // then (seen at d = 6 with more than one wave per SIMD), and the loads
-      // of these bytes go through vector registers.
-      const uint32_t bits = uniform(layout_byte(A.layout->bits, j));
-      const uint32_t shift = uniform(layout_byte(A.layout->shift, j));
-      const uint64_t mask = (1ull << bits) - 1ull;
-      cell |= ((uint64_t)(kap - kl[j]) & mask) << shift;
-      grp |= ((uint64_t)(kap - kl[j]) & bmask) << (j * A.sig_b);
-    }
-    const uint64_t prefix = A.cell_bits < 64 ? ((A.grids[t].seg << A.cell_bits) | cell) : cell;
-    A.qkey[(size_t)q * A.k + t] = prefix;
-    if (A.sig) {
-      const int w = t / A.gpw;
-      if (w != sw) {
-        if (sw >= 0) A.qsig[(size_t)q * A.W + sw] = sword;
-        sword = 0;
-        sw = w;
-      }
-      sword |= grp << ((t - w * A.gpw) * A.g);
-    }
-  }
-  if (A.sig && sw >= 0) A.qsig[(size_t)q * A.W + sw] = sword;
-  if (bad) atomicOr(A.err, 1u);
-}
-
-// First position in keys[0..n) whose cell prefix is >= K.
-__device__ __forceinline__ uint32_t prefix_lower_bound(const uint64_t* keys, uint32_t n, int shift,
+// First position in keys[lo..hi) whose cell prefix is >= K.
+__device__ __forceinline__ uint32_t prefix_lower_bound(const uint64_t* __restrict__ keys,
+                                                       uint32_t lo, uint32_t hi, int shift,
                                                        uint64_t K) {
-  uint32_t lo = 0, hi = n;
   while (lo < hi) {
     const uint32_t mid = lo + ((hi - lo) >> 1);
     if ((keys[mid] >> shift) < K) lo = mid + 1;
@@ -2039,9 +1989,141 @@ __device__ __forceinline__ uint32_t prefix_lower_bound(const uint64_t* keys, uin
   return lo;
 }
 
-// Pairs (query, indexed point): one wave per query; lane t finds grid t's
-// cell by binary search, then the wave tests that cell's members.
+// The cell prefix of a grid's keys: its segment above the packed cell.
+__device__ __forceinline__ uint64_t query_prefix(const QueryGrid& G, int cell_bits, uint64_t cell) {
+  return cell_bits < 64 ? ((G.seg << cell_bits) | cell) : cell;
+}
+
+// tab[t][x] = the first position of grid t whose cell's top tab_bits bits are
+// at least x, for x <= 2^tab_bits.
+__global__ __launch_bounds__(kBlock) void k_query_table(const QueryGrid* __restrict__ grids, int k,
+                                                        uint32_t n, int cell_bits, int tab_bits,
+                                                        uint32_t* __restrict__ tab) {
+  const uint32_t size = 1u << tab_bits;
+  const uint32_t x = blockIdx.x * kBlock + threadIdx.x;
+  const int t = (int)blockIdx.y;
+  if (x > size) return;
+  const QueryGrid G = grids[t];
+  tab[(size_t)t * (size + 1) + x] =
+      x == size ? n
+                : prefix_lower_bound(G.keys, 0, n, G.idx_bits,
+                                     query_prefix(G, cell_bits, (uint64_t)x << (cell_bits - tab_bits)));
+}
+
+// rows[t][p] = the coordinates of the point at position p of grid t.
 template <int D>
+__global__ __launch_bounds__(kBlock) void k_query_rows(const QueryGrid* __restrict__ grids, int64_t n,
+                                                       const float* __restrict__ pts,
+                                                       float* __restrict__ rows) {
+  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (p >= n) return;
+  const QueryGrid G = grids[blockIdx.y];
+  const uint32_t i = G.idx_bits ? (uint32_t)(G.keys[p] & ((1ull << G.idx_bits) - 1ull)) : G.idx[p];
+  const float* src = pts + (size_t)i * D;
+  float* dst = rows + ((size_t)blockIdx.y * n + p) * D;
+  float v[D];
+#pragma unroll
+  for (int l = 0; l < D; ++l) v[l] = src[l];
+#pragma unroll
+  for (int l = 0; l < D; ++l) dst[l] = v[l];
+}
+
+// order[q] = the top `bits` bits of the query's cell under grid 0 above its
+// index: sorted on those bits, queries of one place come together.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_query_order(
+    const QueryArgs A, const double* __restrict__ R, const double* __restrict__ u,
+    const int64_t* __restrict__ klo, const KeyLayout* __restrict__ layout, int bits,
+    uint64_t* __restrict__ order) {
+  const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (q >= A.m) return;
+  const int d = D > 0 ? D : A.d;
+  float p[D > 0 ? D : 1];
+  if (D > 0) {
+#pragma unroll
+    for (int l = 0; l < (D > 0 ? D : 1); ++l) p[l] = A.queries[q * d + l];
+  }
+  uint64_t cell, grp;
+  (void)pack_cell<D>(R, u, klo, layout, p, A.queries, 1, q * d, d, A.inv_c, A.sig_b, cell, grp);
+  order[q] = ((cell >> (A.cell_bits - bits)) << 32) | (uint64_t)q;
+}
+
+// Of every query under every grid: the cell prefix, and the position in the
+// grid where that cell begins (n for a query that is not finite or out of
+// range); and the query's signature words.  A block takes 64 queries, its
+// four waves every fourth grid of a signature word.  The binary search is a
+// chain of dependent reads: tab cuts its first steps (n = 1e6, d = 3: about
+// four instead of twenty).
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_query_find(
+    const QueryArgs A, const double* __restrict__ R, const double* __restrict__ u,
+    const int64_t* __restrict__ klo, const KeyLayout* __restrict__ layout,
+    const QueryGrid* __restrict__ grids, const uint32_t* __restrict__ tab,
+    uint64_t* __restrict__ qkey, uint32_t* __restrict__ qlo, uint64_t* __restrict__ qsig) {
+  __shared__ uint64_t part[kWaves][64];
+  const uint32_t lane = lane_id();
+  const int w = uniform((int)(threadIdx.x >> 6));
+  const int d = D > 0 ? D : A.d;
+  const int64_t at_ = (int64_t)blockIdx.x * 64 + lane;  // place in the order
+  const bool live = at_ < A.m;
+  const int64_t at = live ? at_ : A.m - 1;
+  const int64_t q = A.order ? (int64_t)(uint32_t)A.order[at] : at;
+  float p[D > 0 ? D : 1];
+  if (D > 0) {
+#pragma unroll
+    for (int l = 0; l < (D > 0 ? D : 1); ++l) p[l] = A.queries[q * d + l];
+  }
+  bool finite = true;
+  for (int l = 0; l < d; ++l) finite = finite && isfinite(D > 0 ? p[D > 0 ? l : 0] : A.queries[q * d + l]);
+  bool bad = false;
+  const uint32_t n = (uint32_t)A.n;
+  for (int x = 0; x < A.W; ++x) {
+    uint64_t word = 0;
+    const int tb = min(A.k, (x + 1) * A.gpw);
+    for (int t = x * A.gpw + w; t < tb; t += kWaves) {
+      uint64_t cell, grp;
+      const bool ok = pack_cell<D>(R + (size_t)t * d * d, u + (size_t)t * d, klo + (size_t)t * d,
+                                   layout, p, A.queries, 1, q * d, d, A.inv_c, A.sig_b, cell, grp);
+      bad |= !ok;
+      word |= grp << ((t - x * A.gpw) * A.g);
+      const QueryGrid G = grids[t];
+      const uint64_t K = query_prefix(G, A.cell_bits, cell);
+      uint32_t lo = 0, hi = n;
+      if (tab) {
+        const uint32_t* tt = tab + (size_t)t * ((1u << A.tab_bits) + 1u);
+        const uint32_t top = (uint32_t)(cell >> (A.cell_bits - A.tab_bits));
+        lo = tt[top];
+        hi = tt[top + 1];
+      }
+      lo = prefix_lower_bound(G.keys, lo, hi, G.idx_bits, K);
+      if (live) {
+        qkey[(size_t)at * A.k + t] = K;
+        qlo[(size_t)at * A.k + t] = finite && ok ? lo : n;
+      }
+    }
+    part[w][lane] = word;
+    __syncthreads();
+    if (w == (x & (kWaves - 1)) && live) {
+#pragma unroll
+      for (int o = 0; o < kWaves; ++o) word |= part[o][lane];
+      qsig[(size_t)at * A.W + x] = word;
+    }
+    __syncthreads();  // part is rewritten by the next word
+  }
+  if (!finite) atomicOr(A.err, 2u);
+  else if (bad) atomicOr(A.err, 1u);
+}
+
+// Pairs (query, indexed point).  A.lanes lanes of a wave take a query and
+// walk the members of its cell under each grid together, from the cell's
+// first position while the keys' prefix is the cell's: the cells are short
+// (some tens of points), so a whole wave per query idled most of its lanes
+// and waited on every cell's chain of loads.  Few queries get more lanes
+// each, many get four, which is what fills the chip (see
+// launch_query_pairs; 1e6 queries took 6.9 ms, now 0.9).  ROWS: the coordinates come from the index's copy in
+// grid order, so that neighbouring lanes read one line; else by point index.
+// The screen is the vector pair screen's: FP32 with FP64 in the band.
+template <int D, bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
   __shared__ uint64_t sOut[kWaves][kOutBuf];
   const uint32_t lane = lane_id();
@@ -2051,76 +2133,98 @@ __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
   P.cand = A.cand;
   P.cap = A.cap;
   P.cand_count = A.cand_count;
+  P.nseg = A.nseg;
   OutStage O = out_stage(P, sOut[w]);
   const uint32_t n = (uint32_t)A.n;
-  const int64_t wave_id = (int64_t)blockIdx.x * kWaves + w;
+  const uint32_t G = A.lanes, sub = lane & (G - 1u);
+  const int64_t per_wave = 64 / G;
   const int64_t nwaves = (int64_t)gridDim.x * kWaves;
-  for (int64_t q = wave_id; q < A.m; q += nwaves) {
-    double qc[D > 0 ? D : 1];
+  for (int64_t q0 = ((int64_t)blockIdx.x * kWaves + w) * per_wave; q0 < A.m;
+       q0 += nwaves * per_wave) {
+    const int64_t at_ = q0 + lane / G;  // place in the order
+    const bool live = at_ < A.m;
+    const int64_t at = live ? at_ : A.m - 1;
+    const int64_t q = A.order ? (int64_t)(uint32_t)A.order[at] : at;
+    float qc[D > 0 ? D : 1];
     if (D > 0) {
 #pragma unroll
-      for (int l = 0; l < (D > 0 ? D : 1); ++l) qc[l] = (double)A.queries[q * d + l];
+      for (int l = 0; l < (D > 0 ? D : 1); ++l) qc[l] = A.queries[q * d + l];
     }
-    uint64_t qw[kSigWords] = {0ull, 0ull};
-    if (A.sig)
+    uint64_t qw[kSigWords];
 #pragma unroll
-      for (int x = 0; x < kSigWords; ++x) qw[x] = x < A.W ? A.qsig[(size_t)q * A.W + x] : 0ull;
-    for (int t0 = 0; t0 < A.k; t0 += 64) {
-      // lane t: the range of grid t0 + t
-      uint32_t rlo = 0, rhi = 0;
-      const int tl = t0 + (int)lane;
-      if (tl < A.k) {
-        const uint64_t K = A.qkey[(size_t)q * A.k + tl];
-        const uint64_t* keys = A.grids[tl].keys;
-        const int sh = A.grids[tl].idx_bits;
-        rlo = prefix_lower_bound(keys, n, sh, K);
-        rhi = rlo;
-        while (rhi < n && (keys[rhi] >> sh) == K && rhi - rlo < 8u) ++rhi;
-        if (rhi < n && (keys[rhi] >> sh) == K)
-          rhi = K == ~0ull ? n : prefix_lower_bound(keys + rhi, n - rhi, sh, K + 1ull) + rhi;
-      }
-      const int tn = min(64, A.k - t0);
-      for (int tt = 0; tt < tn; ++tt) {
-        const int t = t0 + tt;
-        const uint32_t lo = lane_value(rlo, tt);
-        const uint32_t hi = lane_value(rhi, tt);
-        const QueryGrid G = A.grids[t];
-        const uint64_t imask = G.idx_bits ? ((1ull << G.idx_bits) - 1ull) : 0ull;
-        for (uint32_t base = lo; base < hi; base += 64) {
-          const uint32_t pos = base + lane;
-          bool hit = false;
-          uint32_t i = 0;
-          if (pos < hi) {
-            i = G.idx_bits ? (uint32_t)(G.keys[pos] & imask) : G.idx[pos];
-            const float* row = A.pts + (size_t)i * d;
+    for (int x = 0; x < kSigWords; ++x) qw[x] = x < A.W ? A.qsig[(size_t)at * A.W + x] : 0ull;
+    for (int t = 0; t < A.k; ++t) {
+      const QueryGrid g = A.grids[t];
+      const uint64_t K = A.qkey[(size_t)at * A.k + t];
+      uint32_t pos = live ? A.qlo[(size_t)at * A.k + t] + sub : n;  // (n < 2^31)
+      // the key and coordinates at a position, loaded one step ahead
+      uint64_t key, key_next;
+      float c[D > 0 ? D : 1], c_next[D > 0 ? D : 1];
+      const float* rows = ROWS ? A.rows + (size_t)t * A.n * D : nullptr;
+      auto load = [&](uint32_t p, uint64_t& kk, float* cc) {
+        const uint32_t x = min(p, n - 1u);
+        kk = g.keys[x];
+        if constexpr (D > 0 && ROWS) {
+          const float* row = rows + (size_t)x * D;
+#pragma unroll
+          for (int l = 0; l < D; ++l) cc[l] = row[l];
+        }
+      };
+      load(pos, key, c);
+      for (;;) {
+        const bool in = pos < n && (key >> g.idx_bits) == K;
+        if (!ballot(in)) break;
+        load(pos + G, key_next, c_next);
+        uint32_t i = 0;
+        if (!(D > 0 && ROWS) && in)
+          i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
+        float d2 = 0.0f;
+        const float* row = (D > 0 && ROWS) ? c : A.pts + (size_t)i * d;
+        if (D > 0) {
+#pragma unroll
+          for (int l = 0; l < (D > 0 ? D : 1); ++l) {
+            const float df = qc[l] - row[l];
+            d2 = __builtin_fmaf(df, df, d2);
+          }
+        } else {
+          for (int l = 0; l < d; ++l) {
+            const float df = A.queries[q * d + l] - row[l];
+            d2 = __builtin_fmaf(df, df, d2);
+          }
+        }
+        bool hit = in && d2 <= A.hi;
+        if (hit) {
+          if (d2 > A.lo) {
+            // the band: as the definition decides
             double s2 = 0.0;
-            if (D > 0) {
-#pragma unroll
-              for (int l = 0; l < (D > 0 ? D : 1); ++l) {
-                const double dl = qc[l] - (double)row[l];
-                s2 = s2 + dl * dl;
-              }
-            } else {
-              for (int l = 0; l < d; ++l) {
-                const double dl = (double)A.queries[q * d + l] - (double)row[l];
-                s2 = s2 + dl * dl;
-              }
+            for (int l = 0; l < d; ++l) {
+              const double dl = (double)(D > 0 ? qc[D > 0 ? l : 0] : A.queries[q * d + l]) -
+                                (double)row[l];
+              s2 = s2 + dl * dl;
             }
             hit = s2 <= A.r2;
-            if (hit && A.sig && t > 0) {
-              // dropped if an earlier grid put the query and the point in one cell
-              const int nw = (t - 1) / A.gpw + 1;
-              for (int x = 0; x < nw && hit; ++x) {
-                const uint64_t xw =
-                    (x < kSigWords ? qw[x] : A.qsig[(size_t)q * A.W + x]) ^ A.sig[(size_t)i * A.W + x];
-                const int ng = min(A.gpw, t - x * A.gpw);
-                const uint64_t keep = (ng * A.g >= 64) ? ~0ull : ((1ull << (ng * A.g)) - 1ull);
-                hit = (((xw - A.lows) & ~xw & A.highs) & keep) == 0ull;
-              }
+          }
+          if (D > 0 && ROWS)
+            i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
+          if (t > 0) {
+            // dropped if an earlier grid put the query and the point in one cell
+            const int nw = (t - 1) / A.gpw + 1;
+            for (int x = 0; x < nw && hit; ++x) {
+              const uint64_t xw =
+                  (x == 0 ? qw[0] : x == 1 ? qw[1] : A.qsig[(size_t)at * A.W + x]) ^
+                  A.sig[(size_t)i * A.W + x];
+              const int ng = min(A.gpw, t - x * A.gpw);
+              const uint64_t keep = (ng * A.g >= 64) ? ~0ull : ((1ull << (ng * A.g)) - 1ull);
+              hit = (((xw - A.lows) & ~xw & A.highs) & keep) == 0ull;
             }
           }
-          const uint64_t pair = ((uint64_t)q << A.pb) | i;
-          emit_pairs(P, O, lane, hit ? 1ull : 0ull, [&](int) { return pair; });
+        }
+        append_pair(P, O, lane, hit, ((uint64_t)q << A.pb) | i);
+        pos += G;
+        key = key_next;
+        if constexpr (D > 0 && ROWS) {
+#pragma unroll
+          for (int l = 0; l < D; ++l) c[l] = c_next[l];
         }
       }
     }
@@ -3840,27 +3944,84 @@ void launch_gather_units(const PairsArgs& a, const uint64_t* sig, float* spts, u
 #undef RTG_GATHER
 }
 
-void launch_query_keys(const QueryArgs& a, hipStream_t s) {
-  if (a.m <= 0) return;
-  const unsigned blocks = (unsigned)((a.m + kBlock - 1) / kBlock);
-#define RTG_QK(DD) hipLaunchKernelGGL(k_query_keys<DD>, dim3(blocks), dim3(kBlock), 0, s, a)
-  switch (a.d) {
-    case 1: RTG_QK(1); break;
-    case 2: RTG_QK(2); break;
-    case 3: RTG_QK(3); break;
-    case 4: RTG_QK(4); break;
-    case 5: RTG_QK(5); break;
-    case 6: RTG_QK(6); break;
-    case 7: RTG_QK(7); break;
-    case 8: RTG_QK(8); break;
-    case 9: RTG_QK(9); break;
-    case 10: RTG_QK(10); break;
-    case 11: RTG_QK(11); break;
-    case 12: RTG_QK(12); break;
-    case 16: RTG_QK(16); break;
-    default: RTG_QK(0); break;
+// Dimensions with their own query kernels; the others read coordinates one
+// by one.
+#define RTG_QUERY_DIMS(X) \
+  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(16)
+
+bool query_rows_fit(int d) { return (d >= 1 && d <= 12) || d == 16; }
+
+void launch_query_rows(const QueryGrid* grids, int k, int64_t n, int d, const float* pts,
+                       float* rows, hipStream_t s) {
+  const dim3 grid(grid_for((size_t)n), (unsigned)k);
+  switch (d) {
+#define RTG_QR(DD) \
+  case DD: hipLaunchKernelGGL(k_query_rows<DD>, grid, dim3(kBlock), 0, s, grids, n, pts, rows); break;
+    RTG_QUERY_DIMS(RTG_QR)
+#undef RTG_QR
   }
-#undef RTG_QK
+}
+
+void launch_query_table(const QueryGrid* grids, int k, int64_t n, int cell_bits, int tab_bits,
+                        uint32_t* tab, hipStream_t s) {
+  hipLaunchKernelGGL(k_query_table, dim3(grid_for(((size_t)1 << tab_bits) + 1), (unsigned)k),
+                     dim3(kBlock), 0, s, grids, k, (uint32_t)n, cell_bits, tab_bits, tab);
+}
+
+void launch_query_order(const QueryArgs& a, int bits, uint64_t* order, hipStream_t s) {
+  const unsigned blocks = grid_for((size_t)a.m);
+#define RTG_QO(DD)                                                                               \
+  hipLaunchKernelGGL(k_query_order<DD>, dim3(blocks), dim3(kBlock), 0, s, a, a.R, a.u, a.klo,    \
+                     a.layout, bits, order)
+  switch (a.d) {
+#define RTG_QO_CASE(DD) \
+  case DD: RTG_QO(DD); break;
+    RTG_QUERY_DIMS(RTG_QO_CASE)
+#undef RTG_QO_CASE
+    default: RTG_QO(0);
+  }
+#undef RTG_QO
+}
+
+void launch_query_find(const QueryArgs& a, hipStream_t s) {
+  if (a.m <= 0 || a.n <= 0) return;
+  const unsigned blocks = (unsigned)((a.m + 63) / 64);
+#define RTG_QF(DD)                                                                             \
+  hipLaunchKernelGGL(k_query_find<DD>, dim3(blocks), dim3(kBlock), 0, s, a, a.R, a.u, a.klo,   \
+                     a.layout, a.grids, a.tab, a.qkey, a.qlo, a.qsig)
+  switch (a.d) {
+#define RTG_QF_CASE(DD) \
+  case DD: RTG_QF(DD); break;
+    RTG_QUERY_DIMS(RTG_QF_CASE)
+#undef RTG_QF_CASE
+    default: RTG_QF(0);
+  }
+#undef RTG_QF
+}
+
+void launch_query_pairs(const QueryArgs& args, hipStream_t s) {
+  if (args.m <= 0 || args.n <= 0) return;
+  QueryArgs a = args;
+  // lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
+  // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; few queries get as many as
+  // give the chip 2^18 lanes
+  a.lanes = 4;
+  while (a.lanes < 64 && (uint64_t)a.m * a.lanes < (1u << 18)) a.lanes *= 2;
+  uint64_t blocks = ((uint64_t)a.m * a.lanes + kBlock - 1) / kBlock;
+  if (blocks > 4096) blocks = 4096;
+#define RTG_QP(DD, RR) \
+  hipLaunchKernelGGL((k_query_pairs<DD, RR>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a)
+  switch (a.d) {
+#define RTG_QP_CASE(DD)          \
+  case DD:                       \
+    if (a.rows) RTG_QP(DD, true); \
+    else RTG_QP(DD, false);      \
+    break;
+    RTG_QUERY_DIMS(RTG_QP_CASE)
+#undef RTG_QP_CASE
+    default: RTG_QP(0, false);
+  }
+#undef RTG_QP
 }
 
 void launch_seg_compact(const uint64_t* src, uint64_t seg_cap, const unsigned long long* cnt,
@@ -3886,30 +4047,6 @@ void launch_mr_filter(const MrFilterArgs& a, hipStream_t s) {
 void launch_bitmap_unique(const BitmapArgs& a, hipStream_t s) {
   if (a.count == 0) return;
   hipLaunchKernelGGL(k_bitmap_unique, dim3(compact_blocks(a.count)), dim3(kBlock), 0, s, a);
-}
-
-void launch_query_pairs(const QueryArgs& a, hipStream_t s) {
-  if (a.m <= 0 || a.n <= 0) return;
-  uint64_t blocks = ((uint64_t)a.m + kWaves - 1) / kWaves;
-  if (blocks > 4096) blocks = 4096;
-#define RTG_QP(DD) hipLaunchKernelGGL(k_query_pairs<DD>, dim3((unsigned)blocks), dim3(kBlock), 0, s, a)
-  switch (a.d) {
-    case 1: RTG_QP(1); break;
-    case 2: RTG_QP(2); break;
-    case 3: RTG_QP(3); break;
-    case 4: RTG_QP(4); break;
-    case 5: RTG_QP(5); break;
-    case 6: RTG_QP(6); break;
-    case 7: RTG_QP(7); break;
-    case 8: RTG_QP(8); break;
-    case 9: RTG_QP(9); break;
-    case 10: RTG_QP(10); break;
-    case 11: RTG_QP(11); break;
-    case 12: RTG_QP(12); break;
-    case 16: RTG_QP(16); break;
-    default: RTG_QP(0); break;
-  }
-#undef RTG_QP
 }
 
 template <int D>

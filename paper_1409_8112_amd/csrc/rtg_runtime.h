@@ -137,6 +137,13 @@ struct Index {
   rtgk::KeyLayout* layout = nullptr;
   rtgk::QueryGrid* grids = nullptr;  // device [k]
   std::vector<void*> blocks;         // arena blocks the index owns
+  // Kept where memory allows and given back when an allocation would fail
+  // otherwise (Ctx::dalloc): the points' coordinates in grid order and the
+  // first positions by top cell bits (see rtgk::QueryArgs).
+  float* rows = nullptr;
+  uint32_t* tab = nullptr;
+  int tab_bits = 0;
+  bool in_use = false;               // a query reads them (under the context's amu)
 };
 
 // Launch settings of one pass (rtg_tuning in rtg.h): the context's
@@ -237,7 +244,7 @@ struct Lane {
   int build_index(const float* points, int64_t n, int32_t d, double r, int32_t k, double alpha,
                   const double* R, const double* u, Index& I);
   int query_index(const Index& I, const float* queries, int64_t m, rtg_stats& st,
-                  rtg_csr* out);
+                  rtg_csr* out, bool extras);
   int tiny_query(const float* points, int64_t n, int32_t d, rtg_csr* out, uint64_t handle);
   // One pass of the pipeline over a batch of instances of one dimension
   // (pp: the pass of a plan, or null).
@@ -307,6 +314,7 @@ struct Ctx {
 
   int hip_fail(hipError_t e, const char* what);
   void* dalloc(size_t bytes);
+  bool drop_index_extras();             // (under amu) true if any memory came back
   void* dalloc_noalloc(size_t bytes);   // from the no-allocation arena
   size_t largest_free_noalloc();
   void dfree(void* p);                  // to whichever arena holds p

@@ -23,3 +23,54 @@ def test_many_queries_every_row(d, r):
     R, u = rtg.make_transforms(seed, k, d)
     ref = oracle.rtg_query(pts, qs, r, alpha, R, u)
     assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+
+
+def _query(ctx, index, qs):
+    import torch
+    res = ctx.index_query(index, torch.from_numpy(qs).cuda())
+    got = res.to_numpy()
+    res.release()
+    return got
+
+
+@pytest.mark.parametrize("d", [2, 6, 13])
+@pytest.mark.parametrize("m", [1, 4095, 4096, 65535, 65536, 65537])
+def test_lanes_and_order_thresholds(d, m):
+    """Either side of the sizes where queries take fewer lanes each and where
+    they are ordered by place; a dimension without kernels of its own."""
+    import torch
+    from paper_1409_8112_amd import rtg
+    k, alpha, seed = 3, 2.0, 4
+    r = {2: 0.03, 6: 0.35, 13: 0.8}[d]
+    pts = workloads.uniform_points(1501, d, seed=7)
+    qs = workloads.uniform_points(m, d, seed=8)
+    qs[:min(m, 100)] = pts[:min(m, 100)]
+    with rtg.Context(0, arena_bytes=2 << 30) as ctx:
+        index = ctx.index_build(torch.from_numpy(pts).cuda(), r, k, alpha, seed)
+        rp, col = _query(ctx, index, qs)
+    ref = oracle.rtg_query(pts, qs, r, alpha, *rtg.make_transforms(seed, k, d))
+    assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+
+
+def test_index_extras_give_way():
+    """The index's tables go back when other calls need the memory; its
+    queries and theirs then run as without them."""
+    import torch
+    from paper_1409_8112_amd import rtg
+    k, alpha, seed, r = 8, 2.0, 4, 0.02
+    pts = workloads.uniform_points(30000, 3, seed=7)
+    qs = workloads.uniform_points(70000, 3, seed=8)
+    ref = oracle.rtg_query(pts, qs, r, alpha, *rtg.make_transforms(seed, k, 3))
+    dev = torch.from_numpy(pts).cuda()
+    with rtg.Context(0, arena_bytes=160 << 20) as ctx:
+        index = ctx.index_build(dev, r, k, alpha, seed)
+        rp, col = _query(ctx, index, qs)
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+        held = []
+        with pytest.raises(rtg.RTGError) as e:
+            for _ in range(2000):
+                held.append(ctx.all_pairs(dev, 0.03, k, alpha, seed))
+        assert e.value.code == rtg.ENOMEM
+        ctx.release_many(held)
+        rp, col = _query(ctx, index, qs)
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
