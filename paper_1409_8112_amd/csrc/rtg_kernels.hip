@@ -1249,8 +1249,8 @@ __device__ __forceinline__ uint32_t point_at(const PairsArgs& P, uint32_t p) {
   return P.idx_bits ? (uint32_t)(P.skeys[p] & ((1ull << P.idx_bits) - 1ull)) : P.sidx[p];
 }
 
-// One tile's data for this lane (lane < n): coordinates, point index and the
-// first signature words.
+// One tile's data for this lane: coordinates, point index and the first
+// signature words.  Lanes past the tile's end hold its last point.
 template <int D>
 struct TileRegs {
   float c[D];
@@ -1258,25 +1258,34 @@ struct TileRegs {
   uint64_t sw[kSigWords];
 };
 
+// Every lane loads a whole point, no lane or coordinate tested on its own: a
+// row's loads then merge into a few wide ones (a test per coordinate made
+// each a masked 4-byte gather: at d = 12 the tiles' loads took half of the
+// L1's time; clustered d12 pairs 8.70 -> 7.22 ms, uniform d6 532 -> 509 us).  D <= 16 is the dimension itself; wider D are
+// padded with zeros.
 template <int D>
 __device__ __forceinline__ void load_tile(const PairsArgs& P, uint32_t p0, uint32_t n, int nw,
                                           uint32_t lane, TileRegs<D>& R) {
-  const bool ok = lane < n;
-  const uint32_t p = p0 + lane;
-  R.idx = ok ? point_at(P, p) : 0u;
+  const uint32_t p = p0 + min(lane, n - 1u);  // (n >= 1)
+  R.idx = point_at(P, p);
   if (P.direct) {
     const float* row = P.rows + (size_t)R.idx * P.row_stride;
+    if constexpr (D <= 16) {
 #pragma unroll
-    for (int l = 0; l < D; ++l) R.c[l] = (ok && l < P.d) ? row[l] : 0.0f;
+      for (int l = 0; l < D; ++l) R.c[l] = row[l];
+    } else {
+#pragma unroll
+      for (int l = 0; l < D; ++l) R.c[l] = l < P.d ? row[l] : 0.0f;
+    }
 #pragma unroll
     for (int q = 0; q < kSigWords; ++q)
-      R.sw[q] = (ok && q < nw) ? P.sigp[(size_t)R.idx * P.sig_stride + q] : 0ull;
+      R.sw[q] = q < nw ? P.sigp[(size_t)R.idx * P.sig_stride + q] : 0ull;
   } else {
 #pragma unroll
-    for (int l = 0; l < D; ++l) R.c[l] = (ok && l < P.d) ? P.spts[(size_t)l * P.N + p] : 0.0f;
+    for (int l = 0; l < D; ++l)
+      R.c[l] = (D <= 16 || l < P.d) ? P.spts[(size_t)l * P.N + p] : 0.0f;
 #pragma unroll
-    for (int q = 0; q < kSigWords; ++q)
-      R.sw[q] = (ok && q < nw) ? P.ssig[(size_t)q * P.N + p] : 0ull;
+    for (int q = 0; q < kSigWords; ++q) R.sw[q] = q < nw ? P.ssig[(size_t)q * P.N + p] : 0ull;
   }
 }
 
@@ -1452,7 +1461,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
   __shared__ uint64_t sOut[kWaves][kOutBuf];
 
   const uint32_t lane = lane_id();
-  const int w = threadIdx.x >> 6;
+  const int w = uniform((int)(threadIdx.x >> 6));  // (a scalar: so are the unit loops)
   unsigned long long nre = 0;
   OutStage O = out_stage(P, sOut[w]);
 
@@ -1676,11 +1685,14 @@ __device__ __forceinline__ void gram_operands(const float* row, float (&op)[2][K
   }
 }
 
-// Four waves per SIMD up to D = 9 (at most 128 registers: a few spills at
-// D = 9 cost less than the lost wave); three above, where the registers the
-// wider rows need would spill more.
+// Four waves per SIMD up to D = 12 (at most 128 registers), three above.  The
+// wave's index is read as a scalar, so the units and the tile loops live in
+// scalar registers (in vector registers they took up to 40 of them, spills
+// and masked branches: uniform d6 509 -> 488 us, study d9 661 -> 625).  A
+// fifth wave (96 registers, no spills) changes nothing: vector and matrix
+// instructions together keep the SIMDs 86-91% busy.
 template <int D>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(D <= 9 ? 4 : 3))) void
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(D <= 12 ? 4 : 3))) void
 k_cell_pairs_gram(
     const PairsArgs P) {
   constexpr int KA = (D + 3) & ~1;  // augmented row length, even
@@ -1697,7 +1709,7 @@ k_cell_pairs_gram(
 
   const uint32_t lane = lane_id();
   const uint32_t l32 = lane & 31u, h = lane >> 5;
-  const int w = threadIdx.x >> 6;
+  const int w = uniform((int)(threadIdx.x >> 6));  // (a scalar: so are the unit loops)
   uint64_t (*sAw)[kPairTile] = reinterpret_cast<uint64_t (*)[kPairTile]>(sAreg[w]);
   uint64_t (*sBw)[kPairTile] = reinterpret_cast<uint64_t (*)[kPairTile]>(sBreg[w]);
   unsigned long long nre = 0;
@@ -1843,12 +1855,17 @@ k_cell_pairs_gram(
             if (all_fp64) {
               // every pair of real points is decided in FP64; the padding
               // rows and columns of a short tile hold no points
+              // (nA through an opaque copy: its 16 compares would otherwise be
+              // hoisted out of this rare branch and paid by every row)
+              uint32_t rows_in = nA;
+              asm volatile("" : "+s"(rows_in));
               const bool col_in = 32u * (uint32_t)C + l32 < nB;
               uint32_t in = 0u;
 #pragma unroll
               for (int i = 0; i < 16; ++i)
                 in = (in << 1) |
-                     ((col_in && 32u * (uint32_t)R + mfma32_row((uint32_t)i, lane) < nA) ? 1u : 0u);
+                     ((col_in && 32u * (uint32_t)R + mfma32_row((uint32_t)i, lane) < rows_in) ? 1u
+                                                                                             : 0u);
               cm = in;
               am = 0u;
             }
