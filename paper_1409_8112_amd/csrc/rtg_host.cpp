@@ -457,7 +457,7 @@ Tuning Ctx::tuning_for(int d, int64_t npts) {
 
 Ctx::~Ctx() {
   stop_server();
-  for (auto& L : side) L->fini();
+  drop_side_lanes();
   if (side_ready) (void)hipEventDestroy(side_ready);
   main.fini();
   if (own_arena && arena_mem) (void)hipFree(arena_mem);
@@ -612,8 +612,6 @@ int Lane::init(Ctx* c, hipStream_t s, bool create_stream) {
   if (hipEventCreateWithFlags(&up_done, hipEventDisableTiming) != hipSuccess) return RTG_EDEVICE;
   if (hipHostMalloc((void**)&mail, kMailBytes + 256) != hipSuccess) return RTG_EDEVICE;
   mail[0] = 0;
-  gather_dev = c->dalloc(64);
-  if (!gather_dev) return RTG_ENOMEM;
   for (auto& e : ev)
     if (hipEventCreate(&e) != hipSuccess) return RTG_EDEVICE;
   return RTG_OK;
@@ -633,8 +631,6 @@ void Lane::fini() {
     if (e) (void)hipEventDestroy(e);
   for (auto& e : kev) (void)hipEventDestroy(e);
   kev.clear();
-  if (gather_dev && ctx) ctx->dfree(gather_dev);
-  gather_dev = nullptr;
   if (own_stream) (void)hipStreamDestroy(stream);
   own_stream = false;
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
@@ -2293,6 +2289,11 @@ int Ctx::side_lanes(int count) {
   return RTG_OK;
 }
 
+void Ctx::drop_side_lanes() {
+  for (auto& L : side) L->fini();
+  side.clear();
+}
+
 // Adds the counts and times of b to a (widths: the larger).
 static void add_stats(rtg_stats& a, const rtg_stats& b) {
   a.cells += b.cells;
@@ -2439,10 +2440,16 @@ int Ctx::batched(const rtg_query* q, int32_t nq, rtg_csr* outs,
       });
     work(main, st);
     for (auto& t : threads) t.join();
-    // The extra lanes go with the call: their streams would otherwise keep
-    // hardware queues (a few per process) that the request loop's lanes need.
-    for (auto& L : side) L->fini();
-    side.clear();
+    // The extra lanes stay for the next call (making and freeing their streams
+    // and pinned buffers took 0.5 ms of a 2 ms batch of 32 instances), unless
+    // the request loop runs: its lanes need the hardware queues, a few per
+    // process, that their streams would hold.  Every pass has drained them.
+    bool serving;
+    {
+      std::lock_guard<std::mutex> slk(server_mu);
+      serving = server != nullptr;
+    }
+    if (serving) drop_side_lanes();
     for (const auto& s2 : sst) add_stats(st, s2);
     for (int r : brc)
       if (r != RTG_OK && r != RTG_ENOMEM && r != kNotRun) return undo(r);

@@ -204,7 +204,6 @@ struct Lane {
   size_t host_up_bytes = 0;
   hipEvent_t up_done = nullptr;  // recorded after the last batched upload's copy
   bool up_pending = false;
-  void* gather_dev = nullptr;  // 8 device u64 that gather_back fills
   // Pinned mailbox of the read-backs: a sequence word, then kMailBytes of
   // values (see wait_mail).
   static constexpr size_t kMailBytes = 64 << 10;
@@ -297,12 +296,14 @@ struct Ctx {
   Lane main;          // the caller's stream: blocking calls
   // More lanes for rtg_all_pairs_batched: batches run batch_lanes at a time
   // (the caller's lane and batch_lanes - 1 more), so one pass's host work and
-  // waits overlap the others' kernels (RTG_BATCH_LANES, 1 to 3).  Made for
-  // each call that has several batches and released at its end.
+  // waits overlap the others' kernels (RTG_BATCH_LANES, 1 to 3).  Made by the
+  // first call that has several batches and kept for the next (under mu),
+  // until the request loop starts.
   int batch_lanes = 3;
   std::vector<std::unique_ptr<Lane>> side;
   hipEvent_t side_ready = nullptr;  // the caller's stream reached the call
   int side_lanes(int count);
+  void drop_side_lanes();
   rtg_stats stats{};  // of the last blocking call
   std::mutex mu;      // one blocking call at a time
   std::mutex amu;     // arena, results, handles

@@ -88,3 +88,37 @@ def test_long_rows_in_bins(ctx, spokes, contiguous):
 def test_few_entries_in_many_buckets(ctx, n):
     pts = workloads.uniform_points(n, 4, seed=n)
     _check(ctx, pts, (6.0 / n) ** 0.25, 4, 2.0, 2)
+
+
+def test_batches_around_the_request_loop():
+    """Batched calls in several passes before, while and after requests are
+    served: their extra streams are kept from call to call and given up to
+    the loop."""
+    import torch
+    from paper_1409_8112_amd import rtg
+    with rtg.Context(0, arena_bytes=2 << 30) as c:
+        queries, refs = [], []
+        for q in range(9):
+            n, d = 700 + 301 * q, (2, 3, 6)[q % 3]
+            pts = workloads.uniform_points(n, d, seed=q)
+            r = {2: 0.05, 3: 0.1, 6: 0.4}[d]
+            queries.append(dict(points=torch.from_numpy(pts).cuda(), r=r, k=3, alpha=2.0, seed=q))
+            refs.append(oracle.rtg(pts, r, 3, 2.0, q))
+
+        def batch():
+            res = c.all_pairs_batched(queries)
+            for x, ref in zip(res, refs):
+                rp, col = x.to_numpy()
+                assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+            c.release_many(res)
+
+        batch()
+        batch()
+        tickets = [c.submit(q["points"], q["r"], q["k"], q["alpha"], q["seed"]) for q in queries]
+        batch()
+        for t, ref in zip(tickets, refs):
+            x = c.wait(t)
+            rp, col = x.to_numpy()
+            assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+            x.release()
+        batch()
