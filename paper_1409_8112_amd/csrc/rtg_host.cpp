@@ -300,9 +300,20 @@ size_t Ctx::pass_bytes_bound(int64_t n, int32_t d, int32_t k, double alpha, uint
   return (size_t)bytes;
 }
 
+// Hashed keys: from six radix passes on (clustered d12: 64 bits, eight passes
+// with values beside the keys), three passes of plain keys instead.  A hash of
+// h bits adds about n^2 / 2^(h + 1) tests per grid, 0.5e6 of 1.6e9 at
+// n = 4e6, and the check of the accepted pairs' cells costs the pair kernel
+// 5%: sort 2.15 -> 0.66 ms, pairs 7.19 -> 7.54, a call 12.25 -> 11.18 (on 32
+// bits, a pass more, 11.33).  At five passes the two are even (uniform d12
+// requests).  Below 2^20 keys a pass is its launches' time and the exact keys
+// stay, with their band per cell.
+constexpr int kHashBits = 24, kHashAbove = 40;
+constexpr int64_t kHashKeys = int64_t(1) << 20;
+
 int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const double* R,
                const double* u, const double* inv_c, const double* alpha, const float* lo,
-               const float* hi, size_t budget_bytes, Packing& P) {
+               const float* hi, size_t budget_bytes, bool may_hash, Packing& P) {
   int64_t S_total = 0, nmax = 0, elems_all = 0;
   for (uint32_t q = 0; q < m; ++q) {
     S_total += k[q];
@@ -347,6 +358,13 @@ int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const doub
   if (bmin > 32) return RTG_ERANGE;
   for (int j = 0; j < d; ++j) need[j] = std::max(need[j], bmin);
 
+  // Cells wider than four radix passes' bits, in a large batch: kHashBits bits
+  // of a hash of the cell (the pair kernels then check the cells of the pairs
+  // they accept, so a collision only adds tests).
+  int exact_bits = 0;
+  for (int j = 0; j < d; ++j) exact_bits += need[j];
+  const bool hash = may_hash && exact_bits > kHashAbove && elems_all >= kHashKeys;
+
   // Segments per pass: as many as the key bits, the 32-bit element index of
   // the sort and the memory budget allow.
   int64_t tb = S_total;
@@ -354,8 +372,7 @@ int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const doub
     const int seg_bits = tb > 1 ? ceil_log2((uint64_t)tb) : 0;
     const int avail = 64 - seg_bits;
     std::vector<int> b = need;
-    int total = 0;
-    for (int j = 0; j < d; ++j) total += b[j];
+    int total = hash ? kHashBits : exact_bits;
     // Narrow the widest fields first, never below bmin.
     while (total > avail) {
       int jw = -1;
@@ -373,8 +390,9 @@ int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const doub
       P.seg_bits = seg_bits;
       P.layout.d = d;
       P.layout.cell_bits = total;
+      P.layout.hashed = hash ? total : 0;
       int sh = 0;
-      P.truncated = false;
+      P.truncated = hash;  // (cells may share a key)
       for (int j = 0; j < d; ++j) {
         P.layout.shift[j] = (uint8_t)sh;
         P.layout.bits[j] = (uint8_t)b[j];
@@ -1576,7 +1594,7 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
       ks[q] = jobs[q]->k;
     }
     rc = plan_batch(d, m, ks.data(), ns.data(), Rh.data(), uh.data(), inv_cs.data(),
-                    alphas.data(), lo.data(), hi.data(), largest_free() / 2, P);
+                    alphas.data(), lo.data(), hi.data(), largest_free() / 2, first_owner, P);
     if (rc) return rc;
   }
   st.key_bits = std::max(st.key_bits, P.key_bits);
@@ -1931,6 +1949,7 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
         pa.lows |= 1ull << (z * sig_g);
         pa.highs |= 1ull << (z * sig_g + sig_g - 1);
       }
+      if (P.layout.hashed) pa.same_cell = sig_g < 64 ? (1ull << sig_g) - 1ull : ~0ull;
     }
     // the unit points' coordinates and signature words by sorted position
     if (!pa.direct) {
@@ -2709,7 +2728,7 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
   }
   const int64_t kk = k, nn = n;
   if ((rc = plan_batch(d, 1, &kk, &nn, R, u, &one.inv_c, &alpha, lo.data(), hi.data(),
-                       ctx->largest_free() / 2, I.P)))
+                       ctx->largest_free() / 2, false, I.P)))
     return rc;
   if ((rc = upload(I.layout, &I.P.layout, sizeof(KeyLayout)))) return rc;
   if ((rc = upload(I.klo, I.P.klo.data(), sizeof(int64_t) * I.P.klo.size()))) return rc;

@@ -18,7 +18,8 @@ constexpr int kMaxDim = 64;
 // Where each axis of a cell vector sits in the packed 64-bit key.
 struct KeyLayout {
   int32_t d;
-  int32_t cell_bits;           // sum of bits[] (segment id sits above)
+  int32_t cell_bits;           // sum of bits[] (segment id sits above), or hashed
+  int32_t hashed;              // > 0: the key holds that many bits of a hash of the cell
   uint8_t shift[kMaxDim];      // bit offset of axis j
   uint8_t bits[kMaxDim];       // width of axis j
 };
@@ -273,6 +274,9 @@ struct PairsArgs {
   const PairTest* tests;   // per instance
   int W, g, gpw;           // signature layout
   uint64_t lows, highs;    // lowest and highest bit of each signature group
+  // nonzero: keys are hashes, so a unit may mix cells; the bits of a pair's
+  // first signature group, which must agree under the unit's own grid
+  uint64_t same_cell;
   uint64_t* cand;
   uint64_t cap;            // entries per segment
   unsigned long long *cand_count, *rechecks;  // cand_count: [nseg]

@@ -352,12 +352,22 @@ __device__ __forceinline__ uint32_t layout_byte(const uint8_t* __restrict__ byte
   return (v >> (8 * (j & 3))) & 0xFFu;
 }
 
+// A multiplier of axis j in hash h (0 or 1): 24 bits, odd.
+__device__ __forceinline__ constexpr uint32_t hash_weight(int j, int h) {
+  uint32_t x = (uint32_t)(2 * j + h + 1) * 0x9E3779B1u;
+  x = (x ^ (x >> 15)) * 0x9E3779B1u;
+  x ^= x >> 13;
+  return (x & 0xFFFFFFu) | 1u;
+}
+
 // The packed cell fields and signature group of one point under one transform
 // (rows Rt, shifts ut, field origins kl); false if a cell coordinate is out of
 // range.  The point is p (D > 0) or soa[l n + i], l < d.  C holds both results
 // (fields are taken modulo their width, at most 32 bits, so 32-bit differences
-// are exact).
-template <int D, typename C>
+// are exact).  HASH: instead of the fields side by side, layout->hashed bits
+// of a hash of all of them: two linear hashes (full-rate 24-bit products), one
+// mixed before they meet so that no difference of cells collides throughout.
+template <int D, typename C, bool HASH = false>
 __device__ __forceinline__ bool pack_cell(const double* __restrict__ Rt,
                                           const double* __restrict__ ut,
                                           const int64_t* __restrict__ kl,
@@ -367,15 +377,26 @@ __device__ __forceinline__ bool pack_cell(const double* __restrict__ Rt,
   const uint32_t bmask = (uint32_t)((1ull << sig_b) - 1ull);
   bool all_ok = true;
   cell = grp = 0;
+  uint32_t h0 = 0, h1 = 0;
   for (int j = 0; j < d; ++j) {
     const double y = cell_y<D>(Rt + (size_t)j * d, p, soa, n, i, d, inv_c, ut[j]);
     const bool ok = fabs(y) < 2147483648.0;
     all_ok = all_ok && ok;
     // |y| < 2^31: the floor fits 32 bits, and one native conversion takes it
     const uint32_t f = (uint32_t)(ok ? (int32_t)floor(y) : 0) - (uint32_t)kl[j];
-    const uint32_t mask = (uint32_t)((1ull << layout_byte(layout->bits, j)) - 1ull);
-    cell |= (C)(f & mask) << layout_byte(layout->shift, j);
+    if constexpr (HASH) {
+      h0 += __umul24(f, hash_weight(j, 0));
+      h1 += __umul24(f, hash_weight(j, 1));
+    } else {
+      const uint32_t mask = (uint32_t)((1ull << layout_byte(layout->bits, j)) - 1ull);
+      cell |= (C)(f & mask) << layout_byte(layout->shift, j);
+    }
     grp |= (C)(f & bmask) << (j * sig_b);
+  }
+  if constexpr (HASH) {
+    uint32_t h = (h0 ^ (h0 >> 15)) * 0x9E3779B1u + h1;
+    h = (h ^ (h >> 14)) * 0x9E3779B1u;
+    cell = (C)(h >> (32 - layout->hashed));
   }
   return all_ok;
 }
@@ -431,7 +452,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
   const int gbits = d * sig_b;
   bool bad = false;
   // one grid's key (stored) and signature group (returned)
-  auto grid = [&](int t, auto zero) -> uint64_t {
+  auto grid = [&](int t, auto zero, auto hash) -> uint64_t {
     using C = decltype(zero);
     const int s = seg_first + t;
     const int tr = tr_off + t;
@@ -439,7 +460,8 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
     const double* ut = u + (size_t)tr * d;
     const int64_t* kl = klo + (size_t)tr * d;
     C cell = 0, grp = 0;
-    bad |= !pack_cell<D>(Rt, ut, kl, layout, p, soa, npts, g, d, inv_c, sig_b, cell, grp);
+    bad |= !pack_cell<D, C, decltype(hash)::value>(Rt, ut, kl, layout, p, soa, npts, g, d, inv_c,
+                                                   sig_b, cell, grp);
     const uint64_t key =
         (cell_bits < 64) ? (((uint64_t)(s - sa) << cell_bits) | (uint64_t)cell) : (uint64_t)cell;
     const int64_t pos = segs[s].key_off + i;
@@ -453,7 +475,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
     }
     return (uint64_t)grp;
   };
-  auto words = [&](auto zero) {
+  auto words = [&](auto zero, auto hash) {
     const int w_lo = t_lo / sig_gpw + (SPLIT ? (int)blockIdx.y * words_per_slice : 0);
     const int w_end = (t_hi + sig_gpw - 1) / sig_gpw;
     const int w_hi = SPLIT ? min(w_end, w_lo + words_per_slice) : w_end;
@@ -461,7 +483,7 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
       const int ta = max(t_lo, x * sig_gpw), tb = min(t_hi, (x + 1) * sig_gpw);
       uint64_t word = 0;
       for (int t = ta + (SPLIT ? w : 0); t < tb; t += SPLIT ? kWaves : 1) {
-        const uint64_t grp = grid(t, zero);
+        const uint64_t grp = grid(t, zero, hash);
         if (sig) word |= grp << ((t - x * sig_gpw) * gbits);
       }
       if (sig) {
@@ -482,8 +504,16 @@ __global__ __launch_bounds__(kBlock) void k_keys(const InstDesc* __restrict__ in
       }
     }
   };
-  if (cell_bits <= 32 && gbits <= 32) words(uint32_t{0});
-  else words(uint64_t{0});
+  const std::false_type packed{};
+  const std::true_type hashed{};
+  if (layout->hashed) {
+    if (gbits <= 32) words(uint32_t{0}, hashed);
+    else words(uint64_t{0}, hashed);
+  } else if (cell_bits <= 32 && gbits <= 32) {
+    words(uint32_t{0}, packed);
+  } else {
+    words(uint64_t{0}, packed);
+  }
   if (bad) atomicOr(err, 1u);
 }
 
@@ -1225,22 +1255,33 @@ __device__ __forceinline__ uint64_t sig_word(const PairsArgs& P, int q, uint32_t
   return P.direct ? P.sigp[(size_t)i * P.sig_stride + q] : P.ssig[(size_t)q * P.N + p];
 }
 
-// Whether two points within r shared a cell under a grid t < tcell; word q of
-// their signatures is aq / bq for q < kSigWords, and is read on demand (the
-// points at sorted positions pa, pb with indices ia, ib) beyond that.
-__device__ __forceinline__ bool shared_earlier_cell(const uint64_t* aq, const uint64_t* bq,
-                                                    int tcell, uint32_t pa, uint32_t ia,
-                                                    uint32_t pb, uint32_t ib,
-                                                    const PairsArgs& P) {
-  const int nw = (tcell - 1) / P.gpw + 1;
-  bool same = false;
+// Whether a pair of points within r found under grid tcell is not to be
+// reported: they shared a cell under a grid t < tcell or, where keys are
+// hashes, do not under tcell itself (P.same_cell).  Word q of their
+// signatures is aq / bq for q < kSigWords, and is read on demand (the points
+// at sorted positions pa, pb with indices ia, ib) beyond that; nw words count.
+// HASHED: whether keys may be hashes (the check, unused, cost the matrix-core
+// screen 2.5% at uniform d6, so it has a variant without).
+template <bool HASHED>
+__device__ __forceinline__ bool not_first_owner(const uint64_t* aq, const uint64_t* bq, int tcell,
+                                                int nw, uint32_t pa, uint32_t ia, uint32_t pb,
+                                                uint32_t ib, const PairsArgs& P) {
+  bool drop = false;
 #pragma unroll
   for (int q = 0; q < kSigWords; ++q)
-    if (q < nw) same |= zero_group(aq[q] ^ bq[q], min(P.gpw, tcell - q * P.gpw), P);
-  for (int q = kSigWords; q < nw && !same; ++q)
-    same = zero_group(sig_word(P, q, pa, ia) ^ sig_word(P, q, pb, ib),
+    if (q < nw) drop |= zero_group(aq[q] ^ bq[q], min(P.gpw, tcell - q * P.gpw), P);
+  for (int q = kSigWords; q < nw && !drop; ++q)
+    drop = zero_group(sig_word(P, q, pa, ia) ^ sig_word(P, q, pb, ib),
                       min(P.gpw, tcell - q * P.gpw), P);
-  return same;
+  if (HASHED && P.same_cell) {
+    // grid tcell's group is in word nw - 1 (unit_view)
+    const int x = nw - 1;
+    const uint64_t v = x == 0   ? aq[0] ^ bq[0]
+                       : x == 1 ? aq[1] ^ bq[1]
+                                : sig_word(P, x, pa, ia) ^ sig_word(P, x, pb, ib);
+    drop |= (v & (P.same_cell << ((tcell - x * P.gpw) * P.g))) != 0ull;
+  }
+  return drop;
 }
 
 // Point index at sorted position p: the low idx_bits of the sorted key when
@@ -1296,6 +1337,7 @@ struct UnitView {
   bool ok;
 };
 
+template <bool HASHED>
 __device__ __forceinline__ UnitView unit_view(const PairsArgs& P, uint32_t u, uint32_t u_end) {
   UnitView v;
   v.ok = u < u_end;
@@ -1312,7 +1354,10 @@ __device__ __forceinline__ UnitView unit_view(const PairsArgs& P, uint32_t u, ui
   v.tcell = (int)uniform(U.t);
   v.inst = uniform(U.inst);
   v.nt = (v.L + kPairTile - 1) / kPairTile;
-  v.nw = (P.first_owner && v.tcell > 0) ? (v.tcell - 1) / P.gpw + 1 : 0;
+  // (with hashed keys grid t's own group counts too)
+  v.nw = HASHED && P.same_cell           ? v.tcell / P.gpw + 1
+         : P.first_owner && v.tcell > 0 ? (v.tcell - 1) / P.gpw + 1
+                                        : 0;
   return v;
 }
 
@@ -1477,12 +1522,12 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
     u_end = uniform(P.wave_first[wave_id + 1]);
     step = 1;
   }
-  UnitView V = unit_view(P, u, u_end);
+  UnitView V = unit_view<true>(P, u, u_end);
   TileRegs<D> cur, nxt;
   if (V.ok)
     load_tile<D>(P, V.s0 + V.ta_begin * kPairTile, tile_len(V, V.ta_begin), V.nw, lane, cur);
   while (V.ok) {
-    const UnitView Vn = unit_view(P, u + step, u_end);
+    const UnitView Vn = unit_view<true>(P, u + step, u_end);
     const PairTest T = P.tests[V.inst];
     for (uint32_t ta = V.ta_begin; ta < V.ta_end; ++ta) {
       const uint32_t nA = tile_len(V, ta);
@@ -1567,8 +1612,8 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
           uint64_t bw[kSigWords];
 #pragma unroll
           for (int q = 0; q < kSigWords; ++q) bw[q] = sBw[w][q][j];
-          if (shared_earlier_cell(A.sw, bw, V.tcell, pa0 + lane, A.idx, pb0 + (uint32_t)j,
-                                  sBi[w][j], P))
+          if (not_first_owner<true>(A.sw, bw, V.tcell, V.nw, pa0 + lane, A.idx, pb0 + (uint32_t)j,
+                              sBi[w][j], P))
             acc &= ~(1ull << j);
         }
       }
@@ -1691,7 +1736,7 @@ __device__ __forceinline__ void gram_operands(const float* row, float (&op)[2][K
 // and masked branches: uniform d6 509 -> 488 us, study d9 661 -> 625).  A
 // fifth wave (96 registers, no spills) changes nothing: vector and matrix
 // instructions together keep the SIMDs 86-91% busy.
-template <int D>
+template <int D, bool HASHED>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(D <= 12 ? 4 : 3))) void
 k_cell_pairs_gram(
     const PairsArgs P) {
@@ -1727,12 +1772,12 @@ k_cell_pairs_gram(
     u_end = uniform(P.wave_first[wave_id + 1]);
     step = 1;
   }
-  UnitView V = unit_view(P, u, u_end);
+  UnitView V = unit_view<HASHED>(P, u, u_end);
   TileRegs<D> cur, nxt;
   if (V.ok)
     load_tile<D>(P, V.s0 + V.ta_begin * kPairTile, tile_len(V, V.ta_begin), V.nw, lane, cur);
   while (V.ok) {
-    const UnitView Vn = unit_view(P, u + step, u_end);
+    const UnitView Vn = unit_view<HASHED>(P, u + step, u_end);
     const PairTest T = P.tests[V.inst];
     const float r2f = (float)T.r2;
     // When every unit is one grid cell, S <= s_bound for all of the unit's
@@ -1944,7 +1989,7 @@ k_cell_pairs_gram(
                 aq[q] = sAw[q][row];
                 bq[q] = sBw[q][col];
               }
-              keep = !shared_earlier_cell(aq, bq, V.tcell, pa0 + row, ia, pb0 + col, ib, P);
+              keep = !not_first_owner<HASHED>(aq, bq, V.tcell, V.nw, pa0 + row, ia, pb0 + col, ib, P);
             }
             pair = pack_pair(ia, ib, T.pair_bits);
           }
@@ -1966,8 +2011,8 @@ k_cell_pairs_gram(
               aq[q] = sAw[q][row];
               bq[q] = sBw[q][col];
             }
-            if (shared_earlier_cell(aq, bq, V.tcell, pa0 + row, sAi[w][row], pb0 + col,
-                                    sBi[w][col], P))
+            if (not_first_owner<HASHED>(aq, bq, V.tcell, V.nw, pa0 + row, sAi[w][row], pb0 + col,
+                                sBi[w][col], P))
               acc &= ~(1ull << b);
           }
         }
@@ -4072,7 +4117,10 @@ static void pairs_dispatch(const PairsArgs& a, hipStream_t s) {
   const uint64_t blocks = pair_waves(a) / kWaves;
   if constexpr (D <= 16) {
     if (a.gram && a.d == D) {
-      hipLaunchKernelGGL((k_cell_pairs_gram<D>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+      if (a.same_cell)
+        hipLaunchKernelGGL((k_cell_pairs_gram<D, true>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+      else
+        hipLaunchKernelGGL((k_cell_pairs_gram<D, false>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
       return;
     }
   }

@@ -112,7 +112,7 @@ constexpr size_t kNoallocStaging = size_t(256) << 10;
 
 int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const double* R,
                const double* u, const double* inv_c, const double* alpha, const float* lo,
-               const float* hi, size_t budget_bytes, Packing& P);
+               const float* hi, size_t budget_bytes, bool may_hash, Packing& P);
 
 struct Result {
   void* mem;

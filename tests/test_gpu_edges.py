@@ -122,3 +122,17 @@ def test_batches_around_the_request_loop():
             assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
             x.release()
         batch()
+
+
+@pytest.mark.parametrize("d,k,robots,upper", [(12, 8, 0, False), (12, 12, 0, True), (12, 8, 2, False),
+                                              (20, 8, 0, False), (16, 9, 0, False)])
+def test_hashed_keys(ctx, d, k, robots, upper):
+    """Cells of more than 40 bits in a pass of 2^20 keys: sorted by a 24-bit
+    hash, some hundred collisions per grid; one to three signature words."""
+    from paper_1409_8112_amd import rtg
+    n = 140_000
+    pts = workloads.clustered_points(n, d, seed=d, n_clusters=40, sigma=0.01)
+    r = {12: 0.028, 16: 0.038, 20: 0.048}[d]
+    flags = (rtg.UPPER_ONLY if upper else 0) | (rtg.robots(robots) if robots else 0)
+    _check(ctx, pts, r * (1.3 if robots else 1.0), k, 2.0, 3, flags)
+    assert ctx.stats()["key_passes"] == 3
