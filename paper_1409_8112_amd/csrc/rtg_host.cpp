@@ -1484,6 +1484,10 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
   Uploads U1(*this);
   const size_t o_inst = U1.add(inst.data(), sizeof(InstDesc) * m);
   const size_t o_tests = U1.add(tests.data(), sizeof(PairTest) * m);
+  std::vector<MrInst> mrs;
+  if (any_mr)
+    for (uint32_t q = 0; q < m; ++q) mrs.push_back(MrInst{inst[q].pt_off, jobs[q]->r, sub[q], 0});
+  const size_t o_mr = U1.add(mrs.data(), sizeof(MrInst) * mrs.size());
   const size_t o_R = U1.add(Rh.data(), sizeof(double) * Rh.size());
   const size_t o_u = U1.add(uh.data(), sizeof(double) * uh.size());
   // A few boxes: their identities, *bad and the pass's counters go up with
@@ -1707,8 +1711,8 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
   // One pass whose first-owner pairs go straight to the row-bucket lists: the
   // list build reads the pair kernel's output segments as they are, so they
   // are not first copied into one array.
-  const bool lists_from_segments = P.tb >= S_total && first_owner && !any_mr &&
-                                   pair_bits <= 24 && ceil_log2((uint64_t)npts) <= 22 &&
+  const bool lists_from_segments = P.tb >= S_total && first_owner && pair_bits <= 24 &&
+                                   ceil_log2((uint64_t)npts) <= 22 &&
                                    ceil_log2((uint64_t)npts) - 14 + pair_bits <= 32;
   PairSource seg_src{nullptr};
   uint64_t rechecks_seen = 0;
@@ -1939,6 +1943,7 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
     pa.sig_stride = sig_stride;
     pa.d = d;
     pa.tests = tests_d;
+    pa.mr = any_mr ? reinterpret_cast<const MrInst*>(up1 + o_mr) : nullptr;
     pa.gram = use_gram ? 1 : 0;
     pa.unit_band = (ctx->unit_band && !P.truncated && !P.wrapped) ? 1 : 0;
     if (first_owner) {
@@ -2057,28 +2062,6 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
                   (void*)sig, (void*)ssig, (void*)rec})
     S.drop(p);
 
-  // --- MR-metric: keep the Euclidean candidates within r under the MR-metric -----
-  if (any_mr && cand_total > 0) {
-    std::vector<MrInst> mi(m);
-    for (uint32_t q = 0; q < m; ++q) mi[q] = MrInst{inst[q].pt_off, jobs[q]->r, sub[q], 0};
-    MrInst* mi_d = S.get<MrInst>(m);
-    uint64_t* kept = S.get<uint64_t>(cand_total);
-    if (!mi_d || !kept) return RTG_ENOMEM;
-    if ((rc = upload(mi_d, mi.data(), sizeof(MrInst) * m))) return rc;
-    launch_fill_u64(reinterpret_cast<uint64_t*>(counters) + 2, 0ull, 1, stream);
-    MrFilterArgs fa{cand, cand_total, pair_bits, d, pts_rows, pts_rows, mi_d, (int)m, kept,
-                    counters + 2};
-    kbegin(RTG_K_COMPACT);
-    launch_mr_filter(fa, stream);
-    kend(RTG_K_COMPACT, (8.0 + 8.0 * d) * (double)cand_total);  // pairs and both rows read
-    unsigned long long nk = 0;
-    if ((rc = read_back(counters + 2, sizeof(nk), &nk))) return rc;
-    st.kernel_bytes[RTG_K_COMPACT] += 8.0 * (double)nk;  // kept pairs written
-    st.band_rechecks += (int64_t)cand_total;
-    S.drop(cand);
-    cand = kept;
-    cand_total = nk;
-  }
   st.candidates += (int64_t)cand_total;
 
   // --- bitmap de-duplication: first arrival of each pair --------------------------

@@ -254,6 +254,17 @@ void launch_unit_fill(const uint32_t* start, const uint32_t* end, const uint32_t
 // contended by every XCD); cand_count[s] is segment s's running total (it
 // may exceed cap: then the overflow is only counted).  rechecks counts FP64
 // band re-tests.
+//
+// Under the MR-metric (the sum of the robots' Euclidean displacements, each
+// robot a block of sub consecutive axes) the screen runs the Euclidean test
+// with a radius a little above r, which keeps every MR neighbour, and a pair
+// it accepts is kept if its MR distance is at most r (mr).
+struct MrInst {
+  int64_t pt_off;  // first row of the instance
+  double r;
+  int32_t sub;     // axes per robot; 0: Euclidean instance
+  int32_t pad;
+};
 struct PairsArgs {
   const UnitDesc* units;
   uint32_t total_units;
@@ -277,6 +288,7 @@ struct PairsArgs {
   // nonzero: keys are hashes, so a unit may mix cells; the bits of a pair's
   // first signature group, which must agree under the unit's own grid
   uint64_t same_cell;
+  const MrInst* mr;        // per instance, when an instance has the MR-metric (else null)
   uint64_t* cand;
   uint64_t cap;            // entries per segment
   unsigned long long *cand_count, *rechecks;  // cand_count: [nseg]
@@ -298,19 +310,11 @@ uint32_t pair_waves(const PairsArgs& a);
 void launch_wave_ranges(const uint64_t* work_off, uint32_t nunits, const uint64_t* total,
                         uint32_t nwaves, uint32_t* first, hipStream_t s);
 // --- MR-metric filter -----------------------------------------------------
-// Under the MR-metric (the sum of the robots' Euclidean displacements, each
-// robot a block of sub consecutive axes) the pair kernels run the Euclidean
-// test with a radius a little above r, which keeps every MR neighbour, and
-// this pass keeps the packed pairs (a << pair_bits | b) whose MR distance is
-// at most r.  The instance of a pair is the last one with pt_off <= a; pairs
-// of Euclidean instances (sub == 0) are kept as they are.  Kept pairs are
-// appended to out in no particular order; out_count must start at zero.
-struct MrInst {
-  int64_t pt_off;  // first row of the instance
-  double r;
-  int32_t sub;     // axes per robot; 0: Euclidean instance
-  int32_t pad;
-};
+// The MR decision (see PairsArgs) over packed pairs (a << pair_bits | b), for
+// the pairs of an index query.  The instance of a pair is the last one with
+// pt_off <= a; pairs of Euclidean instances (sub == 0) are kept as they are.
+// Kept pairs are appended to out in no particular order; out_count must start
+// at zero.
 struct MrFilterArgs {
   const uint64_t* in;
   uint64_t count;

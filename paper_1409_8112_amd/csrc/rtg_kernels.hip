@@ -1284,6 +1284,58 @@ __device__ __forceinline__ bool not_first_owner(const uint64_t* aq, const uint64
   return drop;
 }
 
+// The MR-metric's FP64 decision for the points ra and rb: the robots' squared
+// displacements summed in axis order, their square roots (correctly rounded)
+// added in robot order, the sum tested against r.
+__device__ __forceinline__ bool mr_within(const float* __restrict__ ra, const float* __restrict__ rb,
+                                          int d, const MrInst& I) {
+  double s = 0.0;
+  for (int o = 0; o < d; o += I.sub) {
+    double t = 0.0;
+    for (int l = o; l < o + I.sub; ++l) {
+      const double dl = (double)ra[l] - (double)rb[l];
+      t = t + dl * dl;
+    }
+    s = s + __builtin_sqrt(t);
+  }
+  return s <= I.r;
+}
+
+// That decision for the points with indices ia and ib of an instance of a
+// pass, read again from the rows their tiles were loaded from (they are in
+// the caches: a separate pass over the pairs fetched two random rows each,
+// 164 us for 5.9e6 pairs at d = 6, beside a copy and a read-back).  In FP32
+// first: D differences and products, at most D square roots (1 ulp) and as
+// many sums are within a relative (2 D + 8) 2^-24 < 2^-16 of the FP64 value
+// where no robot's square underflows to matter (r^2 >= 2^-60: the robots'
+// lost squares, below 2^-126 each, add less than 2^-57); FP64 decides the
+// rest.  (Pair kernel of 200003 points, d = 6, two robots: 313 us; 437 with
+// FP64 for every pair, 280 without the decision and 190 more for the pass.)
+template <int D>
+__device__ __forceinline__ bool mr_pair(const PairsArgs& P, uint32_t ia, uint32_t ib,
+                                        const MrInst& I) {
+  const float* ra = P.rows + (size_t)ia * P.row_stride;
+  const float* rb = P.rows + (size_t)ib * P.row_stride;
+  if (D <= 16 && I.r >= 0x1p-30) {
+    float s = 0.0f, t = 0.0f;
+    int c = 0;
+#pragma unroll
+    for (int l = 0; l < D; ++l) {
+      const float df = ra[l] - rb[l];
+      t = __builtin_fmaf(df, df, t);
+      if (++c == I.sub) {
+        s += __builtin_amdgcn_sqrtf(t);
+        t = 0.0f;
+        c = 0;
+      }
+    }
+    const float r = (float)I.r;
+    if (s < r * (1.0f - 0x1p-15f)) return true;
+    if (s > r * (1.0f + 0x1p-15f)) return false;
+  }
+  return mr_within(ra, rb, P.d, I);
+}
+
 // Point index at sorted position p: the low idx_bits of the sorted key when
 // keys carry it, else the separate index array.
 __device__ __forceinline__ uint32_t point_at(const PairsArgs& P, uint32_t p) {
@@ -1529,6 +1581,7 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
   while (V.ok) {
     const UnitView Vn = unit_view<true>(P, u + step, u_end);
     const PairTest T = P.tests[V.inst];
+    const MrInst mr = P.mr ? P.mr[V.inst] : MrInst{};
     for (uint32_t ta = V.ta_begin; ta < V.ta_end; ++ta) {
       const uint32_t nA = tile_len(V, ta);
       const uint32_t pa0 = V.s0 + ta * kPairTile;
@@ -1603,8 +1656,9 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
         ++nre;
       }
 
-      // First owner: drop a pair that an earlier grid put in one cell.
-      if (V.nw && ballot(acc != 0ull)) {
+      // First owner: drop a pair that an earlier grid put in one cell; then
+      // the MR-metric.
+      if ((V.nw || mr.sub) && ballot(acc != 0ull)) {
         uint64_t m = acc;
         while (m) {
           const int j = __builtin_ctzll(m);
@@ -1612,9 +1666,13 @@ __global__ __launch_bounds__(kBlock) void k_cell_pairs(const PairsArgs P) {
           uint64_t bw[kSigWords];
 #pragma unroll
           for (int q = 0; q < kSigWords; ++q) bw[q] = sBw[w][q][j];
-          if (not_first_owner<true>(A.sw, bw, V.tcell, V.nw, pa0 + lane, A.idx, pb0 + (uint32_t)j,
-                              sBi[w][j], P))
-            acc &= ~(1ull << j);
+          bool drop = V.nw && not_first_owner<true>(A.sw, bw, V.tcell, V.nw, pa0 + lane, A.idx,
+                                                    pb0 + (uint32_t)j, sBi[w][j], P);
+          if (!drop && mr.sub) {
+            drop = !mr_pair<D>(P, A.idx, sBi[w][j], mr);
+            ++nre;
+          }
+          if (drop) acc &= ~(1ull << j);
         }
       }
 
@@ -1736,7 +1794,9 @@ __device__ __forceinline__ void gram_operands(const float* row, float (&op)[2][K
 // and masked branches: uniform d6 509 -> 488 us, study d9 661 -> 625).  A
 // fifth wave (96 registers, no spills) changes nothing: vector and matrix
 // instructions together keep the SIMDs 86-91% busy.
-template <int D, bool HASHED>
+// CHECKS: 1 for passes with hashed keys, 2 for those with an MR-metric
+// instance (hashed keys or not).
+template <int D, int CHECKS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(D <= 12 ? 4 : 3))) void
 k_cell_pairs_gram(
     const PairsArgs P) {
@@ -1772,13 +1832,14 @@ k_cell_pairs_gram(
     u_end = uniform(P.wave_first[wave_id + 1]);
     step = 1;
   }
-  UnitView V = unit_view<HASHED>(P, u, u_end);
+  UnitView V = unit_view<(CHECKS > 0)>(P, u, u_end);
   TileRegs<D> cur, nxt;
   if (V.ok)
     load_tile<D>(P, V.s0 + V.ta_begin * kPairTile, tile_len(V, V.ta_begin), V.nw, lane, cur);
   while (V.ok) {
-    const UnitView Vn = unit_view<HASHED>(P, u + step, u_end);
+    const UnitView Vn = unit_view<(CHECKS > 0)>(P, u + step, u_end);
     const PairTest T = P.tests[V.inst];
+    const MrInst mr = CHECKS == 2 && P.mr ? P.mr[V.inst] : MrInst{};
     const float r2f = (float)T.r2;
     // When every unit is one grid cell, S <= s_bound for all of the unit's
     // tile pairs: one band for the unit, no per-tile maxima.
@@ -1989,7 +2050,11 @@ k_cell_pairs_gram(
                 aq[q] = sAw[q][row];
                 bq[q] = sBw[q][col];
               }
-              keep = !not_first_owner<HASHED>(aq, bq, V.tcell, V.nw, pa0 + row, ia, pb0 + col, ib, P);
+              keep = !not_first_owner<(CHECKS > 0)>(aq, bq, V.tcell, V.nw, pa0 + row, ia, pb0 + col, ib, P);
+            }
+            if (CHECKS == 2 && keep && mr.sub) {
+              keep = mr_pair<D>(P, ia, ib, mr);
+              ++nre;
             }
             pair = pack_pair(ia, ib, T.pair_bits);
           }
@@ -1998,7 +2063,7 @@ k_cell_pairs_gram(
         wave_lds_sync();  // sPend is rewritten by the next tile pair
       } else if (total) {
         // more than the list holds: each lane checks and writes its own
-        if (check) {
+        if (check || (CHECKS == 2 && mr.sub)) {
           wave_lds_sync();
           uint64_t m = acc;
           while (m) {
@@ -2011,9 +2076,13 @@ k_cell_pairs_gram(
               aq[q] = sAw[q][row];
               bq[q] = sBw[q][col];
             }
-            if (not_first_owner<HASHED>(aq, bq, V.tcell, V.nw, pa0 + row, sAi[w][row], pb0 + col,
-                                sBi[w][col], P))
-              acc &= ~(1ull << b);
+            bool drop = check && not_first_owner<(CHECKS > 0)>(aq, bq, V.tcell, V.nw, pa0 + row,
+                                                         sAi[w][row], pb0 + col, sBi[w][col], P);
+            if (CHECKS == 2 && !drop && mr.sub) {
+              drop = !mr_pair<D>(P, sAi[w][row], sBi[w][col], mr);
+              ++nre;
+            }
+            if (drop) acc &= ~(1ull << b);
           }
         }
         emit_pairs(P, O, lane, acc, [&](int b) {
@@ -2294,9 +2363,7 @@ __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
   flush_out(P, O, lane);
 }
 
-// The MR-metric's FP64 decision for one candidate pair: the robots' squared
-// displacements summed in axis order, their square roots (correctly rounded)
-// added in robot order, the sum tested against r.
+// The MR decision of one packed pair of the filter.
 __device__ __forceinline__ bool mr_keep(const MrFilterArgs& A, uint64_t v) {
   const uint64_t a = v >> A.pair_bits, b = v & ((1ull << A.pair_bits) - 1ull);
   int lo = 0, hi = A.m - 1;  // the last instance with pt_off <= a
@@ -2307,18 +2374,7 @@ __device__ __forceinline__ bool mr_keep(const MrFilterArgs& A, uint64_t v) {
   }
   const MrInst I = A.inst[lo];
   if (I.sub <= 0) return true;
-  const float* ra = A.rows_a + (size_t)a * A.d;
-  const float* rb = A.rows_b + (size_t)b * A.d;
-  double s = 0.0;
-  for (int o = 0; o < A.d; o += I.sub) {
-    double t = 0.0;
-    for (int l = o; l < o + I.sub; ++l) {
-      const double dl = (double)ra[l] - (double)rb[l];
-      t = t + dl * dl;
-    }
-    s = s + __builtin_sqrt(t);
-  }
-  return s <= I.r;
+  return mr_within(A.rows_a + (size_t)a * A.d, A.rows_b + (size_t)b * A.d, A.d, I);
 }
 
 // Keeps the packed pairs v of in[0, count) with keep(v), appended to out in
@@ -4117,10 +4173,12 @@ static void pairs_dispatch(const PairsArgs& a, hipStream_t s) {
   const uint64_t blocks = pair_waves(a) / kWaves;
   if constexpr (D <= 16) {
     if (a.gram && a.d == D) {
-      if (a.same_cell)
-        hipLaunchKernelGGL((k_cell_pairs_gram<D, true>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+      if (a.mr)
+        hipLaunchKernelGGL((k_cell_pairs_gram<D, 2>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+      else if (a.same_cell)
+        hipLaunchKernelGGL((k_cell_pairs_gram<D, 1>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
       else
-        hipLaunchKernelGGL((k_cell_pairs_gram<D, false>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL((k_cell_pairs_gram<D, 0>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a);
       return;
     }
   }

@@ -136,3 +136,11 @@ def test_hashed_keys(ctx, d, k, robots, upper):
     flags = (rtg.UPPER_ONLY if upper else 0) | (rtg.robots(robots) if robots else 0)
     _check(ctx, pts, r * (1.3 if robots else 1.0), k, 2.0, 3, flags)
     assert ctx.stats()["key_passes"] == 3
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -40, 2.0 ** 40])
+def test_mr_metric_far_from_unit_scale(ctx, scale):
+    """Radii below and above where the MR decision starts in FP32."""
+    from paper_1409_8112_amd import rtg
+    pts = (workloads.uniform_points(5000, 6, seed=3) * scale).astype(np.float32)
+    _check(ctx, pts, 0.45 * scale, 4, 2.0, 2, rtg.robots(2))
