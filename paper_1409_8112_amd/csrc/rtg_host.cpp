@@ -1195,13 +1195,13 @@ bool Ctx::small_fits(int64_t n, int32_t d, int32_t k, uint32_t flags) const {
 }
 
 // Device bytes the small path takes at most for an instance: the uploaded
-// transforms, the pair list, the list staging, the counts and the result
-// block before it gives back its tail (with room for alignment).
+// transforms, the pair list, the counts and the result block before it gives
+// back its tail (with room for alignment).
 size_t Ctx::small_bytes(int64_t n, int32_t d, int32_t k) const {
   auto up = [](size_t b) { return (b + Arena::kAlign - 1) / Arena::kAlign * Arena::kAlign; };
   return up(sizeof(double) * (size_t)k * d * (d + 1)) + up(sizeof(uint64_t) * kTinyPairCap) +
-         up(sizeof(int32_t) * 2 * kTinyPairCap) + up(64) + up(sizeof(int64_t) * (size_t)(n + 1)) +
-         up(sizeof(int32_t) * 2 * kTinyPairCap) + (64u << 10);
+         up(64) + up(sizeof(int64_t) * (size_t)(n + 1)) + up(sizeof(int32_t) * 2 * kTinyPairCap) +
+         (64u << 10);
 }
 
 // Lists for a query of n <= 1 points: empty, after the finiteness check.
@@ -1271,8 +1271,7 @@ int Lane::run_tiny(Job& j, rtg_stats& st) {
   const size_t o_cnt = U.add(kZeroCounts, sizeof(kZeroCounts));
   char* up = S.get<char>(U.total());
   uint64_t* pairs = S.get<uint64_t>(kTinyPairCap);
-  int32_t* stage = S.get<int32_t>(2 * kTinyPairCap);
-  if (!up || !pairs || !stage) return RTG_ENOMEM;
+  if (!up || !pairs) return RTG_ENOMEM;
   unsigned long long* cnt = reinterpret_cast<unsigned long long*>(up + o_cnt);
   if ((rc = U.send(up))) return rc;
   void* res = nullptr;
@@ -1297,7 +1296,6 @@ int Lane::run_tiny(Job& j, rtg_stats& st) {
   a.upper = (j.flags & RTG_UPPER_ONLY) ? 1 : 0;
   a.row_ptr = row_ptr;
   a.col = col;
-  a.stage = stage;
   kbegin(RTG_K_PAIRS);
   launch_tiny(a, d, j.k, stream);
   // points read per grid and pair; pairs, lists and row offsets written

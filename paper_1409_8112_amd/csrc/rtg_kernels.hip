@@ -3273,7 +3273,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
     uint32_t hist[kTinyBins];                // the counting sort's bins
     uint64_t out[kTinyWaves][kTinyOut];      // then each wave's staged pairs
   } sU;
-  __shared__ int32_t wlo[kTinyWaves][D], whi[kTinyWaves][D];
+  __shared__ uint32_t wlo[kTinyWaves][D], whi[kTinyWaves][D];
   __shared__ uint32_t wsum[kTinyWaves];
   __shared__ uint32_t sflag;
   // k parts workgroups: workgroup (t, part) tests slice part of grid t's
@@ -3298,50 +3298,87 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
   int idx_bits = 1;
   while ((1 << idx_bits) < n) ++idx_bits;
 
-  // The packed cell of every point under grids 0..t: the fields (the key
-  // kernel's FP64 formula) less their minimum over the instance, side by
-  // side.  Grid t's cells key the sort; the earlier grids' decide, by one
-  // comparison, whether a pair was already some earlier grid's.
+  // The cell of every point under grids 0..t.  One 32-bit word each: the
+  // fields (the key kernel's FP64 formula) less point 0's, kF bits an axis.
+  // The earlier grids' words decide, by one comparison, whether a pair was
+  // already some earlier grid's; grid t's key the sort, once packed more
+  // tightly below.  Each wave takes every eighth grid (or a share of one, when
+  // there are fewer grids) on its own: one barrier for all of them, where a
+  // pass over the points for each grid's field ranges and another for its
+  // words, both by the whole block, took 2.3 us a grid (n = 200, k = 20: 48
+  // us for the launch, now 15; n = 2000, k = 4: 28, now 23).
+  constexpr int kF = 32 / D;
+  constexpr uint32_t kHalf = kF < 32 ? 1u << (kF - 1) : 0x80000000u;
+  constexpr uint32_t kFMask = kF < 32 ? (1u << kF) - 1u : 0xFFFFFFFFu;
+  {
+    int groups = 1;  // grids at work at a time
+    while (groups < kTinyWaves && groups < t + 1) groups <<= 1;
+    const int per = kTinyWaves / groups;
+    const int i0 = (w % per) * 64 + (int)lane;
+    bad = 0u;
+    for (int g = w / per; g <= t; g += groups) {
+      const double* Rg = sT + (size_t)g * D * D;
+      const double* ug = sT + nR + (size_t)g * D;
+      uint32_t base[D];
+      for (int i = -1, at = 0; at < n; i = at) {
+        // first the fields' origin (point 0, alike in every wave), then points
+        float p[D];
+#pragma unroll
+        for (int l = 0; l < D; ++l) p[l] = sp[(i < 0 ? 0 : i) * D + l];
+        uint32_t cell = 0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          const double y = cell_y<D>(Rg + (size_t)j * D, p, nullptr, 0, 0, D, A.inv_c, ug[j]);
+          const bool ok = fabs(y) < 2147483648.0;
+          const uint32_t kj = (uint32_t)(ok ? (int32_t)floor(y) : 0);
+          if (!ok) bad |= 2u;
+          if (i < 0) {
+            base[j] = kj - kHalf;
+          } else {
+            const uint32_t f = kj - base[j];
+            if (f > kFMask) bad |= 4u;  // too far from point 0
+            cell |= (f & kFMask) << (j * kF);
+          }
+        }
+        if (i < 0) {
+          at = i0;
+        } else {
+          sC[(size_t)g * n + i] = cell;
+          at = i + per * 64;
+        }
+      }
+    }
+    if (bad) atomicOr(&sflag, bad);
+  }
+  __syncthreads();
+  // grid t's fields less their minimum, in as few bits as they take
   int cell_bits = 0;
-  for (int g = 0; g <= t; ++g) {
-    const double* Rg = sT + (size_t)g * D * D;
-    const double* ug = sT + nR + (size_t)g * D;
-    int32_t lo[D], hi[D];
+  {
+    uint32_t lo[D], hi[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {
-      lo[j] = INT32_MAX;
-      hi[j] = INT32_MIN;
+      lo[j] = 0xFFFFFFFFu;
+      hi[j] = 0u;
     }
-    bad = 0u;
+    const uint32_t* words = sC + (size_t)t * n;
     for (int i = (int)threadIdx.x; i < n; i += kTinyThreads) {
-      float p[D];
-#pragma unroll
-      for (int l = 0; l < D; ++l) p[l] = sp[i * D + l];
 #pragma unroll
       for (int j = 0; j < D; ++j) {
-        const double y = cell_y<D>(Rg + (size_t)j * D, p, nullptr, 0, 0, D, A.inv_c, ug[j]);
-        const bool ok = fabs(y) < 2147483648.0;
-        const int32_t kj = ok ? (int32_t)floor(y) : 0;
-        if (!ok) bad |= 2u;
-        lo[j] = min(lo[j], kj);
-        hi[j] = max(hi[j], kj);
+        const uint32_t f = (words[i] >> (j * kF)) & kFMask;
+        lo[j] = min(lo[j], f);
+        hi[j] = max(hi[j], f);
       }
     }
 #pragma unroll
     for (int j = 0; j < D; ++j) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        lo[j] = min(lo[j], __shfl_xor(lo[j], o, 64));
-        hi[j] = max(hi[j], __shfl_xor(hi[j], o, 64));
-      }
+      wave_minmax_u32(lo[j], hi[j]);
       if (lane == 0) {
         wlo[w][j] = lo[j];
         whi[w][j] = hi[j];
       }
     }
-    if (bad) atomicOr(&sflag, bad);
     __syncthreads();
-    int shift[D], total = 0;
+    int shift[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {
       lo[j] = wlo[0][j];
@@ -3351,33 +3388,25 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
         lo[j] = min(lo[j], wlo[q][j]);
         hi[j] = max(hi[j], whi[q][j]);
       }
-      int b = 0;
-      while (b < 32 && ((int64_t)1 << b) < (int64_t)hi[j] - (int64_t)lo[j] + 1) ++b;
-      shift[j] = total;
-      total += b;
+      shift[j] = cell_bits;
+      cell_bits += 32 - __clz((int)(hi[j] - lo[j]));  // (0 bits for one value)
     }
     uint32_t flag = sflag;
-    // grid t's key holds the point index too (and must not match the
-    // bitonic sort's padding); the earlier grids' cells only need 32 bits
-    if (g == t ? total + idx_bits > 31 : total > 32) flag |= 4u;
+    // the key holds the point index too (and must not match the bitonic
+    // sort's padding)
+    if (cell_bits + idx_bits > 31) flag |= 4u;
     if (flag) {
       if (threadIdx.x == 0) atomicOr(A.err, flag);
       return;  // uniform: every thread read the same flag
     }
-    cell_bits = total;
     for (int i = (int)threadIdx.x; i < n; i += kTinyThreads) {
-      float p[D];
-#pragma unroll
-      for (int l = 0; l < D; ++l) p[l] = sp[i * D + l];
+      const uint32_t word = sC[(size_t)t * n + i];
       uint32_t cell = 0;
 #pragma unroll
-      for (int j = 0; j < D; ++j) {
-        const double y = cell_y<D>(Rg + (size_t)j * D, p, nullptr, 0, 0, D, A.inv_c, ug[j]);
-        cell |= (uint32_t)((int32_t)floor(y) - lo[j]) << shift[j];
-      }
-      sC[(size_t)g * n + i] = cell;
+      for (int j = 0; j < D; ++j) cell |= (((word >> (j * kF)) & kFMask) - lo[j]) << shift[j];
+      sC[(size_t)t * n + i] = cell;
     }
-    __syncthreads();  // wlo / whi are reused by the next grid
+    __syncthreads();
   }
   const uint32_t* cur = sC + (size_t)t * n;
 
@@ -3562,31 +3591,40 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
 }
 
 // The pair list to CSR lists, the rows split over the workgroups
-// (kTinyThreads rows each): every workgroup counts every row's degree and
-// takes the offsets of all of them, places the entries of its own rows --
-// in LDS when they fit, else in A.stage -- and writes each at its rank
-// within its row (rows of at most kTinyMaxDeg entries).  count[3] receives
-// the entries written.
-__global__ __launch_bounds__(kTinyThreads) void k_tiny_lists(const TinyArgs A) {
-  __shared__ uint32_t cur[kTinyPoints];
-  __shared__ int32_t scol[kTinyListLds];
-  __shared__ uint32_t wsum[kTinyWaves];
-  __shared__ uint32_t smax, sbase, send;
+// (kTinyListRows rows each): every workgroup counts every row's degree and
+// takes the offsets of all of them, places the entries of its own rows in LDS
+// (rows have at most kTinyMaxDeg entries) and writes each at its rank within
+// its row, an entry a thread.  The pairs a thread loads stay in its registers
+// while they fit.  count[3] receives the entries written.  (512 rows per
+// workgroup, a row per thread and the pairs read twice took 19-21 us at
+// n = 200 and 2000, this 6 and 8.)
+constexpr int kTinyListThreads = 1024;
+constexpr int kTinyListPer = kTinyPoints / kTinyListThreads;
+__global__ __launch_bounds__(kTinyListThreads) void k_tiny_lists(const TinyArgs A) {
+  __shared__ uint32_t cur[kTinyPoints + 1];
+  __shared__ uint32_t ent[kTinyListRows * (int)kTinyMaxDeg];  // (row - r0) << 12 | column
+  __shared__ uint32_t wsum[kTinyListThreads / 64];
+  __shared__ uint32_t smax;
+  static_assert(kTinyPoints <= 1 << 12, "columns in 12 bits");
   constexpr int kB = 8;  // pairs in flight per thread
   const uint64_t P = A.count[0];
   if (P > A.cap || *A.err) return;  // uniform: the caller reruns or fails
   const int n = A.n;
-  const uint32_t r0 = blockIdx.x * kTinyThreads, r1 = min((uint32_t)n, r0 + kTinyThreads);
-  for (int i = (int)threadIdx.x; i < n; i += kTinyThreads) cur[i] = 0u;
-  if (threadIdx.x == 0) smax = 0u;
-  __syncthreads();
-  for (uint32_t base = 0; base < (uint32_t)P; base += kB * kTinyThreads) {
-    uint64_t v[kB];
+  const uint32_t r0 = blockIdx.x * kTinyListRows, r1 = min((uint32_t)n, r0 + kTinyListRows);
+  uint64_t v[kB];
+  auto load = [&](uint32_t base) {
 #pragma unroll
     for (int e = 0; e < kB; ++e) {
-      const uint32_t x = base + e * kTinyThreads + threadIdx.x;
+      const uint32_t x = base + e * kTinyListThreads + threadIdx.x;
       v[e] = x < P ? A.pairs[x] : ~0ull;
     }
+  };
+  load(0);
+  for (int i = (int)threadIdx.x; i < n; i += kTinyListThreads) cur[i] = 0u;
+  if (threadIdx.x == 0) smax = 0u;
+  __syncthreads();
+  for (uint32_t base = 0; base < (uint32_t)P; base += kB * kTinyListThreads) {
+    if (base) load(base);
 #pragma unroll
     for (int e = 0; e < kB; ++e) {
       if (v[e] == ~0ull) continue;
@@ -3595,94 +3633,64 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_lists(const TinyArgs A) {
     }
   }
   __syncthreads();
-  // row offsets: thread t takes the rows [t kTinyPer, (t + 1) kTinyPer);
-  // cur becomes the placement cursor of the workgroup's rows and the end
-  // of every other row (so a row's start is always its predecessor's cur)
-  uint32_t dg[kTinyPer];
+  // row offsets: thread t takes the rows [t kTinyListPer, (t + 1) kTinyListPer);
+  // cur becomes every row's start, cur[n] the total
+  uint32_t dg[kTinyListPer];
   uint32_t mine = 0, mx = 0;
 #pragma unroll
-  for (int e = 0; e < kTinyPer; ++e) {
-    const int i = (int)threadIdx.x * kTinyPer + e;
+  for (int e = 0; e < kTinyListPer; ++e) {
+    const int i = (int)threadIdx.x * kTinyListPer + e;
     dg[e] = i < n ? cur[i] : 0u;
     mine += dg[e];
     mx = max(mx, dg[e]);
   }
-  atomicMax(&smax, mx);
+  if (mx > kTinyMaxDeg) smax = 1u;
   uint32_t all;
-  uint32_t run = tiny_block_scan(mine, wsum, all);
-  if (smax > kTinyMaxDeg) {
+  uint32_t run = csr_block_exclusive_scan(mine, wsum, all);
+  if (smax) {
     if (threadIdx.x == 0) atomicOr(A.err, 8u);
     return;  // uniform after the scan's barriers
   }
 #pragma unroll
-  for (int e = 0; e < kTinyPer; ++e) {
-    const uint32_t i = threadIdx.x * kTinyPer + e;
+  for (int e = 0; e < kTinyListPer; ++e) {
+    const uint32_t i = threadIdx.x * kTinyListPer + e;
     if (i < (uint32_t)n) {
-      const bool own = i >= r0 && i < r1;
-      if (own) A.row_ptr[i] = (int64_t)run;
-      cur[i] = own ? run : run + dg[e];
-      if (i == r0) sbase = run;
-      if (i + 1 == r1) send = run + dg[e];
+      if (i >= r0 && i < r1) A.row_ptr[i] = (int64_t)run;
+      cur[i] = run;
     }
     run += dg[e];
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    A.row_ptr[n] = (int64_t)all;
-    A.count[3] = all;
+  if (threadIdx.x == 0) {
+    cur[n] = all;
+    if (blockIdx.x == gridDim.x - 1) {
+      A.row_ptr[n] = (int64_t)all;
+      A.count[3] = all;
+    }
   }
   __syncthreads();
-  const uint32_t base = sbase;
-  const bool in_lds = send - base <= (uint32_t)kTinyListLds;
-  // entry at list position x: scol[x - base] or A.stage[x]
-  int32_t* stage = in_lds ? scol : A.stage;
-  const uint32_t off = in_lds ? base : 0u;
-  for (uint32_t b0 = 0; b0 < (uint32_t)P; b0 += kB * kTinyThreads) {
-    uint64_t v[kB];
-#pragma unroll
-    for (int e = 0; e < kB; ++e) {
-      const uint32_t x = b0 + e * kTinyThreads + threadIdx.x;
-      v[e] = x < P ? A.pairs[x] : ~0ull;
-    }
+  const uint32_t base = cur[r0], end = cur[r1];
+  __syncthreads();  // the rows' starts become cursors
+  for (uint32_t b0 = 0; b0 < (uint32_t)P; b0 += kB * kTinyListThreads) {
+    if (P > (uint64_t)(kB * kTinyListThreads)) load(b0);
 #pragma unroll
     for (int e = 0; e < kB; ++e) {
       if (v[e] == ~0ull) continue;
       const uint32_t a = (uint32_t)(v[e] >> 32), b = (uint32_t)v[e];
-      if (a >= r0 && a < r1) stage[atomicAdd(&cur[a], 1u) - off] = (int32_t)b;
-      if (!A.upper && b >= r0 && b < r1) stage[atomicAdd(&cur[b], 1u) - off] = (int32_t)a;
+      if (a >= r0 && a < r1) ent[atomicAdd(&cur[a], 1u) - base] = ((a - r0) << 12) | b;
+      if (!A.upper && b >= r0 && b < r1) ent[atomicAdd(&cur[b], 1u) - base] = ((b - r0) << 12) | a;
     }
   }
-  // the workgroup's own stores to A.stage are visible after the barrier
-  __threadfence_block();
   __syncthreads();
   // A row's entries are distinct, so each one's rank within the row is its
-  // place: kR entries at a time are held in registers and compared with
-  // every entry of the row, read kR at a time (INT32_MAX past the row's
-  // end counts below none).  One row per thread.
-  constexpr int kR = 16;
-  const uint32_t i = r0 + threadIdx.x;
-  if (i >= r1) return;
-  const uint32_t s = i ? cur[i - 1] : 0u, len = cur[i] - s;
-  const int32_t* row = stage + (s - off);
-  for (uint32_t x0 = 0; x0 < len; x0 += kR) {
-    int32_t v[kR];
-    uint32_t rank[kR];
-#pragma unroll
-    for (int x = 0; x < kR; ++x) {
-      v[x] = x0 + x < len ? row[x0 + x] : INT32_MAX;
-      rank[x] = 0;
-    }
-    for (uint32_t y0 = 0; y0 < len; y0 += kR) {
-      int32_t wv[kR];
-#pragma unroll
-      for (int y = 0; y < kR; ++y) wv[y] = y0 + y < len ? row[y0 + y] : INT32_MAX;
-#pragma unroll
-      for (int y = 0; y < kR; ++y)
-#pragma unroll
-        for (int x = 0; x < kR; ++x) rank[x] += wv[y] < v[x] ? 1u : 0u;
-    }
-#pragma unroll
-    for (int x = 0; x < kR; ++x)
-      if (x0 + x < len) A.col[s + rank[x]] = v[x];
+  // place; a row's cursor stands at its end, its predecessor's at its start
+  // (entries of one row compare as columns).
+  for (uint32_t x = threadIdx.x; x < end - base; x += kTinyListThreads) {
+    const uint32_t e = ent[x];
+    const uint32_t row = r0 + (e >> 12);
+    const uint32_t lo = row > r0 ? cur[row - 1] - base : 0u, hi = cur[row] - base;
+    uint32_t rank = lo;
+    for (uint32_t y = lo; y < hi; ++y) rank += ent[y] < e ? 1u : 0u;
+    A.col[base + rank] = (int32_t)(e & 0xFFFu);
   }
 }
 
@@ -4200,8 +4208,8 @@ void launch_tiny(const TinyArgs& a, int d, int k, hipStream_t s) {
     default: return;
   }
 #undef RTG_TINY
-  hipLaunchKernelGGL(k_tiny_lists, dim3((a.n + kTinyThreads - 1) / kTinyThreads),
-                     dim3(kTinyThreads), 0, s, a);
+  hipLaunchKernelGGL(k_tiny_lists, dim3((a.n + kTinyListRows - 1) / kTinyListRows),
+                     dim3(kTinyListThreads), 0, s, a);
 }
 
 void launch_cell_pairs(const PairsArgs& a, hipStream_t s) {

@@ -144,3 +144,31 @@ def test_mr_metric_far_from_unit_scale(ctx, scale):
     from paper_1409_8112_amd import rtg
     pts = (workloads.uniform_points(5000, 6, seed=3) * scale).astype(np.float32)
     _check(ctx, pts, 0.45 * scale, 4, 2.0, 2, rtg.robots(2))
+
+
+@pytest.fixture(scope="module")
+def small_ctx():
+    from paper_1409_8112_amd import rtg
+    with rtg.Context(0, arena_bytes=256 << 20) as c:
+        yield c
+
+
+@pytest.mark.parametrize("n", [2, 127, 128, 129, 257, 1000])
+@pytest.mark.parametrize("d,k", [(1, 1), (2, 2), (3, 3), (3, 9), (5, 8), (8, 8)])
+def test_small_instances(small_ctx, n, d, k):
+    """Grids shared by the waves in every way, rows over several workgroups."""
+    pts = workloads.uniform_points(n, d, seed=n + d)
+    _check(small_ctx, pts, 0.4 * np.sqrt(d) * (4.0 / n) ** (1.0 / d), k, 1.5, k)
+
+
+@pytest.mark.parametrize("d,cells", [(3, 505), (3, 520), (8, 6), (8, 11), (1, 100_000)])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_small_instances_far_from_the_first_point(small_ctx, d, cells, sign):
+    """Cells within and beyond what a word's field holds beside point 0's
+    (the general pipeline then)."""
+    rng = np.random.default_rng(cells)
+    r, alpha, n = 0.05, 2.0, 400
+    pts = rng.random((n, d)) * 0.3
+    pts[n // 2:, 0] += sign * cells * alpha * r
+    from paper_1409_8112_amd import rtg
+    _check(small_ctx, pts.astype(np.float32), r, 4, alpha, 5, rtg.NO_ROTATE)
