@@ -892,6 +892,20 @@ std::vector<SortTile> segment_tiles(const std::vector<uint64_t>& off,
   return tab;
 }
 
+// The table of launch_seg_sort when every segment is short enough for it
+// (keys without values only), else the tiles of the passes.
+bool short_segments(const std::vector<uint64_t>& len, bool values) {
+  return !values && !len.empty() &&
+         *std::max_element(len.begin(), len.end()) <= (uint64_t)rtgk::kSegSortKeys;
+}
+std::vector<SortTile> sort_table(const std::vector<uint64_t>& off, const std::vector<uint64_t>& len,
+                                 bool whole) {
+  if (!whole) return segment_tiles(off, len);
+  std::vector<SortTile> tab;
+  for (size_t q = 0; q < off.size(); ++q) tab.push_back(SortTile{off[q], (uint32_t)len[q], 0u, 0u, 0u});
+  return tab;
+}
+
 // Frees every arena block taken through it when it goes out of scope.
 // Blocks are returned only after the lane's stream has drained, so that
 // another lane cannot reuse memory a kernel of this one still touches.
@@ -1625,17 +1639,23 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
   }
   // Each pass of several segments sorts within them (reduce-then-scan):
   // its table of sort tiles goes up with the layout, in one copy.
+  // (The point index rides in the low bits of the key when both fit in 64
+  // bits: the sort then moves 8 bytes per element instead of 12.)
+  const int idx_bits = (P.key_bits + pair_bits <= 64) ? pair_bits : 0;
   std::vector<std::vector<SortTile>> pass_tabs;
+  std::vector<char> pass_whole;  // the pass's segments are sorted one to a block
   for (int32_t sa = 0; sa < S_total; sa += P.tb) {
     const int32_t sb = std::min(S_total, sa + P.tb);
     pass_tabs.emplace_back();
+    pass_whole.push_back(0);
     if (sb - sa > 1 && T.sort_algo == kSortReduceScan) {
       std::vector<uint64_t> soff, slen;
       for (int32_t sg = sa; sg < sb; ++sg) {
         soff.push_back((uint64_t)segs[sg].key_off);
         slen.push_back((uint64_t)jobs[segs[sg].inst]->n);
       }
-      pass_tabs.back() = segment_tiles(soff, slen);
+      pass_whole.back() = short_segments(slen, idx_bits == 0);
+      pass_tabs.back() = sort_table(soff, slen, pass_whole.back());
     }
   }
   Uploads U2(*this);
@@ -1652,9 +1672,6 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
   SegDesc* segs_d = reinterpret_cast<SegDesc*>(up2 + o_segs);
   if ((rc = U2.send(up2))) return rc;
 
-  // The point index rides in the low bits of the key when both fit in 64
-  // bits: the sort then moves 8 bytes per element instead of 12.
-  const int idx_bits = (P.key_bits + pair_bits <= 64) ? pair_bits : 0;
   uint64_t* keys = S.get<uint64_t>(NB);
   uint64_t* keys_alt = S.get<uint64_t>(NB);
   uint32_t* vals = idx_bits ? nullptr : S.get<uint32_t>(NB);
@@ -1741,8 +1758,10 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
     const bool segmented = seg_bits > 0 && T.sort_algo == kSortReduceScan;
     uint32_t ntab = 0;
     SortTile* tab_d = nullptr;
+    bool whole = false;
     if (segmented) {
       const size_t pass = (size_t)(sa / P.tb);
+      whole = pass_whole[pass] != 0;
       ntab = (uint32_t)pass_tabs[pass].size();
       tab_d = reinterpret_cast<SortTile*>(up2 + o_tabs[pass]);
     }
@@ -1769,9 +1788,16 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
       kend(RTG_K_KEYS, 4.0 * (double)pass_pts * d + (idx_bits ? 8.0 : 12.0) * (double)N +
                            (sig ? 16.0 * (double)pass_pts * sig_W : 0.0));
       mark(2);
-      where = radix_sort(keys, vals, keys_alt, vals_alt, N, idx_bits, sort_end, sort_scr,
-                                   err, stream, &tm, RTG_K_KEY_HIST, RTG_K_KEY_SCATTER,
-                                   T.sort_algo, tab_d, ntab);
+      if (whole) {
+        kbegin(RTG_K_KEY_SCATTER);
+        launch_seg_sort(keys, tab_d, ntab, idx_bits, sort_end, stream);
+        kend(RTG_K_KEY_SCATTER, 16.0 * (double)N);
+        where = 0;
+      } else {
+        where = radix_sort(keys, vals, keys_alt, vals_alt, N, idx_bits, sort_end, sort_scr, err,
+                           stream, &tm, RTG_K_KEY_HIST, RTG_K_KEY_SCATTER, T.sort_algo, tab_d,
+                           ntab);
+      }
       st.key_passes = std::max(st.key_passes, (sort_end - idx_bits + kRadixBits - 1) / kRadixBits);
       const uint64_t* skeys = where ? keys_alt : keys;
       mark(3);
@@ -1829,7 +1855,7 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
                         (int64_t)T.sort_algo, (int64_t)T.unit_tiles, (int64_t)sig_stride,
                         (int64_t)sig_b, (int64_t)sig_gpw, (int64_t)cell_bound,
                         (int64_t)counts_direct, (int64_t)seg_bits, (int64_t)NB,
-                        (int64_t)max_cells})
+                        (int64_t)max_cells, (int64_t)whole})
         shape.push_back(v);
     }
     if (graph && pp->exec && shape == pp->shape) {
@@ -2756,13 +2782,15 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
     const bool segmented = seg_bits > 0 && ctx->defaults.sort_algo == kSortReduceScan;
     SortTile* tab_d = nullptr;
     uint32_t ntab = 0;
+    bool whole = false;
     if (segmented) {
       std::vector<uint64_t> soff, slen;
       for (int32_t t = sa; t < sb; ++t) {
         soff.push_back((uint64_t)(t - sa) * (uint64_t)n);
         slen.push_back((uint64_t)n);
       }
-      const std::vector<SortTile> tab = segment_tiles(soff, slen);
+      whole = short_segments(slen, idx_bits == 0);
+      const std::vector<SortTile> tab = sort_table(soff, slen, whole);
       ntab = (uint32_t)tab.size();
       Uploads Ut(*this);
       const size_t o_tab = Ut.add(tab.data(), sizeof(SortTile) * tab.size());
@@ -2772,8 +2800,12 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
       if ((rc = Ut.send(tab_mem))) return rc;
     }
     const int sort_end = idx_bits + (segmented ? I.P.layout.cell_bits : key_bits);
-    const int where = radix_sort(keys, vals, keys_alt, vals_alt, N, idx_bits, sort_end, scr, err,
-                                 stream, nullptr, 0, 0, ctx->defaults.sort_algo, tab_d, ntab);
+    int where = 0;
+    if (whole)
+      launch_seg_sort(keys, tab_d, ntab, idx_bits, sort_end, stream);
+    else
+      where = radix_sort(keys, vals, keys_alt, vals_alt, N, idx_bits, sort_end, scr, err, stream,
+                         nullptr, 0, 0, ctx->defaults.sort_algo, tab_d, ntab);
     uint64_t* sorted = where ? keys_alt : keys;
     uint32_t* sorted_idx = idx_bits ? nullptr : (where ? vals_alt : vals);
     if ((rc = sync())) return rc;  // the other buffers go back below

@@ -186,6 +186,12 @@ int radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* val
                int kid_scatter = 0, int algo = kSortOnesweep, const SortTile* tiles = nullptr,
                uint32_t ntiles_table = 0);
 
+// The same sort, in place, of segments of at most kSegSortKeys keys without
+// values, one SortTile per segment (start and len; len >= 1): one launch.
+constexpr int kSegSortKeys = 8192;
+void launch_seg_sort(uint64_t* keys, const SortTile* segs, uint32_t nsegs, int begin_bit,
+                     int end_bit, hipStream_t s);
+
 // --- cells ----------------------------------------------------------------
 // Runs of equal keys >> shift with length >= 2 in a sorted key array: per
 // tile counts of run heads and run tails (u32 each, ntiles entries), and the

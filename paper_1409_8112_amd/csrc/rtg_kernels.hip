@@ -846,6 +846,100 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
   tile_scatter<HAS_VAL>(S, kout, vout, count, t.start, t.end, shift, nbits, k_, v_, r_);
 }
 
+// --- short segments -------------------------------------------------------------
+
+// One block sorts one segment of at most kSegSortKeys keys: every pass of the
+// radix sort on keys held in registers and exchanged through LDS, in place of
+// a histogram, its scan and a scatter per pass over all segments (seven or so
+// launches of a few microseconds each, whose time the keys hardly show:
+// 25 segments of 6400 keys, three passes: 66 us, now 18).  Wave w holds elements [64 w items, 64 (w + 1) items), items =
+// ceil(len / 1024), so ranks are stable as in tile_rank.
+constexpr int kSegThreads = 1024;
+constexpr int kSegWaves = kSegThreads / 64;
+constexpr int kSegItems = kSegSortKeys / kSegThreads;
+
+__global__ __launch_bounds__(kSegThreads) void k_seg_sort(uint64_t* __restrict__ keys,
+                                                          const SortTile* __restrict__ segs,
+                                                          int begin_bit, int end_bit) {
+  __shared__ uint64_t skey[kSegSortKeys];
+  __shared__ uint32_t wcnt[kSegWaves][256];
+  __shared__ uint32_t wsum[kWaves];
+  const SortTile seg = segs[blockIdx.x];
+  uint64_t* base = keys + seg.start;
+  const uint32_t len = seg.len;
+  const uint32_t lane = lane_id();
+  const uint32_t w = uniform(threadIdx.x >> 6);
+  const uint32_t items = (len + kSegThreads - 1) / kSegThreads;
+  const uint32_t e0 = w * 64u * items + lane;
+  const uint64_t lt = (1ull << lane) - 1ull;
+  uint64_t k_[kSegItems];
+  uint32_t r_[kSegItems];
+#pragma unroll
+  for (int q = 0; q < kSegItems; ++q)
+    if ((uint32_t)q < items) k_[q] = base[min(e0 + 64u * q, len - 1u)];
+  for (int b = begin_bit; b < end_bit; b += kRadixBits) {
+    const int nbits = min(kRadixBits, end_bit - b);
+    const uint32_t mask = (1u << nbits) - 1u;
+    for (uint32_t x = threadIdx.x; x < kSegWaves * 256u; x += kSegThreads) (&wcnt[0][0])[x] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q) {
+      if ((uint32_t)q >= items) break;
+      const bool valid = e0 + 64u * q < len;
+      const uint32_t dg = (uint32_t)(k_[q] >> b) & mask;
+      uint64_t peers = ballot(valid);
+      for (int x = 0; x < nbits; ++x) {
+        const bool bit = (dg >> x) & 1u;
+        const uint64_t m = ballot(bit);
+        peers &= bit ? m : ~m;
+      }
+      uint32_t before = 0;
+      if (valid) before = wcnt[w][dg];
+      r_[q] = before + (uint32_t)__popcll(peers & lt);
+      wave_lds_sync();
+      if (valid && (peers & lt) == 0ull) wcnt[w][dg] = before + (uint32_t)__popcll(peers);
+      wave_lds_sync();
+    }
+    __syncthreads();
+    // thread dg: the digit's first place, then each wave's (the first four
+    // waves scan; every thread meets the barriers)
+    uint32_t c[kSegWaves], tot = 0, inc = 0;
+    if (threadIdx.x < 256u) {
+#pragma unroll
+      for (int x = 0; x < kSegWaves; ++x) {
+        c[x] = wcnt[x][threadIdx.x];
+        tot += c[x];
+      }
+      inc = wave_inclusive_scan(tot);
+      if (lane == 63) wsum[w] = inc;
+    }
+    __syncthreads();
+    if (threadIdx.x < 256u) {
+      uint32_t run = inc - tot;
+#pragma unroll
+      for (int x = 0; x < kWaves; ++x)
+        if ((uint32_t)x < w) run += wsum[x];
+#pragma unroll
+      for (int x = 0; x < kSegWaves; ++x) {
+        wcnt[x][threadIdx.x] = run;
+        run += c[x];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q)
+      if ((uint32_t)q < items && e0 + 64u * q < len)
+        skey[wcnt[w][(uint32_t)(k_[q] >> b) & mask] + r_[q]] = k_[q];
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSegItems; ++q)
+      if ((uint32_t)q < items) k_[q] = skey[min(e0 + 64u * q, len - 1u)];
+  }
+#pragma unroll
+  for (int q = 0; q < kSegItems; ++q)
+    if ((uint32_t)q < items && e0 + 64u * q < len) base[e0 + 64u * q] = k_[q];
+}
+
 // --- onesweep -------------------------------------------------------------------
 
 constexpr int kHistBlockTiles = 4;  // tiles per block of the all-pass histogram
@@ -3965,6 +4059,13 @@ int radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* val
     where ^= 1;
   }
   return where;
+}
+
+void launch_seg_sort(uint64_t* keys, const SortTile* segs, uint32_t nsegs, int begin_bit,
+                     int end_bit, hipStream_t s) {
+  if (!nsegs || end_bit <= begin_bit) return;
+  hipLaunchKernelGGL(k_seg_sort, dim3(nsegs), dim3(kSegThreads), 0, s, keys, segs, begin_bit,
+                     end_bit);
 }
 
 size_t run_mask_words(size_t count) { return 2 * ((count + 63) / 64); }

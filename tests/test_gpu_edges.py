@@ -131,7 +131,7 @@ def test_hashed_keys(ctx, d, k, robots, upper):
     hash, some hundred collisions per grid; one to three signature words."""
     from paper_1409_8112_amd import rtg
     n = 140_000
-    pts = workloads.clustered_points(n, d, seed=d, n_clusters=40, sigma=0.01)
+    pts = workloads.clustered_points(n, d, seed=d, n_clusters=400, sigma=0.01)
     r = {12: 0.028, 16: 0.038, 20: 0.048}[d]
     flags = (rtg.UPPER_ONLY if upper else 0) | (rtg.robots(robots) if robots else 0)
     _check(ctx, pts, r * (1.3 if robots else 1.0), k, 2.0, 3, flags)
@@ -172,3 +172,22 @@ def test_small_instances_far_from_the_first_point(small_ctx, d, cells, sign):
     pts[n // 2:, 0] += sign * cells * alpha * r
     from paper_1409_8112_amd import rtg
     _check(small_ctx, pts.astype(np.float32), r, 4, alpha, 5, rtg.NO_ROTATE)
+
+
+@pytest.mark.parametrize("n", [2, 1024, 1025, 2049, 8191, 8192, 8193])
+@pytest.mark.parametrize("d", [2, 6])
+def test_segments_sorted_one_to_a_block(ctx, n, d):
+    """Segments up to and past the largest a block sorts, alone and beside
+    shorter ones in a batch; one to four radix passes."""
+    import torch
+    pts = workloads.uniform_points(n, d, seed=n)
+    r = 0.9 * (8.0 / n) ** (1.0 / d)
+    _check(ctx, pts, r, 5, 1.3, n)
+    small = workloads.uniform_points(37, d, seed=1)
+    res = ctx.all_pairs_batched([dict(points=torch.from_numpy(p).cuda(), r=r, k=3, alpha=1.3, seed=7)
+                                 for p in (small, pts, small)])
+    for x, p in zip(res, (small, pts, small)):
+        ref = oracle.rtg(p, r, 3, 1.3, 7)
+        rp, col = x.to_numpy()
+        assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+    ctx.release_many(res)
