@@ -2821,24 +2821,36 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
                            (uint64_t)(t - sa), idx_bits, 0};
   }
   if ((rc = upload(I.grids, grids.data(), sizeof(QueryGrid) * grids.size()))) return rc;
-  // About four keys per table entry, and the coordinates in grid order: a
-  // query reads its cells' members in runs (pairs of 1e6 queries, n = 1e6,
-  // d = 3: 1.0 ms, 2.0 by point index; the copy takes 0.12 ms here).  Neither
-  // is needed, so they take at most a sixteenth of what is free.
-  const size_t spare = ctx->largest_free() / 16;
-  I.tab_bits = std::min(I.P.layout.cell_bits, std::max(1, pair_bits - 2));
-  const size_t tab_bytes = sizeof(uint32_t) * (size_t)k * (((size_t)1 << I.tab_bits) + 1);
-  const size_t row_bytes = sizeof(float) * (size_t)k * n * d;
-  if (I.tab_bits > 0 && tab_bytes <= spare) I.tab = static_cast<uint32_t*>(dalloc(tab_bytes));
-  if (I.tab) launch_query_table(I.grids, k, n, I.P.layout.cell_bits, I.tab_bits, I.tab, stream);
-  if (query_rows_fit(d) && row_bytes + tab_bytes <= spare)
-    I.rows = static_cast<float*>(dalloc(row_bytes));
-  if (I.rows) launch_query_rows(I.grids, k, n, d, I.pts, I.rows, stream);
   uint32_t errh = 0;
   if ((rc = read_back(err, sizeof(errh), &errh))) return rc;
   if (errh & 1u) return RTG_ERANGE;
   if (errh) return hip_fail(hipErrorUnknown, "radix sort look-back");
   return RTG_OK;
+}
+
+// The tables an index keeps for speed, made by its first call with queries
+// enough (m >= n / 8): about four keys per start-table entry, and the points'
+// coordinates in grid order, so that a query reads its cells' members in runs.
+// They cost 0.16 ms at n = 1e6, d = 3, k = 8 and save 1 us per thousand
+// queries there.  Neither is needed, so they take at most a sixteenth of what
+// is free.
+int Lane::index_extras(Index& I) {
+  const int bits = std::min(I.P.layout.cell_bits,
+                            std::max(1, ceil_log2((uint64_t)std::max<int64_t>(I.n, 2)) - 2));
+  const size_t tab_bytes = sizeof(uint32_t) * (size_t)I.k * (((size_t)1 << bits) + 1);
+  const size_t row_bytes = sizeof(float) * (size_t)I.k * I.n * I.d;
+  const size_t spare = largest_free() / 16;
+  if (!I.tab && tab_bytes <= spare) {
+    I.tab = static_cast<uint32_t*>(dalloc(tab_bytes));
+    I.tab_bits = bits;
+    if (I.tab)
+      launch_query_table(I.grids, I.k, I.n, I.P.layout.cell_bits, bits, I.tab, stream);
+  }
+  if (!I.rows && query_rows_fit(I.d) && row_bytes + tab_bytes <= spare) {
+    I.rows = static_cast<float*>(dalloc(row_bytes));
+    if (I.rows) launch_query_rows(I.grids, I.k, I.n, I.d, I.pts, I.rows, stream);
+  }
+  return hip_fail(hipGetLastError(), "index tables");
 }
 
 // Queries from which a call orders them by place (their cell under grid 0, on
@@ -2852,7 +2864,7 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
 constexpr int64_t kQueryOrderMin = 65536;
 constexpr int kQueryOrderBits = 24;
 
-int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats& st,
+int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
                       rtg_csr* out, bool extras) {
   int rc;
   if (m == 0 || I.n == 0) return make_empty_result(m, out, 0);
@@ -2865,6 +2877,7 @@ int Lane::query_index(const Index& I, const float* queries, int64_t m, rtg_stats
       c.kstats = nullptr;
     }
   } detach{*this};
+  if (extras && m >= I.n / 8 && (rc = index_extras(I))) return rc;
   Scratch S(*this);
   const int k = I.k, d = I.d;
   uint64_t* qkey = S.get<uint64_t>((size_t)m * k);

@@ -242,7 +242,8 @@ struct Lane {
   int make_empty_result(int64_t n, rtg_csr* out, uint64_t handle);
   int build_index(const float* points, int64_t n, int32_t d, double r, int32_t k, double alpha,
                   const double* R, const double* u, Index& I);
-  int query_index(const Index& I, const float* queries, int64_t m, rtg_stats& st,
+  int index_extras(Index& I);
+  int query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
                   rtg_csr* out, bool extras);
   int tiny_query(const float* points, int64_t n, int32_t d, rtg_csr* out, uint64_t handle);
   // One pass of the pipeline over a batch of instances of one dimension
