@@ -303,7 +303,9 @@ int rtg_release_many(rtg_ctx *ctx, const uint64_t *handles, int32_t count);
  * them, a copy of the points and their signatures in the context under
  * *index (free with rtg_release).  Arguments and errors as rtg_all_pairs;
  * flags: RTG_NO_ROTATE, RTG_ROBOTS(b) (the queries' distance test is then
- * the MR-metric's; list flags are ignored).
+ * the MR-metric's; list flags are ignored).  The first call with m >= n / 8
+ * queries also makes tables for the index (at most a sixteenth of the free
+ * budget, given back when an allocation would fail otherwise).
  *
  * rtg_index_query answers m query points (device, row-major [m][d] FP32,
  * the index's d): row s of the result lists, ascending and once each, the

@@ -49,7 +49,7 @@ struct LaunchTimer {
   }
 };
 
-// Device scalars to bring back with one copy (launch_gather).
+// Device scalars to bring back together (launch_mailbox).
 struct Gather {
   const void* src[8] = {};
   int bytes[8] = {};
@@ -60,7 +60,6 @@ struct Gather {
     ++count;
   }
 };
-void launch_gather(const Gather& g, uint64_t* dst, hipStream_t s);
 // Writes words 32-bit words of src (or, with src null, the scalars of *g as
 // u64) to pinned host memory at host, then seq to *host_seq with a
 // system-scope release once every value is visible (one block).
@@ -188,7 +187,7 @@ int radix_sort(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* val
 
 // The same sort, in place, of segments of at most kSegSortKeys keys without
 // values, one SortTile per segment (start and len; len >= 1): one launch.
-constexpr int kSegSortKeys = 8192;
+constexpr int kSegSortKeys = 16384;  // 16 a thread, 128 KB of LDS
 void launch_seg_sort(uint64_t* keys, const SortTile* segs, uint32_t nsegs, int begin_bit,
                      int end_bit, hipStream_t s);
 

@@ -852,7 +852,8 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
 // radix sort on keys held in registers and exchanged through LDS, in place of
 // a histogram, its scan and a scatter per pass over all segments (seven or so
 // launches of a few microseconds each, whose time the keys hardly show:
-// 25 segments of 6400 keys, three passes: 66 us, now 18).  Wave w holds elements [64 w items, 64 (w + 1) items), items =
+// 25 segments of 6400 keys, three passes: 66 us, now 18; calls of n = 12000
+// and 16384 points still gain 6 to 12%).  Wave w holds elements [64 w items, 64 (w + 1) items), items =
 // ceil(len / 1024), so ranks are stable as in tile_rank.
 constexpr int kSegThreads = 1024;
 constexpr int kSegWaves = kSegThreads / 64;
@@ -2718,10 +2719,9 @@ __global__ void k_csr_fill_lower(const uint64_t* __restrict__ lo, size_t count, 
 // partitioned into buckets of 2^rb consecutive rows: per-block bucket counts,
 // one device-wide scan in bucket-major order, and a scatter in which each
 // block places its entries through LDS cursors.  An entry is stored as the
-// 32-bit local key (row mod 2^rb) << pb | col.  Each bucket is then sorted in
-// LDS (bitonic) with repeats removed, and the emit step writes col and the
-// bucket's slice of row_ptr.  The order of entries inside a bucket before the
-// local sort does not matter: the sort makes it canonical.
+// 32-bit local key (row mod 2^rb) << pb | col.  Each bucket is then ordered in
+// LDS and written as its part of col and row_ptr (k_bucket_csr).  The order of
+// entries inside a bucket before that does not matter.
 
 // The pairs a partition block reads: a chunk of one array, or -- when the
 // pairs are still in the pair kernels' nseg output segments (segment s at
@@ -3177,15 +3177,6 @@ __global__ void k_widen(const uint32_t* __restrict__ src, size_t count, uint64_t
   if (q < count) dst[q] = src[q];
 }
 
-// dst[q] = the 4- or 8-byte device scalar at src[q], zero-extended: several
-// scalars come back to the host with one copy.
-__global__ void k_gather(Gather g, uint64_t* __restrict__ dst) {
-  const int q = threadIdx.x;
-  if (q >= g.count) return;
-  dst[q] = g.bytes[q] == 8 ? *static_cast<const uint64_t*>(g.src[q])
-                           : (uint64_t)*static_cast<const uint32_t*>(g.src[q]);
-}
-
 // Read-backs into pinned host memory: the values (words of a device buffer,
 // or the scalars of a Gather), then -- after every thread's stores are
 // visible at system scope -- the sequence number the host waits for.
@@ -3294,17 +3285,15 @@ inline unsigned tiles_for(size_t count) { return (unsigned)((count + kTile - 1) 
 // ---------------------------------------------------------------------------
 // Small instances in two launches.  For n <= kTinyPoints (and d <= 8) the
 // whole pipeline fits a few workgroups per grid: block (t, part) computes
-// every point's cell under grids 0..t (the FP64 formula of k_keys) and
-// packs each cell's fields into 32 bits (field widths from the block's own
-// minimum and maximum), sorts grid t's keys -- cell and point index -- in
+// every point's cell under grids 0..t (the FP64 formula of k_keys) as a
+// 32-bit word of its fields, sorts grid t's keys -- cell and point index -- in
 // LDS (counting sort over few cells, else bitonic), tests its slice of the
-// pairs of the cells in FP64 in the definition's order, keeps a pair within
-// r only if no earlier
-// grid's packed cells of the two points are equal, and appends it to one
-// pair list.  A second launch turns the list into the CSR lists.
-// Anything outside these limits -- wider keys, more pairs than the list
-// holds (kTinyPairCap), a row longer than kTinyMaxDeg -- is flagged and the
-// caller runs the general pipeline instead.
+// pairs of the cells in FP64 in the definition's order, keeps a pair within r
+// only if no earlier grid's words of the two points are equal, and appends it
+// to one pair list.  A second launch turns the list into the CSR lists.
+// Anything outside these limits -- cells too far apart for a word, wider
+// keys, more pairs than the list holds (kTinyPairCap), a row longer than
+// kTinyMaxDeg -- is flagged and the caller runs the general pipeline instead.
 
 constexpr int kTinyThreads = 512;
 constexpr int kTinyWaves = kTinyThreads / 64;
@@ -4475,11 +4464,6 @@ void launch_mailbox(const uint32_t* src, uint32_t words, const Gather* g, uint32
                     uint64_t* host_seq, uint64_t seq, hipStream_t s) {
   hipLaunchKernelGGL(k_mailbox, dim3(1), dim3(kBlock), 0, s, src, words, g ? *g : Gather{}, host,
                      host_seq, seq);
-}
-
-void launch_gather(const Gather& g, uint64_t* dst, hipStream_t s) {
-  if (g.count <= 0) return;
-  hipLaunchKernelGGL(k_gather, dim3(1), dim3(64), 0, s, g, dst);
 }
 
 void launch_records(const float* rows, int64_t n, int d, int rs, float* rec, hipStream_t s) {

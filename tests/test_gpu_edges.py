@@ -174,7 +174,7 @@ def test_small_instances_far_from_the_first_point(small_ctx, d, cells, sign):
     _check(small_ctx, pts.astype(np.float32), r, 4, alpha, 5, rtg.NO_ROTATE)
 
 
-@pytest.mark.parametrize("n", [2, 1024, 1025, 2049, 8191, 8192, 8193])
+@pytest.mark.parametrize("n", [2, 1024, 1025, 2049, 8193, 16383, 16384, 16385])
 @pytest.mark.parametrize("d", [2, 6])
 def test_segments_sorted_one_to_a_block(ctx, n, d):
     """Segments up to and past the largest a block sorts, alone and beside
