@@ -1029,25 +1029,41 @@ int csr_by_buckets(Lane& c, Scratch& S, const Tuning& T, const PairSource& pairs
   if ((1 << rb) > kBucketMaxRows) return RTG_ENOMEM;  // callers keep n <= 2^22
   // (and, of few entries, as large as still gives the chip's CUs two each)
   const double per_row = (double)E / (double)n;
-  const double target = std::min((double)T.bucket_entries,
-                                 std::max(kMinBucketEntries, (double)E / kCsrResident));
-  while ((2 << rb) <= kBucketMaxRows && rb + 1 + pb <= 32 &&
-         per_row * (double)(1u << (rb + 1)) <= target)
-    ++rb;
-  const uint32_t nbuckets = (uint32_t)((n + ((int64_t)1 << rb) - 1) >> rb);
+  const int rb_least = rb;
+  auto rows_for = [&](double target) {
+    int b = rb_least;
+    while ((2 << b) <= kBucketMaxRows && b + 1 + pb <= 32 &&
+           per_row * (double)(1u << (b + 1)) <= target)
+      ++b;
+    return b;
+  };
+  const int rb_most = rows_for((double)T.bucket_entries);
+  rb = rows_for(std::min((double)T.bucket_entries,
+                         std::max(kMinBucketEntries, (double)E / kCsrResident)));
   uint32_t nblocks = (uint32_t)std::max<size_t>(
       1, std::min<size_t>(T.bucket_blocks, (count + 4095) / 4096));
   // pairs still in output segments: every segment gets the same number of
   // blocks
   if (pairs.nseg) nblocks = (nblocks + pairs.nseg - 1) / pairs.nseg * pairs.nseg;
   const uint32_t chunk = (uint32_t)((count + nblocks - 1) / nblocks);
-  const size_t np = (size_t)nbuckets * nblocks;
-  uint32_t* part = S.get<uint32_t>(np + 1);
-  uint32_t* pscr = S.get<uint32_t>(scan_scratch_elems(np) + 1);
-  uint32_t* entries = S.get<uint32_t>(E);
-  uint32_t* over = S.get<uint32_t>((size_t)nbuckets + 1);  // [0] count, then bucket ids
-  if (!part || !pscr || !entries || !over) return RTG_ENOMEM;
-  if ((rc = alloc_result(c, n, E, res, row_ptr, col))) return rc;
+  uint32_t nbuckets = 0;
+  size_t np = 0;
+  uint32_t *part = nullptr, *pscr = nullptr, *entries = nullptr, *over = nullptr;
+  for (;;) {
+    nbuckets = (uint32_t)((n + ((int64_t)1 << rb) - 1) >> rb);
+    np = (size_t)nbuckets * nblocks;
+    part = S.get<uint32_t>(np + 1);
+    pscr = S.get<uint32_t>(scan_scratch_elems(np) + 1);
+    entries = S.get<uint32_t>(E);
+    over = S.get<uint32_t>((size_t)nbuckets + 1);  // [0] count, then bucket ids
+    if (part && pscr && entries && over && !alloc_result(c, n, E, res, row_ptr, col)) break;
+    // without room for the small buckets' counts, the large ones
+    if (rb >= rb_most) return RTG_ENOMEM;
+    for (uint32_t* p : {part, pscr, entries, over})
+      if (p) S.drop(p);
+    (void)S.flush();
+    rb = rb_most;
+  }
   if (tm) tm->on_begin(RTG_K_CSR);
   const int pt = (int)T.part_threads;
   // the histogram launch also clears the oversized count; the CSR launch
@@ -1108,6 +1124,7 @@ int csr_by_buckets(Lane& c, Scratch& S, const Tuning& T, const PairSource& pairs
       return rc;
     }
   }
+  if (rb < rb_most) S.drop(part);  // (a caller's next blocks may need the room)
   *nnz_out = E;
   return RTG_OK;
 }
