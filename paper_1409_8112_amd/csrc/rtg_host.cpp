@@ -2881,8 +2881,10 @@ int Lane::index_extras(Index& I) {
 constexpr int64_t kQueryOrderMin = 65536;
 constexpr int kQueryOrderBits = 24;
 
+// lean: in the least memory, without what a call only has for speed (the
+// index's tables, an order of the queries, several output segments).
 int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
-                      rtg_csr* out, bool extras) {
+                      rtg_csr* out, bool lean) {
   int rc;
   if (m == 0 || I.n == 0) return make_empty_result(m, out, 0);
   kstats = &st;
@@ -2894,17 +2896,16 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
       c.kstats = nullptr;
     }
   } detach{*this};
-  if (extras && m >= I.n / 8 && (rc = index_extras(I))) return rc;
+  if (!lean && m >= I.n / 8 && (rc = index_extras(I))) return rc;
   Scratch S(*this);
   const int k = I.k, d = I.d;
-  uint64_t* qkey = S.get<uint64_t>((size_t)m * k);
   uint32_t* qlo = S.get<uint32_t>((size_t)m * k);
   uint64_t* qsig = S.get<uint64_t>((size_t)m * I.sig_W);
   // the output segments' counts, then a filter's count and the error bits
   // ([0] the queries', [1] the list build's)
   constexpr uint32_t kWords = kCandSegments + 2;
   unsigned long long* counts = S.get<unsigned long long>(kWords);
-  if (!qkey || !qlo || !qsig || !counts) return RTG_ENOMEM;
+  if (!qlo || !qsig || !counts) return RTG_ENOMEM;
   unsigned long long* counter = counts + kCandSegments;
   uint32_t* err = reinterpret_cast<uint32_t*>(counter + 1);
   launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kWords, stream);
@@ -2923,8 +2924,8 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   A.grids = I.grids;
   A.n = I.n;
   A.pts = I.pts;
-  A.rows = extras ? I.rows : nullptr;
-  A.tab = extras ? I.tab : nullptr;
+  A.rows = lean ? nullptr : I.rows;
+  A.tab = lean ? nullptr : I.tab;
   A.tab_bits = I.tab_bits;
   A.sig = I.sig;
   A.W = I.sig_W;
@@ -2933,7 +2934,6 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   A.gpw = I.sig_gpw;
   A.lows = I.lows;
   A.highs = I.highs;
-  A.qkey = qkey;
   A.qlo = qlo;
   A.qsig = qsig;
   A.err = err;
@@ -2945,18 +2945,20 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   // Queries in the order of their place: those that read the same cells run
   // side by side, so the cells come from the caches.  (Without room the
   // queries run as given.)
-  if (m >= kQueryOrderMin) {
+  if (!lean && m >= kQueryOrderMin) {
     const int bits = std::min(A.cell_bits, kQueryOrderBits);
     uint64_t* o1 = S.get<uint64_t>((size_t)m);
-    uint64_t* o2 = o1 ? S.get<uint64_t>((size_t)m) : nullptr;
-    void* scr = o2 ? S.get<char>(radix_scratch_bytes((size_t)m, 32, 32 + bits)) : nullptr;
-    if (scr) {
+    uint64_t* o2 = S.get<uint64_t>((size_t)m);
+    void* scr = S.get<char>(radix_scratch_bytes((size_t)m, 32, 32 + bits));
+    if (o1 && o2 && scr) {
       launch_query_order(A, bits, o1, stream);
       A.order = radix_sort(o1, nullptr, o2, nullptr, (size_t)m, 32, 32 + bits, scr, err, stream,
                            nullptr, 0, 0, kSortReduceScan)
                     ? o2
                     : o1;
     }
+    for (void* p : {(void*)o1, (void*)o2, scr})
+      if (p && p != A.order) S.drop(p);
   }
   launch_query_find(A, stream);
 
@@ -2966,13 +2968,9 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   const bool bucket_rows = pb <= 24 && ceil_log2((uint64_t)m) <= 22 &&
                            ceil_log2((uint64_t)m) - 14 + pb <= 32;
   const uint64_t guess = std::max<uint64_t>(1u << 20, (uint64_t)m * 32);
-  A.nseg = kCandSegments;
-  A.cap = guess / A.nseg + guess / (4 * A.nseg) + 1024;
+  A.nseg = lean ? 1 : kCandSegments;
+  A.cap = lean ? guess : guess / A.nseg + guess / (4 * A.nseg) + 1024;
   uint64_t* cand = S.get<uint64_t>(A.nseg * A.cap);
-  if (!cand) {
-    A.cap = guess / A.nseg;
-    cand = S.get<uint64_t>(A.nseg * A.cap);
-  }
   if (!cand) return RTG_ENOMEM;
   uint64_t C = 0, most = 0;
   for (int attempt = 0;; ++attempt) {
@@ -3235,16 +3233,21 @@ int rtg_index_query(rtg_ctx* ctx, uint64_t index, const float* queries, int64_t 
     I->in_use = v;
   };
   in_use(true);
-  int rc = c->main.query_index(*I, queries, m, st, out, true);
+  int rc = c->main.query_index(*I, queries, m, st, out, false);
+  // (a call that failed may have left kernels behind that use the tables)
+  if (rc) (void)hipStreamSynchronize(c->main.stream);
   in_use(false);
-  // out of memory beside what the index keeps for speed: once more without it
-  if (rc == RTG_ENOMEM && (I->rows || I->tab)) {
-    (void)hipStreamSynchronize(c->main.stream);
+  // Out of memory: once more in the least there is for it.
+  if (rc == RTG_ENOMEM) {
     {
       std::lock_guard<std::mutex> alk(c->amu);
       c->drop_index_extras();
     }
-    rc = c->main.query_index(*I, queries, m, st, out, false);
+    st = rtg_stats{};
+    st.n = m;
+    st.d = I->d;
+    st.k = I->k;
+    rc = c->main.query_index(*I, queries, m, st, out, true);
   }
   if (!rc) c->stats = st;
   return rc;

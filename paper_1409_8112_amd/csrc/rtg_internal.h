@@ -387,8 +387,7 @@ struct QueryArgs {
   float lo, hi;             // the FP32 screen of r2 (see PairTest)
   const uint64_t* order;    // [m] queries by place, the index in the low 32 bits (null: as given)
   // by place in the order:
-  uint64_t* qkey;           // [m][k] cell prefix of each query under each grid
-  uint32_t* qlo;            // [m][k] and the cell's first position
+  uint32_t* qlo;            // [m][k] first position of each query's cell under each grid
   uint64_t* qsig;           // [m][W] signature words of each query
   uint32_t* err;            // bit 0: a cell coordinate out of range, bit 1: not finite
   int pb;                   // bits of an index in a packed (query, point) pair

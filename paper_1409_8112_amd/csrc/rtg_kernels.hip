@@ -2274,9 +2274,9 @@ __global__ __launch_bounds__(kBlock) void k_query_order(
   order[q] = ((cell >> (A.cell_bits - bits)) << 32) | (uint64_t)q;
 }
 
-// Of every query under every grid: the cell prefix, and the position in the
-// grid where that cell begins (n for a query that is not finite or out of
-// range); and the query's signature words.  A block takes 64 queries, its
+// Of every query under every grid: the position in the grid where the query's
+// cell begins (n where the cell is empty, and for a query that is not finite
+// or out of range); and its signature words.  A block takes 64 queries, its
 // four waves every fourth grid of a signature word.  The binary search is a
 // chain of dependent reads: tab cuts its first steps (n = 1e6, d = 3: about
 // four instead of twenty).
@@ -2285,7 +2285,7 @@ __global__ __launch_bounds__(kBlock) void k_query_find(
     const QueryArgs A, const double* __restrict__ R, const double* __restrict__ u,
     const int64_t* __restrict__ klo, const KeyLayout* __restrict__ layout,
     const QueryGrid* __restrict__ grids, const uint32_t* __restrict__ tab,
-    uint64_t* __restrict__ qkey, uint32_t* __restrict__ qlo, uint64_t* __restrict__ qsig) {
+    uint32_t* __restrict__ qlo, uint64_t* __restrict__ qsig) {
   __shared__ uint64_t part[kWaves][64];
   const uint32_t lane = lane_id();
   const int w = uniform((int)(threadIdx.x >> 6));
@@ -2322,10 +2322,8 @@ __global__ __launch_bounds__(kBlock) void k_query_find(
         hi = tt[top + 1];
       }
       lo = prefix_lower_bound(G.keys, lo, hi, G.idx_bits, K);
-      if (live) {
-        qkey[(size_t)at * A.k + t] = K;
-        qlo[(size_t)at * A.k + t] = finite && ok ? lo : n;
-      }
+      const bool found = finite && ok && lo < n && (G.keys[min(lo, n - 1u)] >> G.idx_bits) == K;
+      if (live) qlo[(size_t)at * A.k + t] = found ? lo : n;
     }
     part[w][lane] = word;
     __syncthreads();
@@ -2381,8 +2379,9 @@ __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
     for (int x = 0; x < kSigWords; ++x) qw[x] = x < A.W ? A.qsig[(size_t)at * A.W + x] : 0ull;
     for (int t = 0; t < A.k; ++t) {
       const QueryGrid g = A.grids[t];
-      const uint64_t K = A.qkey[(size_t)at * A.k + t];
-      uint32_t pos = live ? A.qlo[(size_t)at * A.k + t] + sub : n;  // (n < 2^31)
+      const uint32_t lo = live ? A.qlo[(size_t)at * A.k + t] : n;
+      const uint64_t K = g.keys[min(lo, n - 1u)] >> g.idx_bits;  // the cell's prefix
+      uint32_t pos = lo + sub;                                   // (n < 2^31)
       // the key and coordinates at a position, loaded one step ahead
       uint64_t key, key_next;
       float c[D > 0 ? D : 1], c_next[D > 0 ? D : 1];
@@ -4204,7 +4203,7 @@ void launch_query_find(const QueryArgs& a, hipStream_t s) {
   const unsigned blocks = (unsigned)((a.m + 63) / 64);
 #define RTG_QF(DD)                                                                             \
   hipLaunchKernelGGL(k_query_find<DD>, dim3(blocks), dim3(kBlock), 0, s, a, a.R, a.u, a.klo,   \
-                     a.layout, a.grids, a.tab, a.qkey, a.qlo, a.qsig)
+                     a.layout, a.grids, a.tab, a.qlo, a.qsig)
   switch (a.d) {
 #define RTG_QF_CASE(DD) \
   case DD: RTG_QF(DD); break;

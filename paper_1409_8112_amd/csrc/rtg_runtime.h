@@ -244,7 +244,7 @@ struct Lane {
                   const double* R, const double* u, Index& I);
   int index_extras(Index& I);
   int query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
-                  rtg_csr* out, bool extras);
+                  rtg_csr* out, bool lean);
   int tiny_query(const float* points, int64_t n, int32_t d, rtg_csr* out, uint64_t handle);
   // One pass of the pipeline over a batch of instances of one dimension
   // (pp: the pass of a plan, or null).
