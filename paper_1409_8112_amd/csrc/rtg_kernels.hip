@@ -1559,18 +1559,21 @@ struct OutStage {
   uint64_t* dst;               // this block's output segment
   unsigned long long* count;   // and its running total
   uint64_t cap;                // the segment's capacity
+  uint32_t seg;
 };
 
 __device__ __forceinline__ OutStage out_stage(const PairsArgs& P, uint64_t* buf) {
   OutStage O;
   O.buf = buf;
-  const uint32_t seg = P.nseg > 1 ? blockIdx.x % P.nseg : 0u;
-  O.dst = P.cand + (size_t)seg * P.cap;
-  O.count = P.cand_count + seg;
+  O.seg = P.nseg > 1 ? blockIdx.x % P.nseg : 0u;
+  O.dst = P.cand + (size_t)O.seg * P.cap;
+  O.count = P.cand_count + O.seg;
   O.cap = P.cap;
   return O;
 }
 
+// SPREAD: the wave goes on to the next segment.
+template <bool SPREAD = false>
 __device__ __forceinline__ void flush_out(const PairsArgs& P, OutStage& O, uint32_t lane) {
   wave_lds_sync();
   if (O.n) {
@@ -1582,6 +1585,11 @@ __device__ __forceinline__ void flush_out(const PairsArgs& P, OutStage& O, uint3
       if (g < O.cap) O.dst[g] = O.buf[e];
     }
     O.n = 0;
+    if constexpr (SPREAD) {
+      O.seg = O.seg + 1 < P.nseg ? O.seg + 1 : 0u;
+      O.dst = P.cand + (size_t)O.seg * P.cap;
+      O.count = P.cand_count + O.seg;
+    }
   }
   wave_lds_sync();
 }
@@ -1624,12 +1632,13 @@ __device__ __forceinline__ uint64_t pack_pair(uint64_t x, uint64_t y, int pair_b
 
 // Appends pair (when keep) to the wave's staging buffer: one slot per
 // keeping lane, in lane order, flushing first if they would not fit.
+template <bool SPREAD = false>
 __device__ __forceinline__ void append_pair(const PairsArgs& P, OutStage& O, uint32_t lane,
                                             bool keep, uint64_t pair) {
   const uint64_t kb = ballot(keep);
   const uint32_t nk = (uint32_t)__popcll(kb);
   if (!nk) return;
-  if (O.n + nk > (uint32_t)kOutBuf) flush_out(P, O, lane);
+  if (O.n + nk > (uint32_t)kOutBuf) flush_out<SPREAD>(P, O, lane);
   if (keep) O.buf[O.n + rank_below(kb)] = pair;
   O.n += nk;
 }
@@ -2347,6 +2356,10 @@ __global__ __launch_bounds__(kBlock) void k_query_find(
 // launch_query_pairs; 1e6 queries took 6.9 ms, now 0.9).  ROWS: the coordinates come from the index's copy in
 // grid order, so that neighbouring lanes read one line; else by point index.
 // The screen is the vector pair screen's: FP32 with FP64 in the band.
+// A wave's pairs go to every output segment in turn: the pairs of a few
+// queries, which one block finds, then fill the segments as evenly as those
+// of many (one query with 76 000 neighbours overflowed its block's segment,
+// and the launch ran again).
 template <int D, bool ROWS>
 __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
   __shared__ uint64_t sOut[kWaves][kOutBuf];
@@ -2444,7 +2457,7 @@ __global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
             }
           }
         }
-        append_pair(P, O, lane, hit, ((uint64_t)q << A.pb) | i);
+        append_pair<true>(P, O, lane, hit, ((uint64_t)q << A.pb) | i);
         pos += G;
         key = key_next;
         if constexpr (D > 0 && ROWS) {

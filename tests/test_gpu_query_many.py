@@ -74,3 +74,21 @@ def test_index_extras_give_way():
         ctx.release_many(held)
         rp, col = _query(ctx, index, qs)
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+
+
+@pytest.mark.parametrize("m", [1, 5])
+def test_many_pairs_of_few_queries_run_once(m):
+    """Some hundred thousand pairs that one block finds: they fit the first
+    guess of their number, so one launch does."""
+    import torch
+    from paper_1409_8112_amd import rtg
+    pts = workloads.uniform_points(200_000, 3, seed=7)
+    qs = (0.5 + 0.02 * workloads.uniform_points(m, 3, seed=8)).astype(np.float32)
+    with rtg.Context(0, arena_bytes=1 << 30) as ctx:
+        index = ctx.index_build(torch.from_numpy(pts).cuda(), 0.45, 4, 2.0, 3)
+        rp, col = _query(ctx, index, qs)
+        launches = ctx.stats()["kernel_launches"][rtg.KERNELS.index("pairs")]
+    ref = oracle.rtg_query(pts, qs, 0.45, 2.0, *rtg.make_transforms(3, 4, 3))
+    assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
+    assert 50_000 * m < len(col) < 1 << 20
+    assert launches == 1
