@@ -2871,15 +2871,25 @@ int Lane::index_extras(Index& I) {
 }
 
 // Queries from which a call orders them by place (their cell under grid 0, on
-// up to 24 bits: three sort passes).  The order costs about 45 us; without
-// it every cell's keys and coordinates come from HBM for each query.  At
-// 65536 queries both ways measure the same (258 against 256 us at n = 1e6,
-// d = 3; 633 against 778 at d = 6; 181 / 175 and 494 / 501 us at n = 5e4),
-// below it the order loses (158 / 117 us at 16384), at 1e6 queries of 1e6
-// points, d = 3, pairs and search take 4.2 ms without and 1.04 with it (1.17
-// on 16 bits).
+// up to 24 bits: three sort passes).  The order costs 45 to 60 us; without it
+// every cell's keys and coordinates come from HBM for each query.  At 1e6
+// queries of 1e6 points, d = 3, a call takes 3.48 ms without and 1.07 with it.
+// At 70000 queries it gains where the index is large (1e6 points, d = 6: 1106
+// us without, 837 with; 1e5: 454 and 388) and loses where the caches hold much
+// of it (20000 points: d = 3 176 and 200, d = 9 398 and 439, d = 16 569 and
+// 643), so an index of fewer points than kQueryOrderMin takes twice as many
+// queries; at 300000 it gains for all but the smallest (5000 points, d = 6:
+// 820 and 593; 1000 points, d = 9: 555 and 572).
 constexpr int64_t kQueryOrderMin = 65536;
 constexpr int kQueryOrderBits = 24;
+// Members of a cell that a query's few lanes test; a wave takes the rest
+// (k_query_long).  Up to d = 6 cells are of a size and those few lanes are
+// the better way up to the longest ordinary ones: 1e6 queries of 1e6 points,
+// d = 6, 4.75 / 5.51 / 6.22 ms with 256 / 128 / 64, 5003 of 50021 points 141 /
+// 165 / 184 us.  Above, cells of a few points lie beside those of hundreds and
+// a wave's queries wait for its longest: 70000 queries of 20000 points, d = 9,
+// 806 / 662 / 621 us, 20000 of 1e5 points 357 / 336 / 357.
+uint32_t query_walk(int d) { return d <= 6 ? 256 : 128; }
 
 // lean: in the least memory, without what a call only has for speed (the
 // index's tables, an order of the queries, several output segments).
@@ -2901,12 +2911,13 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   const int k = I.k, d = I.d;
   uint32_t* qlo = S.get<uint32_t>((size_t)m * k);
   uint64_t* qsig = S.get<uint64_t>((size_t)m * I.sig_W);
-  // the output segments' counts, then a filter's count and the error bits
-  // ([0] the queries', [1] the list build's)
-  constexpr uint32_t kWords = kCandSegments + 2;
+  // the output segments' counts, whether cells were left to the second
+  // launch, a filter's count and the error bits ([0] the queries', [1] the
+  // list build's)
+  constexpr uint32_t kWords = kCandSegments + 3;
   unsigned long long* counts = S.get<unsigned long long>(kWords);
   if (!qlo || !qsig || !counts) return RTG_ENOMEM;
-  unsigned long long* counter = counts + kCandSegments;
+  unsigned long long* counter = counts + kCandSegments + 1;
   uint32_t* err = reinterpret_cast<uint32_t*>(counter + 1);
   launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kWords, stream);
   QueryArgs A{};
@@ -2942,10 +2953,12 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   A.lo = pt.lo;
   A.hi = pt.hi;
   A.cand_count = counts;
+  A.long_cells = counts + kCandSegments;
+  A.walk = query_walk(d);
   // Queries in the order of their place: those that read the same cells run
   // side by side, so the cells come from the caches.  (Without room the
   // queries run as given.)
-  if (!lean && m >= kQueryOrderMin) {
+  if (!lean && m >= kQueryOrderMin && (I.n >= kQueryOrderMin || m >= 2 * kQueryOrderMin)) {
     const int bits = std::min(A.cell_bits, kQueryOrderBits);
     uint64_t* o1 = S.get<uint64_t>((size_t)m);
     uint64_t* o2 = S.get<uint64_t>((size_t)m);
@@ -2983,6 +2996,12 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
     const uint32_t errh = (uint32_t)got[kWords - 1];
     if (errh & 2u) return RTG_EINVAL;
     if (errh & 1u) return RTG_ERANGE;
+    if (got[kCandSegments]) {
+      kbegin(RTG_K_PAIRS);
+      launch_query_long(A, stream);
+      kend(RTG_K_PAIRS, 0.0);
+      if ((rc = read_back(counts, sizeof(got), got))) return rc;
+    }
     C = most = 0;
     for (uint32_t g = 0; g < A.nseg; ++g) {
       C += got[g];
@@ -2999,7 +3018,7 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
       cand = S.get<uint64_t>(C);
     }
     if (!cand) return RTG_ENOMEM;
-    launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kCandSegments, stream);
+    launch_fill_u64(reinterpret_cast<uint64_t*>(counts), 0ull, kCandSegments + 1, stream);
   }
   // The row-bucket lists read the segments as they are; the filter and the
   // sorted build take one array.

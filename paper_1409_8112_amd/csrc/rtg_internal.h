@@ -366,6 +366,7 @@ struct QueryGrid {
   int32_t idx_bits;     // > 0: the point index in the low idx_bits of the keys
   int32_t pad;
 };
+constexpr uint32_t kQueryLong = 0x80000000u;
 struct QueryArgs {
   const float* queries;     // [m][d] row-major
   int64_t m;
@@ -388,10 +389,13 @@ struct QueryArgs {
   const uint64_t* order;    // [m] queries by place, the index in the low 32 bits (null: as given)
   // by place in the order:
   uint32_t* qlo;            // [m][k] first position of each query's cell under each grid
+                            // (n: none), with kQueryLong where it has more than walk members
   uint64_t* qsig;           // [m][W] signature words of each query
   uint32_t* err;            // bit 0: a cell coordinate out of range, bit 1: not finite
   int pb;                   // bits of an index in a packed (query, point) pair
-  uint32_t lanes;           // lanes per query (set by launch_query_pairs)
+  uint32_t lanes;           // lanes per query, cells per wave (set by the launches)
+  uint32_t walk;            // members of a cell that launch_query_pairs tests (multiple of 64)
+  unsigned long long* long_cells;  // set to 1 where a cell has more
   uint64_t* cand;           // nseg output segments of cap pairs each (see PairsArgs)
   uint64_t cap;
   uint32_t nseg;
@@ -401,6 +405,8 @@ struct QueryArgs {
 void launch_query_order(const QueryArgs& a, int bits, uint64_t* order, hipStream_t s);
 void launch_query_find(const QueryArgs& a, hipStream_t s);
 void launch_query_pairs(const QueryArgs& a, hipStream_t s);
+// The rest of the cells with more than a.walk members (after launch_query_pairs).
+void launch_query_long(const QueryArgs& a, hipStream_t s);
 // What an index keeps beside its keys where memory allows: rows (dimensions
 // query_rows_fit takes) and tab of QueryArgs.
 bool query_rows_fit(int d);

@@ -2347,124 +2347,210 @@ __global__ __launch_bounds__(kBlock) void k_query_find(
   else if (bad) atomicOr(A.err, 1u);
 }
 
-// Pairs (query, indexed point).  A.lanes lanes of a wave take a query and
-// walk the members of its cell under each grid together, from the cell's
-// first position while the keys' prefix is the cell's: the cells are short
-// (some tens of points), so a whole wave per query idled most of its lanes
-// and waited on every cell's chain of loads.  Few queries get more lanes
-// each, many get four, which is what fills the chip (see
-// launch_query_pairs; 1e6 queries took 6.9 ms, now 0.9).  ROWS: the coordinates come from the index's copy in
-// grid order, so that neighbouring lanes read one line; else by point index.
-// The screen is the vector pair screen's: FP32 with FP64 in the band.
-// A wave's pairs go to every output segment in turn: the pairs of a few
-// queries, which one block finds, then fill the segments as evenly as those
-// of many (one query with 76 000 neighbours overflowed its block's segment,
-// and the launch ran again).
-template <int D, bool ROWS>
-__global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
-  __shared__ uint64_t sOut[kWaves][kOutBuf];
-  const uint32_t lane = lane_id();
-  const int w = threadIdx.x >> 6;
+// A query that lanes of a wave are at, and its output.
+template <int D>
+struct QueryAt {
+  int64_t at, q;  // its place in the order, its index
+  float c[D > 0 ? D : 1];
+  uint64_t sw[kSigWords];
+};
+
+template <int D>
+__device__ __forceinline__ QueryAt<D> query_at(const QueryArgs& A, int64_t at) {
   const int d = D > 0 ? D : A.d;
-  PairsArgs P{};  // output staging shares the pair kernels' machinery
+  QueryAt<D> Q;
+  Q.at = at;
+  Q.q = A.order ? (int64_t)(uint32_t)A.order[at] : at;
+  if (D > 0) {
+#pragma unroll
+    for (int l = 0; l < (D > 0 ? D : 1); ++l) Q.c[l] = A.queries[Q.q * d + l];
+  }
+#pragma unroll
+  for (int x = 0; x < kSigWords; ++x) Q.sw[x] = x < A.W ? A.qsig[(size_t)at * A.W + x] : 0ull;
+  return Q;
+}
+
+// G lanes (this one the sub-th of them) test the query's cell under grid t,
+// which begins at position lo, from member `from` on: a member a lane and
+// step, at most steps steps.  True if this lane's next member is in the cell
+// too.  ROWS: the coordinates come from the index's copy in grid order, so
+// that neighbouring lanes read one line; else by point index.  The screen is
+// the vector pair screen's: FP32 with FP64 in the band.
+template <int D, bool ROWS>
+__device__ __forceinline__ bool walk_cell(const QueryArgs& A, const PairsArgs& P, OutStage& O,
+                                          const QueryAt<D>& Q, int t, uint32_t lo, uint32_t from,
+                                          uint32_t G, uint32_t sub, uint32_t steps,
+                                          uint32_t lane) {
+  const int d = D > 0 ? D : A.d;
+  const uint32_t n = (uint32_t)A.n;
+  const QueryGrid g = A.grids[t];
+  const uint64_t K = g.keys[min(lo, n - 1u)] >> g.idx_bits;  // the cell's prefix
+  uint32_t pos = lo + from + sub;                            // (n < 2^31)
+  // the key and coordinates at a position, loaded one step ahead
+  uint64_t key, key_next;
+  float c[D > 0 ? D : 1], c_next[D > 0 ? D : 1];
+  const float* rows = ROWS ? A.rows + (size_t)t * A.n * D : nullptr;
+  auto load = [&](uint32_t p, uint64_t& kk, float* cc) {
+    const uint32_t x = min(p, n - 1u);
+    kk = g.keys[x];
+    if constexpr (D > 0 && ROWS) {
+      const float* row = rows + (size_t)x * D;
+#pragma unroll
+      for (int l = 0; l < D; ++l) cc[l] = row[l];
+    }
+  };
+  load(pos, key, c);
+  for (;; --steps) {
+    const bool in = pos < n && (key >> g.idx_bits) == K;
+    if (!ballot(in)) return false;
+    if (steps == 0) return in;
+    load(pos + G, key_next, c_next);
+    uint32_t i = 0;
+    if (!(D > 0 && ROWS) && in)
+      i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
+    float d2 = 0.0f;
+    const float* row = (D > 0 && ROWS) ? c : A.pts + (size_t)i * d;
+    if (D > 0) {
+#pragma unroll
+      for (int l = 0; l < (D > 0 ? D : 1); ++l) {
+        const float df = Q.c[l] - row[l];
+        d2 = __builtin_fmaf(df, df, d2);
+      }
+    } else {
+      // eight axes at a time, their loads before the first is used
+      for (int l0 = 0; l0 < d; l0 += 8) {
+        float a[8], b[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const int l = min(l0 + x, d - 1);
+          a[x] = A.queries[Q.q * d + l];
+          b[x] = row[l];
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+          const float df = l0 + x < d ? a[x] - b[x] : 0.0f;
+          d2 = __builtin_fmaf(df, df, d2);
+        }
+      }
+    }
+    bool hit = in && d2 <= A.hi;
+    if (hit) {
+      if (d2 > A.lo) {
+        // the band: as the definition decides
+        double s2 = 0.0;
+        for (int l = 0; l < d; ++l) {
+          const double dl = (double)(D > 0 ? Q.c[D > 0 ? l : 0] : A.queries[Q.q * d + l]) -
+                            (double)row[l];
+          s2 = s2 + dl * dl;
+        }
+        hit = s2 <= A.r2;
+      }
+      if (D > 0 && ROWS)
+        i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
+      if (t > 0) {
+        // dropped if an earlier grid put the query and the point in one cell
+        const int nw = (t - 1) / A.gpw + 1;
+        for (int x = 0; x < nw && hit; ++x) {
+          const uint64_t xw =
+              (x == 0 ? Q.sw[0] : x == 1 ? Q.sw[1] : A.qsig[(size_t)Q.at * A.W + x]) ^
+              A.sig[(size_t)i * A.W + x];
+          const int ng = min(A.gpw, t - x * A.gpw);
+          const uint64_t keep = (ng * A.g >= 64) ? ~0ull : ((1ull << (ng * A.g)) - 1ull);
+          hit = (((xw - A.lows) & ~xw & A.highs) & keep) == 0ull;
+        }
+      }
+    }
+    append_pair<true>(P, O, lane, hit, ((uint64_t)Q.q << A.pb) | i);
+    pos += G;
+    key = key_next;
+    if constexpr (D > 0 && ROWS) {
+#pragma unroll
+      for (int l = 0; l < D; ++l) c[l] = c_next[l];
+    }
+  }
+}
+
+// Output staging shares the pair kernels' machinery.  A wave's pairs go to
+// every output segment in turn: the pairs of a few queries, which one block
+// finds, then fill the segments as evenly as those of many (one query with
+// 76 000 neighbours overflowed its block's segment, and the launch ran again).
+__device__ __forceinline__ PairsArgs query_output(const QueryArgs& A) {
+  PairsArgs P{};
   P.cand = A.cand;
   P.cap = A.cap;
   P.cand_count = A.cand_count;
   P.nseg = A.nseg;
+  return P;
+}
+
+// Pairs (query, indexed point).  A.lanes lanes of a wave take a query and
+// walk the members of its cell under each grid together, from the cell's
+// first position while the keys' prefix is the cell's: most cells are short
+// (some tens of points), so a whole wave per query idled most of its lanes
+// and waited on every cell's chain of loads.  Few queries get more lanes
+// each, many get four (16 above d = 6), which is what fills the chip (see
+// launch_query_pairs; 1e6 queries of 1e6 points, d = 3, took 6.9 ms, now
+// 0.9).  Members from A.walk on are left to k_query_long: the cell is marked
+// (kQueryLong in qlo, and *A.long_cells).  Without that limit a few lanes
+// walked every crowded cell to its end while the wave's other queries waited:
+// 64 of 70000 queries in a cell of 1e5 points took 195 ms, one wave per query
+// 18.3; 70000 queries in 1e5 points, d = 12 (cells of thousands), 8.3 against
+// 3.8 ms.
+template <int D, bool ROWS>
+__global__ __launch_bounds__(kBlock) void k_query_pairs(const QueryArgs A) {
+  __shared__ uint64_t sOut[kWaves][kOutBuf];
+  const uint32_t lane = lane_id();
+  const int w = uniform((int)(threadIdx.x >> 6));
+  const PairsArgs P = query_output(A);
   OutStage O = out_stage(P, sOut[w]);
-  const uint32_t n = (uint32_t)A.n;
   const uint32_t G = A.lanes, sub = lane & (G - 1u);
   const int64_t per_wave = 64 / G;
   const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  bool any = false;
   for (int64_t q0 = ((int64_t)blockIdx.x * kWaves + w) * per_wave; q0 < A.m;
        q0 += nwaves * per_wave) {
-    const int64_t at_ = q0 + lane / G;  // place in the order
+    const int64_t at_ = q0 + lane / G;
     const bool live = at_ < A.m;
-    const int64_t at = live ? at_ : A.m - 1;
-    const int64_t q = A.order ? (int64_t)(uint32_t)A.order[at] : at;
-    float qc[D > 0 ? D : 1];
-    if (D > 0) {
-#pragma unroll
-      for (int l = 0; l < (D > 0 ? D : 1); ++l) qc[l] = A.queries[q * d + l];
-    }
-    uint64_t qw[kSigWords];
-#pragma unroll
-    for (int x = 0; x < kSigWords; ++x) qw[x] = x < A.W ? A.qsig[(size_t)at * A.W + x] : 0ull;
+    const QueryAt<D> Q = query_at<D>(A, live ? at_ : A.m - 1);
+    uint32_t* qlo = A.qlo + (size_t)Q.at * A.k;
     for (int t = 0; t < A.k; ++t) {
-      const QueryGrid g = A.grids[t];
-      const uint32_t lo = live ? A.qlo[(size_t)at * A.k + t] : n;
-      const uint64_t K = g.keys[min(lo, n - 1u)] >> g.idx_bits;  // the cell's prefix
-      uint32_t pos = lo + sub;                                   // (n < 2^31)
-      // the key and coordinates at a position, loaded one step ahead
-      uint64_t key, key_next;
-      float c[D > 0 ? D : 1], c_next[D > 0 ? D : 1];
-      const float* rows = ROWS ? A.rows + (size_t)t * A.n * D : nullptr;
-      auto load = [&](uint32_t p, uint64_t& kk, float* cc) {
-        const uint32_t x = min(p, n - 1u);
-        kk = g.keys[x];
-        if constexpr (D > 0 && ROWS) {
-          const float* row = rows + (size_t)x * D;
-#pragma unroll
-          for (int l = 0; l < D; ++l) cc[l] = row[l];
-        }
-      };
-      load(pos, key, c);
-      for (;;) {
-        const bool in = pos < n && (key >> g.idx_bits) == K;
-        if (!ballot(in)) break;
-        load(pos + G, key_next, c_next);
-        uint32_t i = 0;
-        if (!(D > 0 && ROWS) && in)
-          i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
-        float d2 = 0.0f;
-        const float* row = (D > 0 && ROWS) ? c : A.pts + (size_t)i * d;
-        if (D > 0) {
-#pragma unroll
-          for (int l = 0; l < (D > 0 ? D : 1); ++l) {
-            const float df = qc[l] - row[l];
-            d2 = __builtin_fmaf(df, df, d2);
-          }
-        } else {
-          for (int l = 0; l < d; ++l) {
-            const float df = A.queries[q * d + l] - row[l];
-            d2 = __builtin_fmaf(df, df, d2);
-          }
-        }
-        bool hit = in && d2 <= A.hi;
-        if (hit) {
-          if (d2 > A.lo) {
-            // the band: as the definition decides
-            double s2 = 0.0;
-            for (int l = 0; l < d; ++l) {
-              const double dl = (double)(D > 0 ? qc[D > 0 ? l : 0] : A.queries[q * d + l]) -
-                                (double)row[l];
-              s2 = s2 + dl * dl;
-            }
-            hit = s2 <= A.r2;
-          }
-          if (D > 0 && ROWS)
-            i = g.idx_bits ? (uint32_t)(key & ((1ull << g.idx_bits) - 1ull)) : g.idx[pos];
-          if (t > 0) {
-            // dropped if an earlier grid put the query and the point in one cell
-            const int nw = (t - 1) / A.gpw + 1;
-            for (int x = 0; x < nw && hit; ++x) {
-              const uint64_t xw =
-                  (x == 0 ? qw[0] : x == 1 ? qw[1] : A.qsig[(size_t)at * A.W + x]) ^
-                  A.sig[(size_t)i * A.W + x];
-              const int ng = min(A.gpw, t - x * A.gpw);
-              const uint64_t keep = (ng * A.g >= 64) ? ~0ull : ((1ull << (ng * A.g)) - 1ull);
-              hit = (((xw - A.lows) & ~xw & A.highs) & keep) == 0ull;
-            }
-          }
-        }
-        append_pair<true>(P, O, lane, hit, ((uint64_t)q << A.pb) | i);
-        pos += G;
-        key = key_next;
-        if constexpr (D > 0 && ROWS) {
-#pragma unroll
-          for (int l = 0; l < D; ++l) c[l] = c_next[l];
-        }
-      }
+      const uint32_t lo = live ? qlo[t] & ~kQueryLong : (uint32_t)A.n;
+      const bool more = walk_cell<D, ROWS>(A, P, O, Q, t, lo, 0u, G, sub, A.walk / G, lane);
+      // (the lane with the next member is the group's first)
+      if (more && sub == 0) qlo[t] = lo | kQueryLong;
+      any |= more;
+    }
+  }
+  if (any) *A.long_cells = 1ull;  // (every such lane writes the same)
+  flush_out(P, O, lane);
+}
+
+// The marked cells' members from A.walk on, a whole wave to a cell.  The
+// cells of a wave lie a long way apart in the order, so that the cells of
+// queries of one crowded place go to different waves.
+template <int D, bool ROWS>
+__global__ __launch_bounds__(kBlock) void k_query_long(const QueryArgs A) {
+  __shared__ uint64_t sOut[kWaves][kOutBuf];
+  const uint32_t lane = lane_id();
+  const int w = uniform((int)(threadIdx.x >> 6));
+  const PairsArgs P = query_output(A);
+  OutStage O = out_stage(P, sOut[w]);
+  const int64_t cells = A.m * A.k;
+  const int64_t share = (cells + A.lanes - 1) / A.lanes;  // A.lanes cells of a wave
+  const int64_t nwaves = (int64_t)gridDim.x * kWaves;
+  for (int64_t x = (int64_t)blockIdx.x * kWaves + w; x < share; x += nwaves) {
+    const int64_t mine = x + (int64_t)lane * share;
+    const uint32_t word = lane < A.lanes && mine < cells ? A.qlo[mine] : 0u;
+    uint64_t todo = ballot((word & kQueryLong) != 0u);
+    while (todo) {
+      const int j = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int64_t e = x + (int64_t)j * share;
+      const int64_t at = e / A.k;
+      const int t = (int)(e - at * A.k);
+      const QueryAt<D> Q = query_at<D>(A, at);
+      const uint32_t lo = lane_value(word, j) & ~kQueryLong;
+      (void)walk_cell<D, ROWS>(A, P, O, Q, t, lo, A.walk, 64u, lane, ~0u, lane);
     }
   }
   flush_out(P, O, lane);
@@ -4175,9 +4261,13 @@ void launch_gather_units(const PairsArgs& a, const uint64_t* sig, float* spts, u
 // Dimensions with their own query kernels; the others read coordinates one
 // by one.
 #define RTG_QUERY_DIMS(X) \
-  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(16)
+  RTG_QUERY_ROW_DIMS(X) X(16)
+#define RTG_QUERY_ROW_DIMS(X) \
+  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12)
 
-bool query_rows_fit(int d) { return (d >= 1 && d <= 12) || d == 16; }
+// (At d = 16 a row is half a line wherever it lies: 300000 queries of 20000
+// points, 1644 us from the copy, 1510 by point index.)
+bool query_rows_fit(int d) { return d >= 1 && d <= 12; }
 
 void launch_query_rows(const QueryGrid* grids, int k, int64_t n, int d, const float* pts,
                        float* rows, hipStream_t s) {
@@ -4185,7 +4275,7 @@ void launch_query_rows(const QueryGrid* grids, int k, int64_t n, int d, const fl
   switch (d) {
 #define RTG_QR(DD) \
   case DD: hipLaunchKernelGGL(k_query_rows<DD>, grid, dim3(kBlock), 0, s, grids, n, pts, rows); break;
-    RTG_QUERY_DIMS(RTG_QR)
+    RTG_QUERY_ROW_DIMS(RTG_QR)
 #undef RTG_QR
   }
 }
@@ -4227,29 +4317,51 @@ void launch_query_find(const QueryArgs& a, hipStream_t s) {
 #undef RTG_QF
 }
 
-void launch_query_pairs(const QueryArgs& args, hipStream_t s) {
-  if (args.m <= 0 || args.n <= 0) return;
-  QueryArgs a = args;
-  // lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
-  // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; few queries get as many as
-  // give the chip 2^18 lanes
-  a.lanes = 4;
-  while (a.lanes < 64 && (uint64_t)a.m * a.lanes < (1u << 18)) a.lanes *= 2;
-  uint64_t blocks = ((uint64_t)a.m * a.lanes + kBlock - 1) / kBlock;
-  if (blocks > 4096) blocks = 4096;
-#define RTG_QP(DD, RR) \
-  hipLaunchKernelGGL((k_query_pairs<DD, RR>), dim3((unsigned)blocks), dim3(kBlock), 0, s, a)
+static void query_dispatch(const QueryArgs& a, unsigned blocks, bool long_cells, hipStream_t s) {
+#define RTG_QP(DD, RR)                                                                          \
+  do {                                                                                          \
+    if (long_cells)                                                                             \
+      hipLaunchKernelGGL((k_query_long<DD, RR>), dim3(blocks), dim3(kBlock), 0, s, a);          \
+    else                                                                                        \
+      hipLaunchKernelGGL((k_query_pairs<DD, RR>), dim3(blocks), dim3(kBlock), 0, s, a);         \
+  } while (0)
   switch (a.d) {
-#define RTG_QP_CASE(DD)          \
-  case DD:                       \
+#define RTG_QP_CASE(DD)           \
+  case DD:                        \
     if (a.rows) RTG_QP(DD, true); \
-    else RTG_QP(DD, false);      \
+    else RTG_QP(DD, false);       \
     break;
-    RTG_QUERY_DIMS(RTG_QP_CASE)
+    RTG_QUERY_ROW_DIMS(RTG_QP_CASE)
+    case 16: RTG_QP(16, false); break;
 #undef RTG_QP_CASE
     default: RTG_QP(0, false);
   }
 #undef RTG_QP
+}
+
+void launch_query_pairs(const QueryArgs& args, hipStream_t s) {
+  if (args.m <= 0 || args.n <= 0) return;
+  QueryArgs a = args;
+  // lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
+  // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; above d = 6, where cells
+  // are longer and uneven, 16 (1e5 queries of 1e5 points, d = 9: 1252 us with
+  // 4, 1133 with 16; 70000 of 1e5, d = 12: 1893 and 1743); few queries get as
+  // many as give the chip 2^18 lanes
+  a.lanes = a.d > 6 ? 16 : 4;
+  while (a.lanes < 64 && (uint64_t)a.m * a.lanes < (1u << 18)) a.lanes *= 2;
+  uint64_t blocks = ((uint64_t)a.m * a.lanes + kBlock - 1) / kBlock;
+  if (blocks > 4096) blocks = 4096;
+  query_dispatch(a, (unsigned)blocks, false, s);
+}
+
+void launch_query_long(const QueryArgs& args, hipStream_t s) {
+  if (args.m <= 0 || args.n <= 0) return;
+  // about 16384 waves, each with as many cells to look at (at most 64)
+  QueryArgs a = args;
+  const uint64_t cells = (uint64_t)a.m * (uint64_t)a.k;
+  a.lanes = (uint32_t)std::min<uint64_t>(64, (cells + 16383) / 16384);
+  const uint64_t waves = std::min<uint64_t>(16384, (cells + a.lanes - 1) / a.lanes);
+  query_dispatch(a, (unsigned)((waves + kWaves - 1) / kWaves), true, s);
 }
 
 void launch_seg_compact(const uint64_t* src, uint64_t seg_cap, const unsigned long long* cnt,

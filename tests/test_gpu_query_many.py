@@ -79,7 +79,8 @@ def test_index_extras_give_way():
 @pytest.mark.parametrize("m", [1, 5])
 def test_many_pairs_of_few_queries_run_once(m):
     """Some hundred thousand pairs that one block finds: they fit the first
-    guess of their number, so one launch does."""
+    guess of their number, so one launch does, and one more for the cells
+    of so many points that a query's own lanes do not finish."""
     import torch
     from paper_1409_8112_amd import rtg
     pts = workloads.uniform_points(200_000, 3, seed=7)
@@ -91,4 +92,29 @@ def test_many_pairs_of_few_queries_run_once(m):
     ref = oracle.rtg_query(pts, qs, 0.45, 2.0, *rtg.make_transforms(3, 4, 3))
     assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
     assert 50_000 * m < len(col) < 1 << 20
-    assert launches == 1
+    assert launches == 2
+
+
+@pytest.mark.parametrize("d", [1, 3, 6, 13])
+@pytest.mark.parametrize("m", [1, 70, 5000, 70000])
+@pytest.mark.parametrize("crowd", [255, 256, 257, 320, 3000])
+def test_crowded_cells(d, m, crowd):
+    """Cells of as many points as a query's own lanes test, and of more, which
+    a wave finishes: with and without tables, in order and as given."""
+    import torch
+    from paper_1409_8112_amd import rtg
+    rng = np.random.default_rng(crowd + d)
+    r, k, alpha, seed = 0.03, 3, 2.0, 5
+    pts = rng.random((4000 + crowd, d)).astype(np.float32)
+    pts[::2][:crowd // 2] = (0.4 + 0.001 * rng.random((crowd // 2, d)))
+    pts[1::2][:crowd - crowd // 2] = (0.7 + 0.02 * rng.random((crowd - crowd // 2, d)))
+    qs = rng.random((m, d)).astype(np.float32)
+    near = rng.permutation(m)[:min(m, 60)]
+    qs[near] = pts[rng.integers(0, crowd, len(near))] + 0.001
+    with rtg.Context(0, arena_bytes=1 << 30) as ctx:
+        index = ctx.index_build(torch.from_numpy(pts).cuda(), r, k, alpha, seed)
+        rp, col = _query(ctx, index, qs)
+    rows = np.union1d(near, rng.permutation(m)[:100])
+    ref = oracle.rtg_query(pts, qs[rows], r, alpha, *rtg.make_transforms(seed, k, d))
+    assert np.array_equal(np.diff(rp)[rows], np.diff(ref.row_ptr))
+    assert np.array_equal(np.concatenate([col[rp[i]:rp[i + 1]] for i in rows]), ref.col)
