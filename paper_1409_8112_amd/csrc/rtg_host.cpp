@@ -2888,8 +2888,13 @@ constexpr int kQueryOrderBits = 24;
 // d = 6, 4.75 / 5.51 / 6.22 ms with 256 / 128 / 64, 5003 of 50021 points 141 /
 // 165 / 184 us.  Above, cells of a few points lie beside those of hundreds and
 // a wave's queries wait for its longest: 70000 queries of 20000 points, d = 9,
-// 806 / 662 / 621 us, 20000 of 1e5 points 357 / 336 / 357.
-uint32_t query_walk(int d) { return d <= 6 ? 256 : 128; }
+// 806 / 662 / 621 us, 20000 of 1e5 points 357 / 336 / 357.  Few queries, with
+// more lanes each, test 16 members a lane: another launch and the wait before
+// it cost them more (5003 of 50021 points, d = 6, in a fresh index: 360 us with
+// 256 members, 344 with 1024).
+uint32_t query_walk(int d, uint32_t lanes) {
+  return lanes > 16 ? 16 * lanes : d <= 6 ? 256 : 128;
+}
 
 // lean: in the least memory, without what a call only has for speed (the
 // index's tables, an order of the queries, several output segments).
@@ -2954,7 +2959,7 @@ int Lane::query_index(Index& I, const float* queries, int64_t m, rtg_stats& st,
   A.hi = pt.hi;
   A.cand_count = counts;
   A.long_cells = counts + kCandSegments;
-  A.walk = query_walk(d);
+  A.walk = query_walk(d, query_lanes(d, m));
   // Queries in the order of their place: those that read the same cells run
   // side by side, so the cells come from the caches.  (Without room the
   // queries run as given.)

@@ -404,6 +404,7 @@ struct QueryArgs {
 // order[q] = the top bits (at most 32) of query q's cell under grid 0, above q.
 void launch_query_order(const QueryArgs& a, int bits, uint64_t* order, hipStream_t s);
 void launch_query_find(const QueryArgs& a, hipStream_t s);
+uint32_t query_lanes(int d, int64_t m);
 void launch_query_pairs(const QueryArgs& a, hipStream_t s);
 // The rest of the cells with more than a.walk members (after launch_query_pairs).
 void launch_query_long(const QueryArgs& a, hipStream_t s);

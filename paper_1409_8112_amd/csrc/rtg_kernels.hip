@@ -4339,16 +4339,21 @@ static void query_dispatch(const QueryArgs& a, unsigned blocks, bool long_cells,
 #undef RTG_QP
 }
 
+// Lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
+// 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; above d = 6, where cells are
+// longer and uneven, 16 (1e5 queries of 1e5 points, d = 9: 1252 us with 4,
+// 1133 with 16; 70000 of 1e5, d = 12: 1893 and 1743); few queries get as many
+// as give the chip 2^18 lanes.
+uint32_t query_lanes(int d, int64_t m) {
+  uint32_t lanes = d > 6 ? 16 : 4;
+  while (lanes < 64 && (uint64_t)m * lanes < (1u << 18)) lanes *= 2;
+  return lanes;
+}
+
 void launch_query_pairs(const QueryArgs& args, hipStream_t s) {
   if (args.m <= 0 || args.n <= 0) return;
   QueryArgs a = args;
-  // lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
-  // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; above d = 6, where cells
-  // are longer and uneven, 16 (1e5 queries of 1e5 points, d = 9: 1252 us with
-  // 4, 1133 with 16; 70000 of 1e5, d = 12: 1893 and 1743); few queries get as
-  // many as give the chip 2^18 lanes
-  a.lanes = a.d > 6 ? 16 : 4;
-  while (a.lanes < 64 && (uint64_t)a.m * a.lanes < (1u << 18)) a.lanes *= 2;
+  a.lanes = query_lanes(a.d, a.m);
   uint64_t blocks = ((uint64_t)a.m * a.lanes + kBlock - 1) / kBlock;
   if (blocks > 4096) blocks = 4096;
   query_dispatch(a, (unsigned)blocks, false, s);

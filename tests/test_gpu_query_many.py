@@ -97,7 +97,7 @@ def test_many_pairs_of_few_queries_run_once(m):
 
 @pytest.mark.parametrize("d", [1, 3, 6, 13])
 @pytest.mark.parametrize("m", [1, 70, 5000, 70000])
-@pytest.mark.parametrize("crowd", [255, 256, 257, 320, 3000])
+@pytest.mark.parametrize("crowd", [128, 256, 257, 1025, 3000])
 def test_crowded_cells(d, m, crowd):
     """Cells of as many points as a query's own lanes test, and of more, which
     a wave finishes: with and without tables, in order and as given."""
