@@ -301,15 +301,19 @@ size_t Ctx::pass_bytes_bound(int64_t n, int32_t d, int32_t k, double alpha, uint
 }
 
 // Hashed keys: from six radix passes on (clustered d12: 64 bits, eight passes
-// with values beside the keys), three passes of plain keys instead.  A hash of
-// h bits adds about n^2 / 2^(h + 1) tests per grid, 0.5e6 of 1.6e9 at
-// n = 4e6, and the check of the accepted pairs' cells costs the pair kernel
-// 5%: sort 2.15 -> 0.66 ms, pairs 7.19 -> 7.54, a call 12.25 -> 11.18 (on 32
-// bits, a pass more, 11.33).  At five passes the two are even (uniform d12
-// requests).  Below 2^20 keys a pass is its launches' time and the exact keys
-// stay, with their band per cell.
-constexpr int kHashBits = 24, kHashAbove = 40;
-constexpr int64_t kHashKeys = int64_t(1) << 20;
+// with values beside the keys), three passes of plain keys instead, or four
+// where the largest instance has more than kHashFew points.  A hash of h bits
+// adds about n^2 / 2^(h + 1) tests per grid, and for points that mostly have a
+// cell to themselves as many units: 4e6 such points, d = 9, k = 8, took 4.89 ms
+// with 24 bits and 1.66 with 32 (3.51 with their exact keys), 1e6 0.72 and
+// 0.52 (0.86); where cells are full the fourth pass shows (clustered d12, 4e6
+// points: 1% of the call; 7e5: 1.71 and 1.80 ms).  The check of the accepted
+// pairs' cells costs the pair kernel 5%.  At five passes hashed and exact keys
+// are even (uniform d12 requests).  Below 2^20 keys a pass is its launches'
+// time and the exact keys stay, with their band per cell.
+constexpr int kHashAbove = 40;
+constexpr int64_t kHashKeys = int64_t(1) << 20, kHashFew = int64_t(1) << 20;
+constexpr int hash_bits(int64_t nmax) { return nmax <= kHashFew ? 24 : 32; }
 
 int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const double* R,
                const double* u, const double* inv_c, const double* alpha, const float* lo,
@@ -358,7 +362,7 @@ int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const doub
   if (bmin > 32) return RTG_ERANGE;
   for (int j = 0; j < d; ++j) need[j] = std::max(need[j], bmin);
 
-  // Cells wider than four radix passes' bits, in a large batch: kHashBits bits
+  // Cells wider than four radix passes' bits, in a large batch: hash_bits bits
   // of a hash of the cell (the pair kernels then check the cells of the pairs
   // they accept, so a collision only adds tests).
   int exact_bits = 0;
@@ -372,7 +376,7 @@ int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const doub
     const int seg_bits = tb > 1 ? ceil_log2((uint64_t)tb) : 0;
     const int avail = 64 - seg_bits;
     std::vector<int> b = need;
-    int total = hash ? kHashBits : exact_bits;
+    int total = hash ? hash_bits(nmax) : exact_bits;
     // Narrow the widest fields first, never below bmin.
     while (total > avail) {
       int jw = -1;

@@ -365,8 +365,10 @@ __device__ __forceinline__ constexpr uint32_t hash_weight(int j, int h) {
 // range.  The point is p (D > 0) or soa[l n + i], l < d.  C holds both results
 // (fields are taken modulo their width, at most 32 bits, so 32-bit differences
 // are exact).  HASH: instead of the fields side by side, layout->hashed bits
-// of a hash of all of them: two linear hashes (full-rate 24-bit products), one
-// mixed before they meet so that no difference of cells collides throughout.
+// of a hash of all of them: two linear hashes of the fields' low 24 bits
+// (full-rate 24-bit products), one mixed before they meet so that no
+// difference of cells collides throughout, except where every axis differs by
+// a multiple of 2^24 cells.
 template <int D, typename C, bool HASH = false>
 __device__ __forceinline__ bool pack_cell(const double* __restrict__ Rt,
                                           const double* __restrict__ ut,
