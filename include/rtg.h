@@ -426,6 +426,12 @@ int rtg_get_stats(rtg_ctx *ctx, rtg_stats *out);
 int rtg_debug_cell_coords(rtg_ctx *ctx, const float *points, int64_t n, int32_t d, double r,
                           double alpha, const double *R, const double *u, int64_t *kappa);
 
+/* What the context keeps between calls for speed only: the extra lanes (a
+ * stream and pinned buffers each) of rtg_all_pairs_batched, 0 once the
+ * request loop has started and while a batched call runs, and the bytes of
+ * the indexes' tables.  Errors: RTG_EINVAL. */
+int rtg_debug_kept(rtg_ctx *ctx, int32_t *lanes, int64_t *index_table_bytes);
+
 const char *rtg_strerror(int status);
 
 #ifdef __cplusplus

@@ -2341,6 +2341,23 @@ void Ctx::drop_side_lanes() {
   side.clear();
 }
 
+void Ctx::side_begin() {
+  std::lock_guard<std::mutex> lk(side_mu);
+  side_busy = true;
+}
+
+void Ctx::side_end() {
+  std::lock_guard<std::mutex> lk(side_mu);
+  side_busy = false;
+  if (side_serving) drop_side_lanes();
+}
+
+void Ctx::side_yield(bool serving) {
+  std::lock_guard<std::mutex> lk(side_mu);
+  side_serving = serving;
+  if (serving && !side_busy) drop_side_lanes();
+}
+
 // Adds the counts and times of b to a (widths: the larger).
 static void add_stats(rtg_stats& a, const rtg_stats& b) {
   a.cells += b.cells;
@@ -2457,6 +2474,14 @@ int Ctx::batched(const rtg_query* q, int32_t nq, rtg_csr* outs,
   constexpr int kNotRun = 1 << 20;
   std::vector<int> brc(batches.size(), kNotRun);
   const int extra = (int)std::min<size_t>(batch_lanes - 1, batches.size() - 1);
+  // The extra lanes stay for the next call (making and freeing their streams
+  // and pinned buffers took 0.5 ms of a 2 ms batch of 32 instances), unless
+  // the request loop has started.  Every pass has drained them.
+  struct SideUse {
+    Ctx& c;
+    explicit SideUse(Ctx& ctx) : c(ctx) { c.side_begin(); }
+    ~SideUse() { c.side_end(); }
+  } side_use{*this};
   if (batches.size() >= 2 && extra > 0 && side_lanes(extra) == RTG_OK) {
     if ((rc = hip_fail(hipEventRecord(side_ready, main.stream), "hipEventRecord"))) return undo(rc);
     for (int l = 0; l < extra; ++l) {
@@ -2487,16 +2512,6 @@ int Ctx::batched(const rtg_query* q, int32_t nq, rtg_csr* outs,
       });
     work(main, st);
     for (auto& t : threads) t.join();
-    // The extra lanes stay for the next call (making and freeing their streams
-    // and pinned buffers took 0.5 ms of a 2 ms batch of 32 instances), unless
-    // the request loop runs: its lanes need the hardware queues, a few per
-    // process, that their streams would hold.  Every pass has drained them.
-    bool serving;
-    {
-      std::lock_guard<std::mutex> slk(server_mu);
-      serving = server != nullptr;
-    }
-    if (serving) drop_side_lanes();
     for (const auto& s2 : sst) add_stats(st, s2);
     for (int r : brc)
       if (r != RTG_OK && r != RTG_ENOMEM && r != kNotRun) return undo(r);
@@ -2858,8 +2873,7 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
 int Lane::index_extras(Index& I) {
   const int bits = std::min(I.P.layout.cell_bits,
                             std::max(1, ceil_log2((uint64_t)std::max<int64_t>(I.n, 2)) - 2));
-  const size_t tab_bytes = sizeof(uint32_t) * (size_t)I.k * (((size_t)1 << bits) + 1);
-  const size_t row_bytes = sizeof(float) * (size_t)I.k * I.n * I.d;
+  const size_t tab_bytes = I.tab_bytes(bits), row_bytes = I.row_bytes();
   const size_t spare = largest_free() / 16;
   if (!I.tab && tab_bytes <= spare) {
     I.tab = static_cast<uint32_t*>(dalloc(tab_bytes));
@@ -3312,6 +3326,19 @@ int rtg_get_stats(rtg_ctx* ctx, rtg_stats* out) {
   out->served_requests = c->served_requests;
   out->served_batches = c->served_batches;
   out->served_small = c->served_small;
+  return RTG_OK;
+}
+
+int rtg_debug_kept(rtg_ctx* ctx, int32_t* lanes, int64_t* index_table_bytes) {
+  if (!ctx || !lanes || !index_table_bytes) return RTG_EINVAL;
+  Ctx* c = reinterpret_cast<Ctx*>(ctx);
+  {
+    std::lock_guard<std::mutex> lk(c->side_mu);
+    *lanes = c->side_busy ? 0 : (int32_t)c->side.size();
+  }
+  std::lock_guard<std::mutex> alk(c->amu);
+  *index_table_bytes = 0;
+  for (const auto& ix : c->indexes) *index_table_bytes += (int64_t)ix.second->table_bytes();
   return RTG_OK;
 }
 

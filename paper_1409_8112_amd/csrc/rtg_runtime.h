@@ -144,6 +144,11 @@ struct Index {
   uint32_t* tab = nullptr;
   int tab_bits = 0;
   bool in_use = false;               // a query reads them (under the context's amu)
+  size_t row_bytes() const { return sizeof(float) * (size_t)k * (size_t)n * (size_t)d; }
+  size_t tab_bytes(int bits) const {
+    return sizeof(uint32_t) * (size_t)k * (((size_t)1 << bits) + 1);
+  }
+  size_t table_bytes() const { return (rows ? row_bytes() : 0) + (tab ? tab_bytes(tab_bits) : 0); }
 };
 
 // Launch settings of one pass (rtg_tuning in rtg.h): the context's
@@ -298,13 +303,20 @@ struct Ctx {
   // More lanes for rtg_all_pairs_batched: batches run batch_lanes at a time
   // (the caller's lane and batch_lanes - 1 more), so one pass's host work and
   // waits overlap the others' kernels (RTG_BATCH_LANES, 1 to 3).  Made by the
-  // first call that has several batches and kept for the next (under mu),
-  // until the request loop starts.
+  // first call that has several batches and kept for the next, until the
+  // request loop starts: its lanes need the hardware queues, a few per
+  // process, that theirs would hold.  While a call uses them they are its own
+  // (side_busy); it drops them at its end if the loop has started by then.
   int batch_lanes = 3;
   std::vector<std::unique_ptr<Lane>> side;
   hipEvent_t side_ready = nullptr;  // the caller's stream reached the call
+  std::mutex side_mu;               // the two flags, and side while not busy
+  bool side_busy = false, side_serving = false;
   int side_lanes(int count);
   void drop_side_lanes();
+  void side_begin();
+  void side_end();
+  void side_yield(bool serving);    // the request loop starts (or failed to)
   rtg_stats stats{};  // of the last blocking call
   std::mutex mu;      // one blocking call at a time
   std::mutex amu;     // arena, results, handles

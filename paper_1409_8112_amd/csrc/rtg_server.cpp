@@ -330,12 +330,12 @@ int Ctx::submit(const rtg_query& q, uint64_t* ticket) {
     std::lock_guard<std::mutex> lk(server_mu);
     if (!server) {
       // the batched call's extra lanes leave their hardware queues to the
-      // loop's (a batched call that runs now drops them at its end)
-      std::unique_lock<std::mutex> blk(mu, std::try_to_lock);
-      if (blk.owns_lock()) drop_side_lanes();
+      // loop's (at the end of a batched call that runs now)
+      side_yield(true);
       std::unique_ptr<Server> sv(new Server(*this));
       if ((rc = sv->start(server_lanes))) {
         sv->shutdown();
+        side_yield(false);
         return rc;
       }
       server = sv.release();

@@ -134,6 +134,7 @@ def lib() -> ctypes.CDLL:
                 "rtg_set_timing": [vp, u32],
                 "rtg_get_stats": [vp, ctypes.POINTER(rtg_stats)],
                 "rtg_debug_cell_coords": [vp, vp, i64, i32, f64, f64, vp, vp, vp],
+                "rtg_debug_kept": [vp, ctypes.POINTER(i32), ctypes.POINTER(i64)],
             }
             for name, args in sig.items():
                 fn = getattr(L, name)
@@ -544,6 +545,12 @@ class Context:
                "rtg_debug_cell_coords")
         return kap
 
+    def rtg_debug_kept(self) -> dict:
+        lanes, tables = ctypes.c_int32(), ctypes.c_int64()
+        _check(lib().rtg_debug_kept(self.h, ctypes.byref(lanes), ctypes.byref(tables)),
+               "rtg_debug_kept")
+        return {"lanes": lanes.value, "index_table_bytes": tables.value}
+
     # short aliases
     index_build = rtg_index_build
     index_query = rtg_index_query
@@ -565,3 +572,4 @@ class Context:
     set_timing = rtg_set_timing
     stats = rtg_get_stats
     debug_cell_coords = rtg_debug_cell_coords
+    debug_kept = rtg_debug_kept
