@@ -130,6 +130,20 @@ void* Arena::alloc(size_t bytes) {
   return base_ + off;
 }
 
+void* Arena::alloc_high(size_t bytes) {
+  bytes = (std::max<size_t>(bytes, 1) + kAlign - 1) & ~(size_t)(kAlign - 1);
+  if (by_size_.empty() || by_size_.rbegin()->first < bytes) return nullptr;
+  const auto s = std::prev(by_size_.end());
+  const size_t off = s->second, len = s->first;
+  by_size_.erase(s);
+  free_.erase(off);
+  if (len > bytes) add_free(off, len - bytes);
+  used_[off + len - bytes] = bytes;
+  in_use_ += bytes;
+  peak_ = std::max(peak_, in_use_);
+  return base_ + off + len - bytes;
+}
+
 void Arena::release(void* p) {
   if (!p) return;
   const size_t off = (size_t)(static_cast<char*>(p) - base_);
@@ -517,6 +531,16 @@ bool Ctx::drop_index_extras() {
   return any;
 }
 
+void* Ctx::dalloc_high(size_t bytes) {
+  std::lock_guard<std::mutex> lk(amu);
+  return arena->alloc_high(bytes);
+}
+
+bool Ctx::give_back_extras() {
+  std::lock_guard<std::mutex> lk(amu);
+  return drop_index_extras();
+}
+
 void* Ctx::dalloc_noalloc(size_t bytes) {
   std::lock_guard<std::mutex> lk(amu);
   return noalloc_arena ? noalloc_arena->alloc(bytes) : nullptr;
@@ -551,7 +575,10 @@ size_t Ctx::largest_free() {
 
 size_t Ctx::free_bytes() {
   std::lock_guard<std::mutex> lk(amu);
-  return arena->size() - arena->in_use();
+  size_t free = arena->size() - arena->in_use();
+  for (const auto& ix : indexes)  // (given back when an allocation needs them)
+    if (!ix.second->in_use) free += ix.second->table_bytes();
+  return free;
 }
 
 uint64_t Ctx::new_handle() {
@@ -1578,8 +1605,9 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
       bits += nq * (nq - 1) / 2;
     }
     const uint64_t words = (bits + 31) / 32;
-    const uint64_t limit = std::min<uint64_t>(kBitmapMaxBytes, largest_free() / 4);
-    if (4 * words <= limit) bitmap_words = std::max<uint64_t>(words, 1);
+    auto fits = [&] { return 4 * words <= std::min<uint64_t>(kBitmapMaxBytes, largest_free() / 4); };
+    if (fits() || (!noalloc && 4 * words <= kBitmapMaxBytes && ctx->give_back_extras() && fits()))
+      bitmap_words = std::max<uint64_t>(words, 1);
   }
   const bool bitmap = bitmap_words > 0;
   const bool first_owner = !(flags & RTG_DEDUP_SORT) && !bitmap && sig_g <= 64;
@@ -1630,8 +1658,13 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
       ns[q] = jobs[q]->n;
       ks[q] = jobs[q]->k;
     }
-    rc = plan_batch(d, m, ks.data(), ns.data(), Rh.data(), uh.data(), inv_cs.data(),
-                    alphas.data(), lo.data(), hi.data(), largest_free() / 2, first_owner, P);
+    auto plan = [&] {
+      return plan_batch(d, m, ks.data(), ns.data(), Rh.data(), uh.data(), inv_cs.data(),
+                        alphas.data(), lo.data(), hi.data(), largest_free() / 2, first_owner, P);
+    };
+    rc = plan();
+    // several passes: once more with the memory of the indexes' tables
+    if (!rc && P.tb < S_total && !noalloc && ctx->give_back_extras()) rc = plan();
     if (rc) return rc;
   }
   st.key_bits = std::max(st.key_bits, P.key_bits);
@@ -2770,9 +2803,13 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
     hi[j] = decode_order(hb[2 * j + 1]);
   }
   const int64_t kk = k, nn = n;
-  if ((rc = plan_batch(d, 1, &kk, &nn, R, u, &one.inv_c, &alpha, lo.data(), hi.data(),
-                       ctx->largest_free() / 2, false, I.P)))
-    return rc;
+  auto plan = [&] {
+    return plan_batch(d, 1, &kk, &nn, R, u, &one.inv_c, &alpha, lo.data(), hi.data(),
+                      ctx->largest_free() / 2, false, I.P);
+  };
+  rc = plan();
+  if (!rc && I.P.tb < k && ctx->give_back_extras()) rc = plan();
+  if (rc) return rc;
   if ((rc = upload(I.layout, &I.P.layout, sizeof(KeyLayout)))) return rc;
   if ((rc = upload(I.klo, I.P.klo.data(), sizeof(int64_t) * I.P.klo.size()))) return rc;
 
@@ -2875,15 +2912,23 @@ int Lane::index_extras(Index& I) {
                             std::max(1, ceil_log2((uint64_t)std::max<int64_t>(I.n, 2)) - 2));
   const size_t tab_bytes = I.tab_bytes(bits), row_bytes = I.row_bytes();
   const size_t spare = largest_free() / 16;
+  // (the fields are read under amu by what counts or gives back the tables)
   if (!I.tab && tab_bytes <= spare) {
-    I.tab = static_cast<uint32_t*>(dalloc(tab_bytes));
-    I.tab_bits = bits;
-    if (I.tab)
-      launch_query_table(I.grids, I.k, I.n, I.P.layout.cell_bits, bits, I.tab, stream);
+    uint32_t* tab = static_cast<uint32_t*>(ctx->dalloc_high(tab_bytes));
+    if (tab) {
+      std::lock_guard<std::mutex> alk(ctx->amu);
+      I.tab = tab;
+      I.tab_bits = bits;
+    }
+    if (tab) launch_query_table(I.grids, I.k, I.n, I.P.layout.cell_bits, bits, tab, stream);
   }
   if (!I.rows && query_rows_fit(I.d) && row_bytes + tab_bytes <= spare) {
-    I.rows = static_cast<float*>(dalloc(row_bytes));
-    if (I.rows) launch_query_rows(I.grids, I.k, I.n, I.d, I.pts, I.rows, stream);
+    float* rows = static_cast<float*>(ctx->dalloc_high(row_bytes));
+    if (rows) {
+      std::lock_guard<std::mutex> alk(ctx->amu);
+      I.rows = rows;
+    }
+    if (rows) launch_query_rows(I.grids, I.k, I.n, I.d, I.pts, rows, stream);
   }
   return hip_fail(hipGetLastError(), "index tables");
 }

@@ -27,6 +27,7 @@ class Arena {
   static constexpr size_t kAlign = 256;
   Arena(char* base, size_t bytes);
   void* alloc(size_t bytes);  // nullptr when no free block is large enough
+  void* alloc_high(size_t bytes);  // from the end of the largest free block
   void release(void* p);
   void shrink(void* p, size_t bytes);  // gives back the tail of a block past bytes
   size_t largest_free() const;
@@ -329,6 +330,10 @@ struct Ctx {
   int hip_fail(hipError_t e, const char* what);
   void* dalloc(size_t bytes);
   bool drop_index_extras();             // (under amu) true if any memory came back
+  bool give_back_extras();              // the same, takes amu
+  // For what may be given back at any time: at the far end of the free
+  // memory, so that what it leaves joins the rest again.
+  void* dalloc_high(size_t bytes);
   void* dalloc_noalloc(size_t bytes);   // from the no-allocation arena
   size_t largest_free_noalloc();
   void dfree(void* p);                  // to whichever arena holds p

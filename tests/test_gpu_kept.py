@@ -77,3 +77,35 @@ def test_index_tables_yield_to_requests():
             _equal(x, want)
         _equal(ctx.index_query(index, dq), ref)
         assert ctx.debug_kept()["index_table_bytes"] > 0
+
+
+def test_index_tables_count_as_free():
+    """The tables of several indexes do not split a call into more passes."""
+    from paper_1409_8112_amd import rtg
+    pts, qs = _dev(workloads.uniform_points(20000, 3, seed=7)), _dev(workloads.uniform_points(2500, 3, seed=8))
+    other = workloads.uniform_points(100_000, 3, seed=9)
+    dev = _dev(other)
+
+    def passes(mib, tables):
+        with rtg.Context(0, arena_bytes=mib << 20) as ctx:
+            kept = [ctx.index_build(pts, 0.03, 8, 2.0, q) for q in range(8)]
+            if tables:
+                for ix in kept:
+                    ctx.index_query(ix, qs).release()
+                assert ctx.debug_kept()["index_table_bytes"] > 8 << 20
+            res = ctx.all_pairs(dev, 0.02, 8, 2.0, 1)
+            grids = ctx.stats()["transforms_per_sort"]
+            rp, col = res.to_numpy()
+            assert not tables or ctx.debug_kept()["index_table_bytes"] == 0
+            return grids, rp, col
+
+    ref = oracle.rtg(other, 0.02, 8, 2.0, 1)
+    for mib in range(60, 120, 2):  # the least budget of one pass, without tables
+        try:
+            if passes(mib, False)[0] == 8:
+                break
+        except rtg.RTGError as e:
+            assert e.code == rtg.ENOMEM
+    grids, rp, col = passes(mib, True)
+    assert grids == 8
+    assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
