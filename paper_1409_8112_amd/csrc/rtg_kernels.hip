@@ -3391,8 +3391,8 @@ inline unsigned tiles_for(size_t count) { return (unsigned)((count + kTile - 1) 
 // pairs of the cells in FP64 in the definition's order, keeps a pair within r
 // only if no earlier grid's words of the two points are equal, and appends it
 // to one pair list.  A second launch turns the list into the CSR lists.
-// Anything outside these limits -- cells too far apart for a word, wider
-// keys, more pairs than the list holds (kTinyPairCap), a row longer than
+// Anything outside these limits -- cells that need more bits than a word,
+// wider keys, more pairs than the list holds (kTinyPairCap), a row longer than
 // kTinyMaxDeg -- is flagged and the caller runs the general pipeline instead.
 
 constexpr int kTinyThreads = 512;
@@ -3459,6 +3459,7 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
   __shared__ uint32_t wlo[kTinyWaves][D], whi[kTinyWaves][D];
   __shared__ uint32_t wsum[kTinyWaves];
   __shared__ uint32_t sflag;
+  __shared__ int s_bits;
   // k parts workgroups: workgroup (t, part) tests slice part of grid t's
   // pairs (every part finds the grid's cells itself)
   const int t = (int)(blockIdx.x / A.parts);
@@ -3493,11 +3494,11 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
   constexpr int kF = 32 / D;
   constexpr uint32_t kHalf = kF < 32 ? 1u << (kF - 1) : 0x80000000u;
   constexpr uint32_t kFMask = kF < 32 ? (1u << kF) - 1u : 0xFFFFFFFFu;
+  int groups = 1;  // grids at work at a time
+  while (groups < kTinyWaves && groups < t + 1) groups <<= 1;
+  const int per = kTinyWaves / groups;
+  const int i0 = (w % per) * 64 + (int)lane;
   {
-    int groups = 1;  // grids at work at a time
-    while (groups < kTinyWaves && groups < t + 1) groups <<= 1;
-    const int per = kTinyWaves / groups;
-    const int i0 = (w % per) * 64 + (int)lane;
     bad = 0u;
     for (int g = w / per; g <= t; g += groups) {
       const double* Rg = sT + (size_t)g * D * D;
@@ -3534,9 +3535,88 @@ __global__ __launch_bounds__(kTinyThreads) void k_tiny_grids(const TinyArgs A) {
     if (bad) atomicOr(&sflag, bad);
   }
   __syncthreads();
-  // grid t's fields less their minimum, in as few bits as they take
   int cell_bits = 0;
-  {
+  if (sflag == 4u) {
+    // Points too far from point 0 on some axis: each grid's fields less their
+    // minimum, in as few bits as they take, which hold long thin sets as well
+    // (2000 points on a path of 1000 cells, d = 3, k = 4: 88 us a call, 166
+    // when the general pipeline ran after the two launches).  Only these
+    // instances pay for it: with ranges for all, 2000 points in a cube took 85
+    // us instead of 62.
+    if (threadIdx.x == 0) s_bits = 0;
+    for (int g0 = 0; g0 <= t; g0 += groups) {
+      const int g = g0 + w / per;
+      const double* Rg = sT + (size_t)g * D * D;
+      const double* ug = sT + nR + (size_t)g * D;
+      const int i1 = g <= t ? n : 0;  // (waves without a grid meet the barriers)
+      auto fields = [&](int i, uint32_t (&f)[D]) {
+        float p[D];
+#pragma unroll
+        for (int l = 0; l < D; ++l) p[l] = sp[i * D + l];
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          const double y = cell_y<D>(Rg + (size_t)j * D, p, nullptr, 0, 0, D, A.inv_c, ug[j]);
+          f[j] = (uint32_t)(int32_t)floor(y) ^ 0x80000000u;  // (in the order of the cells)
+        }
+      };
+      uint32_t lo[D], hi[D], f[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        lo[j] = 0xFFFFFFFFu;
+        hi[j] = 0u;
+      }
+      for (int i = i0; i < i1; i += per * 64) {
+        fields(i, f);
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          lo[j] = min(lo[j], f[j]);
+          hi[j] = max(hi[j], f[j]);
+        }
+      }
+      __syncthreads();  // (every thread has read sflag, and the ranges before)
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        wave_minmax_u32(lo[j], hi[j]);
+        if (lane == 0) {
+          wlo[w][j] = lo[j];
+          whi[w][j] = hi[j];
+        }
+      }
+      if (g0 == 0 && threadIdx.x == 0) sflag = 0u;
+      __syncthreads();
+      int shift[D], bits = 0;
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        lo[j] = wlo[w / per * per][j];
+        hi[j] = whi[w / per * per][j];
+        for (int q = 1; q < per; ++q) {
+          lo[j] = min(lo[j], wlo[w / per * per + q][j]);
+          hi[j] = max(hi[j], whi[w / per * per + q][j]);
+        }
+        shift[j] = bits;
+        bits += hi[j] > lo[j] ? 32 - __clz((int)(hi[j] - lo[j])) : 0;
+      }
+      // grid t's key holds the point index too
+      const bool fits = g == t ? bits + idx_bits <= 31 : bits <= 32;
+      if (g <= t && !fits && lane == 0) atomicOr(&sflag, 4u);
+      if (g == t && lane == 0) s_bits = bits;
+      for (int i = i0; i < (fits ? i1 : 0); i += per * 64) {
+        fields(i, f);
+        uint32_t cell = 0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) cell |= (f[j] - lo[j]) << (shift[j] & 31);
+        sC[(size_t)g * n + i] = cell;
+      }
+    }
+    __syncthreads();
+    const uint32_t flag = sflag;
+    if (flag) {
+      if (threadIdx.x == 0) atomicOr(A.err, flag);
+      return;  // uniform: every thread read the same flag
+    }
+    cell_bits = s_bits;
+  } else {
+    // grid t's fields less their minimum, in as few bits as they take
     uint32_t lo[D], hi[D];
 #pragma unroll
     for (int j = 0; j < D; ++j) {

@@ -191,3 +191,33 @@ def test_segments_sorted_one_to_a_block(ctx, n, d):
         rp, col = x.to_numpy()
         assert np.array_equal(rp, ref.row_ptr) and np.array_equal(col, ref.col)
     ctx.release_many(res)
+
+
+@pytest.mark.parametrize("n,d,cells,k", [(2000, 3, 1000, 4), (200, 3, 700, 20), (400, 8, 40, 1),
+                                         (400, 8, 40, 5), (1000, 8, 12, 8), (1500, 6, 40, 6),
+                                         (2000, 2, 60000, 3), (64, 3, 500_000, 2)])
+@pytest.mark.parametrize("first", ["end", "middle", "stray"])
+def test_small_thin_sets(small_ctx, n, d, cells, k, first):
+    """Points along one axis, many more cells long than wide, however point 0
+    lies: the two launches take them, whatever a field beside point 0 holds."""
+    from paper_1409_8112_amd import rtg
+    r, alpha = 0.05, 2.0
+    rng = np.random.default_rng(n + d)
+    pts = rng.random((n, d)) * 0.2
+    pts[:, 0] = np.linspace(0.0, cells * alpha * r, n)
+    if first == "middle":
+        pts[[0, n // 2]] = pts[[n // 2, 0]]
+    if first == "stray":
+        pts = pts[rng.permutation(n)]
+        pts[:, 0] = rng.random(n) * 3.0
+        pts[0, 0] = cells * alpha * r
+    _check(small_ctx, pts.astype(np.float32), r, k, alpha, 5, rtg.NO_ROTATE)
+    assert small_ctx.stats()["kernel_launches"][rtg.KERNELS.index("keys")] == 0
+
+
+def test_small_cells_beyond_a_word(small_ctx):
+    """Cells that take more than 32 bits go through the general pipeline."""
+    from paper_1409_8112_amd import rtg
+    pts = (workloads.uniform_points(500, 3, seed=1) * 800.0).astype(np.float32)
+    _check(small_ctx, pts, 0.05, 4, 2.0, 5)
+    assert small_ctx.stats()["kernel_launches"][rtg.KERNELS.index("keys")] == 1
