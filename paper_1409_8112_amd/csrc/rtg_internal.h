@@ -511,7 +511,7 @@ void launch_bucket_scatter(const PairSource& src, size_t count, int pb, int rb, 
 // Writes col and row_ptr (row_ptr[n] = nnz) for every bucket of at most
 // cap (<= kBucketMaxEntries) entries: entries of unique pairs, so a bucket's
 // start in the entry array is its start in col.  Larger buckets, and
-// buckets with a row of more than 1024 entries whose columns crowd together,
+// buckets with a row of more than 1024 entries close together in the columns,
 // are listed in oversized[] (count in *n_oversized, cleared beforehand) for
 // the caller.
 void launch_bucket_csr(const uint32_t* entries, const uint32_t* offs, uint32_t nbuckets,

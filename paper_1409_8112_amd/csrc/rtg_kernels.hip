@@ -2947,14 +2947,17 @@ __device__ __forceinline__ void bucket_range(const uint32_t* __restrict__ offs, 
 // for 107e6 in clustered d12, bins 111-120 and 550; for rows of about 20 both
 // ways measure 104 us per 19e6, bound by the LDS, and with few entries per
 // bucket the extra steps cost 36 against 25 us).  A quarter bin per entry,
-// 16 bits each, keeps two blocks on a CU.  Where a bin holds more than
-// kMaxBin entries (long rows whose columns lie together), the short rows are
-// ranked by counting and the longer ones sorted in place by one wave.
-// Buckets larger than cap, and those with such bins and a row longer than
-// kLongRow, are listed in oversized for the caller.
-constexpr uint32_t kLongRow = 1024;
+// 16 bits each, keeps two blocks on a CU.  A bin of more than
+// kMaxBin entries (long rows whose columns lie together) is sorted in place by
+// one wave: 150000 points, rows of 500 whose columns lie in 2 / 4 / 8 places
+// of the index order, took a call 2334 / 2257 / 1959 us, with bins ranked up to
+// 128 entries and whole rows sorted beyond that 2381 / 2688 / 2150, with every
+// long row sorted 2294 / 2307 / 2314 (the worst found: rows of 1000 in two
+// places, 4746 against 4376).  Buckets larger than cap, and those with a bin
+// of more than kLongBin, are listed in oversized for the caller.
+constexpr uint32_t kLongBin = 1024;  // (what a wave sorts)
 constexpr uint32_t kShortRow = 64;
-constexpr uint32_t kMaxBin = 128;
+constexpr uint32_t kMaxBin = 96;
 
 // Ascending sort of v[0..len) in LDS by one wave (len <= 1024): a bitonic
 // network in its flip form, where every compare-exchange puts the smaller
@@ -3032,7 +3035,8 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
   __shared__ uint32_t rstart[kBucketMaxRows + 1];
   __shared__ uint32_t bins[(kCsrBins + 1) / 2];  // two 16-bit counters a word
   __shared__ uint32_t wsum[kCsrWaves];
-  __shared__ uint32_t s_min, s_max, s_bin, s_long;
+  __shared__ uint32_t s_min, s_max, s_long, s_over, s_ncrowded;
+  __shared__ uint16_t s_crowded[kBucketMaxEntries / kMaxBin];
   const uint32_t b = blockIdx.x;
   const uint32_t lane = lane_id();
   if (b == 0 && threadIdx.x == 0) row_ptr[n] = nnz;
@@ -3054,8 +3058,9 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
   if (threadIdx.x == 0) {
     s_min = 0xFFFFFFFFu;
     s_max = 0u;
-    s_bin = 0u;
     s_long = 0u;
+    s_over = 0u;
+    s_ncrowded = 0u;
   }
   __syncthreads();
 #pragma unroll
@@ -3065,7 +3070,7 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
   // row starts (at most one row per thread)
   static_assert(kBucketMaxRows <= kCsrThreads, "one row per thread");
   const uint32_t mine = threadIdx.x < nrows ? rstart[threadIdx.x] : 0u;
-  if (mine > kShortRow) atomicOr(&s_long, mine > kLongRow ? 3u : 1u);
+  if (mine > kShortRow) s_long = 1u;
   uint32_t all;
   const uint32_t run = csr_block_exclusive_scan(mine, wsum, all);
   if (threadIdx.x < nrows) {
@@ -3076,13 +3081,17 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
   }
   if (threadIdx.x == 0) rstart[nrows] = cnt;
   __syncthreads();
-  const uint32_t long_rows = s_long;
-  // Each short row's entries, at positions t, t + 1024, ... of the row-ordered
-  // array for thread t: the lanes of a wave cover a few whole rows and read
-  // the same row element at each step (broadcast reads, no bank conflicts).
-  // An entry's place is the number of smaller columns in its row (the row
-  // bits are equal, so whole entries compare as columns).
-  auto rank_short_rows = [&]() {
+  if (!s_long) {
+#pragma unroll
+    for (int q = 0; q < kCsrItems; ++q)
+      if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt)
+        s[atomicAdd(&bins[e_[q] >> pb], 1u)] = e_[q];
+    __syncthreads();
+    // A row's entries, at positions t, t + 1024, ... of the row-ordered array
+    // for thread t: the lanes of a wave cover a few whole rows and read the
+    // same row element at each step (broadcast reads, no bank conflicts).  An
+    // entry's place is the number of smaller columns in its row (the row bits
+    // are equal, so whole entries compare as columns).
 #pragma unroll
     for (int q = 0; q < kCsrItems; ++q) {
       const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
@@ -3090,24 +3099,14 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
         const uint32_t e = s[x];
         const uint32_t r = e >> pb;
         const uint32_t lo = rstart[r], hi = rstart[r + 1];
-        if (hi - lo <= kShortRow) {
-          uint32_t rank = lo, y = lo;
-          for (; y + 4 <= hi; y += 4)
-            rank += (s[y] < e ? 1u : 0u) + (s[y + 1] < e ? 1u : 0u) + (s[y + 2] < e ? 1u : 0u) +
-                    (s[y + 3] < e ? 1u : 0u);
-          for (; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
-          col[(size_t)start + rank] = (int32_t)(e & cmask);
-        }
+        uint32_t rank = lo, y = lo;
+        for (; y + 4 <= hi; y += 4)
+          rank += (s[y] < e ? 1u : 0u) + (s[y + 1] < e ? 1u : 0u) + (s[y + 2] < e ? 1u : 0u) +
+                  (s[y + 3] < e ? 1u : 0u);
+        for (; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
+        col[(size_t)start + rank] = (int32_t)(e & cmask);
       }
     }
-  };
-  if (!long_rows) {
-#pragma unroll
-    for (int q = 0; q < kCsrItems; ++q)
-      if (threadIdx.x + (uint32_t)q * kCsrThreads < cnt)
-        s[atomicAdd(&bins[e_[q] >> pb], 1u)] = e_[q];
-    __syncthreads();
-    rank_short_rows();
     return;
   }
   // Long rows: bins.
@@ -3143,18 +3142,19 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
   __syncthreads();
   {
     // bin starts: each thread scans a contiguous run of bins
-    uint32_t v[kCsrBinsPer / 2], sum = 0, most = 0;
+    uint32_t v[kCsrBinsPer / 2], sum = 0;
 #pragma unroll
     for (int x = 0; x < kCsrBinsPer / 2; ++x) {
       const uint32_t at = threadIdx.x * (kCsrBinsPer / 2) + (uint32_t)x;
       v[x] = 2 * at < nbins ? bins[at] : 0u;
       const uint32_t a0 = v[x] & 0xFFFFu, a1 = v[x] >> 16;
       sum += a0 + a1;
-      most = max(most, max(a0, a1));
+      if (max(a0, a1) > kMaxBin) {
+        if (a0 > kMaxBin) s_crowded[atomicAdd(&s_ncrowded, 1u)] = (uint16_t)(2 * at);
+        if (a1 > kMaxBin) s_crowded[atomicAdd(&s_ncrowded, 1u)] = (uint16_t)(2 * at + 1);
+        if (max(a0, a1) > kLongBin) s_over = 1u;
+      }
     }
-    uint32_t none = 0;
-    wave_minmax_u32(none, most);
-    if (lane == 0 && most > kMaxBin) s_bin = 1u;
     uint32_t at0 = csr_block_exclusive_scan(sum, wsum, all);
 #pragma unroll
     for (int x = 0; x < kCsrBinsPer / 2; ++x) {
@@ -3165,7 +3165,7 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
     }
   }
   __syncthreads();
-  if (s_bin && (long_rows & 2u)) {
+  if (s_over) {
     if (threadIdx.x == 0) oversized[atomicAdd(n_oversized, 1u)] = b;
     return;
   }
@@ -3177,31 +3177,34 @@ __global__ __launch_bounds__(kCsrThreads, 8) void k_bucket_csr(
       s[(old >> (16 * (x & 1u))) & 0xFFFFu] = e_[q];
     }
   __syncthreads();
-  if (!s_bin) {
-    // A bin's cursor now stands at its end, and so at the next bin's start.
+  // A bin's cursor now stands at its end, and so at the next bin's start.
+  auto bin_extent = [&](uint32_t z, uint32_t& lo, uint32_t& hi) {
+    hi = (bins[z >> 1] >> (16 * (z & 1u))) & 0xFFFFu;
+    lo = z ? (bins[(z - 1) >> 1] >> (16 * ((z - 1) & 1u))) & 0xFFFFu : 0u;
+  };
 #pragma unroll
-    for (int q = 0; q < kCsrItems; ++q) {
-      const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
-      if (x < cnt) {
-        const uint32_t e = s[x];
-        const uint32_t z = bin_of(e);
-        const uint32_t hi = (bins[z >> 1] >> (16 * (z & 1u))) & 0xFFFFu;
-        const uint32_t lo = z ? (bins[(z - 1) >> 1] >> (16 * ((z - 1) & 1u))) & 0xFFFFu : 0u;
+  for (int q = 0; q < kCsrItems; ++q) {
+    const uint32_t x = threadIdx.x + (uint32_t)q * kCsrThreads;
+    if (x < cnt) {
+      const uint32_t e = s[x];
+      uint32_t lo, hi;
+      bin_extent(bin_of(e), lo, hi);
+      if (hi - lo <= kMaxBin) {
         uint32_t rank = lo;
         for (uint32_t y = lo; y < hi; ++y) rank += s[y] < e ? 1u : 0u;
         col[(size_t)start + rank] = (int32_t)(e & cmask);
       }
     }
-    return;
   }
-  rank_short_rows();
-  __syncthreads();  // (the sorts below rewrite only long rows)
-  for (uint32_t r = threadIdx.x >> 6; r < nrows; r += kCsrWaves) {
-    const uint32_t lo = rstart[r], len = rstart[r + 1] - lo;
-    if (len <= kShortRow) continue;
-    wave_sort_lds(s + lo, len, lane);
-    for (uint32_t x = lane; x < len; x += 64)
-      col[(size_t)start + lo + x] = (int32_t)(s[lo + x] & cmask);
+  const uint32_t ncrowded = s_ncrowded;
+  if (!ncrowded) return;
+  __syncthreads();  // (the sorts move entries that were read above)
+  for (uint32_t q = threadIdx.x >> 6; q < ncrowded; q += kCsrWaves) {
+    uint32_t lo, hi;
+    bin_extent(s_crowded[q], lo, hi);
+    wave_sort_lds(s + lo, hi - lo, lane);
+    for (uint32_t x = lo + lane; x < hi; x += 64)
+      col[(size_t)start + x] = (int32_t)(s[x] & cmask);
   }
 }
 

@@ -221,3 +221,17 @@ def test_small_cells_beyond_a_word(small_ctx):
     pts = (workloads.uniform_points(500, 3, seed=1) * 800.0).astype(np.float32)
     _check(small_ctx, pts, 0.05, 4, 2.0, 5)
     assert small_ctx.stats()["kernel_launches"][rtg.KERNELS.index("keys")] == 1
+
+
+@pytest.mark.parametrize("size", [95, 97, 200, 500, 1000, 1100, 2300])
+@pytest.mark.parametrize("places", [1, 2, 5])
+def test_rows_crowded_in_a_few_places(ctx, size, places):
+    """Clusters whose indices lie in a few runs: a row's columns fill few of
+    its bins, with fewer and more entries than a wave sorts."""
+    rng = np.random.default_rng(size + places)
+    n, d = 9000, 6
+    pts = np.concatenate([np.repeat(rng.random((n // size + 1, d)), size, axis=0)[:n],
+                          rng.random((9000, d)) + 5.0])
+    pts[:n] += 0.002 * rng.standard_normal((n, d))
+    pts = np.concatenate([pts[i::places] for i in range(places)]).astype(np.float32)
+    _check(ctx, pts, 0.02, 3, 2.5, size)
