@@ -4428,9 +4428,12 @@ static void query_dispatch(const QueryArgs& a, unsigned blocks, bool long_cells,
 // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; above d = 6, where cells are
 // longer and uneven, 16 (1e5 queries of 1e5 points, d = 9: 1252 us with 4,
 // 1133 with 16; 70000 of 1e5, d = 12: 1893 and 1743); few queries get as many
-// as give the chip 2^18 lanes.
+// as give the chip 2^18 lanes.  At d = 5 and 6 (cells of about a hundred
+// points) queries that are not in order get 32: each cell then comes from HBM
+// in a few wide steps (50000 queries of 1e6 points, d = 6: 1212 us with 8,
+// 1021 with 32; 33000: 720 and 718).
 uint32_t query_lanes(int d, int64_t m) {
-  uint32_t lanes = d > 6 ? 16 : 4;
+  uint32_t lanes = d > 6 ? 16 : d > 4 && m < 65536 ? 32 : 4;
   while (lanes < 64 && (uint64_t)m * lanes < (1u << 18)) lanes *= 2;
   return lanes;
 }
