@@ -316,18 +316,22 @@ size_t Ctx::pass_bytes_bound(int64_t n, int32_t d, int32_t k, double alpha, uint
 
 // Hashed keys: from six radix passes on (clustered d12: 64 bits, eight passes
 // with values beside the keys), three passes of plain keys instead, or four
-// where the largest instance has more than kHashFew points.  A hash of h bits
-// adds about n^2 / 2^(h + 1) tests per grid, and for points that mostly have a
-// cell to themselves as many units: 4e6 such points, d = 9, k = 8, took 4.89 ms
-// with 24 bits and 1.66 with 32 (3.51 with their exact keys), 1e6 0.72 and
-// 0.52 (0.86); where cells are full the fourth pass shows (clustered d12, 4e6
-// points: 1% of the call; 7e5: 1.71 and 1.80 ms).  The check of the accepted
+// where the largest instance has more than 2^20 points.  A hash of h bits adds
+// about n^2 / 2^(h + 1) tests per grid, and for points that mostly have a cell
+// to themselves as many units, so instances of up to 2^(h - 4) points take h
+// bits (under 3% of their points then collide in a grid): 4e6 such points, d =
+// 9, k = 8, took 4.89 ms with 24 bits, 2.60 with 26, 1.86 with 28 and 1.66 with
+// 32 (3.51 with their exact keys), 1e6 0.72 with 24 (0.86).  Where cells are
+// full the fourth pass shows: clustered d12, 4e6 points, 11.14 / 11.31 / 11.30 /
+// 11.50 ms (12.25 with exact keys).  The check of the accepted
 // pairs' cells costs the pair kernel 5%.  At five passes hashed and exact keys
 // are even (uniform d12 requests).  Below 2^20 keys a pass is its launches'
 // time and the exact keys stay, with their band per cell.
 constexpr int kHashAbove = 40;
-constexpr int64_t kHashKeys = int64_t(1) << 20, kHashFew = int64_t(1) << 20;
-constexpr int hash_bits(int64_t nmax) { return nmax <= kHashFew ? 24 : 32; }
+constexpr int64_t kHashKeys = int64_t(1) << 20;
+constexpr int hash_bits(int64_t nmax) {
+  return nmax <= (int64_t(1) << 20) ? 24 : nmax <= (int64_t(1) << 24) ? 28 : 32;
+}
 
 int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const double* R,
                const double* u, const double* inv_c, const double* alpha, const float* lo,
@@ -1619,8 +1623,9 @@ int Lane::run_batch(std::vector<Job*>& jobs, rtg_stats& st, PassPlan* pp) {
   // point gets a 32-byte record (coordinates, padding, then the signature
   // word in the last 8 bytes): a tile load reads one aligned run per lane
   // instead of a row and a word apart (uniform d6 pair kernel about 1.5%
-  // faster; wider records at d = 12 cost more than they saved).  The stage
-  // kernel writes them while it reads the points.
+  // faster; wider records at d = 12 cost more than they saved, measured when
+  // a tile load tested every coordinate on its own).  The stage kernel writes
+  // them while it reads the points.
   const int rs = (d + 2 + 3) & ~3;
   float* rec = nullptr;
   int sig_stride = sig_W;
@@ -2905,7 +2910,8 @@ int Lane::build_index(const float* points, int64_t n, int32_t d, double r, int32
 // enough (m >= n / 8): about four keys per start-table entry, and the points'
 // coordinates in grid order, so that a query reads its cells' members in runs.
 // They cost 0.16 ms at n = 1e6, d = 3, k = 8 and save 1 us per thousand
-// queries there.  Neither is needed, so they take at most a sixteenth of what
+// queries there; a call with fewer queries does not pay them back, and calls
+// are not added up.  Neither is needed, so they take at most a sixteenth of what
 // is free.
 int Lane::index_extras(Index& I) {
   const int bits = std::min(I.P.layout.cell_bits,

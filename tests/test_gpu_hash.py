@@ -16,8 +16,8 @@ def _dev(p):
 
 @pytest.mark.parametrize("n,passes", [(1 << 20, 3), ((1 << 20) + 1, 4)])
 def test_hash_is_wider_for_more_points(n, passes):
-    """More points than 2^20 take 32 bits (24 would put unrelated points of
-    sparse sets into one run); the lists are those of the exact keys, which
+    """More points than 2^20 take more than 24 bits (which would put unrelated
+    points of sparse sets into one run); the lists are those of the exact keys, which
     the sort-unique rule keeps."""
     from paper_1409_8112_amd import rtg
     pts = _dev(workloads.clustered_points(n, 12, seed=2, n_clusters=8000, sigma=0.01))
