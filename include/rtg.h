@@ -23,8 +23,11 @@
  * so no decision differs from the FP64 one.  Under the MR-metric
  * (RTG_ROBOTS) the test is sum_b sqrt(s_b) <= r, s_b each robot's squared
  * displacement summed as above, square roots correctly rounded, sum in robot
- * order; the FP32 screen then only rejects pairs beyond r in the Euclidean
- * sense, and every other pair is decided in FP64.
+ * order.  The Euclidean screen, with a radius a little above r, then only
+ * rejects.  A pair it keeps is decided by the FP32 sum of the robots'
+ * displacements where that lies outside a relative 2^-15 of r (d <= 16 and
+ * r >= 2^-30; its error there is below 2^-16), and in the FP64 order above
+ * otherwise; index queries decide every such pair in FP64.
  *
  * Output.  A CSR neighbour list in device memory: row_ptr[n+1] (int64) and
  * col[nnz] (int32); row i lists its neighbours in ascending order.  By default
@@ -136,9 +139,13 @@ typedef struct rtg_stats {
   int64_t n, d, k;
   int64_t point_transforms;  /* n * k                                          */
   int64_t cells;             /* cells holding >= 2 points, summed over grids   */
-  int64_t tests;             /* same-cell pairs tested, summed over grids      */
+                             /* (runs of equal keys: where keys are hashes of  */
+                             /* the cells, a run may hold several cells)       */
+  int64_t tests;             /* pairs of one such run tested, summed over grids */
   int64_t candidates;        /* pairs within r before de-duplication           */
-  int64_t band_rechecks;     /* pairs re-tested in FP64                        */
+  int64_t band_rechecks;     /* pairs re-tested in FP64 by the screen; under   */
+                             /* the MR-metric also every pair it decided, in   */
+                             /* FP32 or FP64                                   */
   int64_t unique_pairs;      /* unordered pairs reported                       */
   int32_t key_bits;          /* bits of the sorted cell key                    */
   int32_t key_passes;        /* radix passes over the cell keys                */
@@ -190,13 +197,13 @@ int rtg_destroy(rtg_ctx *ctx);
  * d <= 8, n d <= 12288, k n <= 12288, k d (d + 1) <= 2048) run in two
  * launches -- up to eight workgroups per grid find its cells, test their
  * share of its pairs and keep the first grid's, then the lists are built --
- * and take the general pipeline when their keys, pairs (131072) or rows
- * (128) exceed what those launches hold; the lists are the same either
- * way, and the stats count
- * both launches under RTG_K_PAIRS with candidates = unique_pairs.  The
- * environment setting RTG_SMALL=0 turns the small path off.  Errors:
- * RTG_EINVAL (also for NaN/Inf coordinates), RTG_ERANGE, RTG_ENOMEM,
- * RTG_EDEVICE. */
+ * and take the general pipeline when their keys (31 bits of cell and point
+ * index; each grid's cells, packed by their ranges on the axes, in 32 bits),
+ * pairs (131072) or rows (128) exceed what those launches hold; the lists are
+ * the same either way, and the stats count both launches under RTG_K_PAIRS
+ * with candidates = unique_pairs.  The environment setting RTG_SMALL=0 turns
+ * the small path off.  Errors: RTG_EINVAL (also for NaN/Inf coordinates),
+ * RTG_ERANGE, RTG_ENOMEM, RTG_EDEVICE. */
 int rtg_all_pairs(rtg_ctx *ctx, const float *points, int64_t n, int32_t d, double r, int32_t k,
                   double alpha, uint64_t seed, uint32_t flags, rtg_csr *out);
 
@@ -305,14 +312,16 @@ int rtg_release_many(rtg_ctx *ctx, const uint64_t *handles, int32_t count);
  * flags: RTG_NO_ROTATE, RTG_ROBOTS(b) (the queries' distance test is then
  * the MR-metric's; list flags are ignored).  The first call with m >= n / 8
  * queries also makes tables for the index (at most a sixteenth of the free
- * budget, given back when an allocation would fail otherwise).
+ * budget; they count as free and are given back to whoever needs them).
  *
  * rtg_index_query answers m query points (device, row-major [m][d] FP32,
  * the index's d): row s of the result lists, ascending and once each, the
  * indexed points p_i with ||p_i - q_s|| <= r that share a cell with q_s
  * under some grid of the index, decided exactly as the pairs of
- * rtg_all_pairs (FP64 cell coordinates and distances).  A query equal to an
- * indexed point reports that point.  Errors: RTG_EINVAL (also NaN/Inf
+ * rtg_all_pairs (cells from FP64 coordinates, distances by the FP32 screen
+ * with its FP64 band).  A query equal to an indexed point reports that point.
+ * A call that runs out of memory runs again in the least there is for it,
+ * more slowly, before it returns RTG_ENOMEM.  Errors: RTG_EINVAL (also NaN/Inf
  * coordinates), RTG_ERANGE, RTG_ENOMEM, RTG_ENOENT (unknown index). */
 int rtg_index_build(rtg_ctx *ctx, const float *points, int64_t n, int32_t d, double r, int32_t k,
                     double alpha, uint64_t seed, uint32_t flags, uint64_t *index);

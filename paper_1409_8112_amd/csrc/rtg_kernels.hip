@@ -854,9 +854,11 @@ __global__ __launch_bounds__(kBlock) void k_radix_scatter(
 // radix sort on keys held in registers and exchanged through LDS, in place of
 // a histogram, its scan and a scatter per pass over all segments (seven or so
 // launches of a few microseconds each, whose time the keys hardly show:
-// 25 segments of 6400 keys, three passes: 66 us, now 18; calls of n = 12000
-// and 16384 points still gain 6 to 12%).  Wave w holds elements [64 w items, 64 (w + 1) items), items =
-// ceil(len / 1024), so ranks are stable as in tile_rank.
+// 25 segments of 6400 keys, three passes: 66 us, now 18).  Two segments are
+// enough for it: calls of 4200, 9000 and 16384 points gain with 2 grids (d = 6:
+// 233 -> 172, 251 -> 183, 254 -> 204 us, of which this is a part) as with 25.
+// Wave w holds elements [64 w items, 64 (w + 1) items), items = ceil(len /
+// 1024), so ranks are stable as in tile_rank.
 constexpr int kSegThreads = 1024;
 constexpr int kSegWaves = kSegThreads / 64;
 constexpr int kSegItems = kSegSortKeys / kSegThreads;
@@ -1451,8 +1453,8 @@ struct TileRegs {
 // Every lane loads a whole point, no lane or coordinate tested on its own: a
 // row's loads then merge into a few wide ones (a test per coordinate made
 // each a masked 4-byte gather: at d = 12 the tiles' loads took half of the
-// L1's time; clustered d12 pairs 8.70 -> 7.22 ms, uniform d6 532 -> 509 us).  D <= 16 is the dimension itself; wider D are
-// padded with zeros.
+// L1's time; clustered d12 pairs 8.70 -> 7.22 ms, uniform d6 532 -> 509 us).
+// D <= 16 is the dimension itself; wider D are padded with zeros.
 template <int D>
 __device__ __forceinline__ void load_tile(const PairsArgs& P, uint32_t p0, uint32_t n, int nw,
                                           uint32_t lane, TileRegs<D>& R) {
@@ -2156,7 +2158,8 @@ k_cell_pairs_gram(
                 aq[q] = sAw[q][row];
                 bq[q] = sBw[q][col];
               }
-              keep = !not_first_owner<(CHECKS > 0)>(aq, bq, V.tcell, V.nw, pa0 + row, ia, pb0 + col, ib, P);
+              keep = !not_first_owner<(CHECKS > 0)>(aq, bq, V.tcell, V.nw, pa0 + row, ia,
+                                                    pb0 + col, ib, P);
             }
             if (CHECKS == 2 && keep && mr.sub) {
               keep = mr_pair<D>(P, ia, ib, mr);

@@ -139,8 +139,9 @@ struct Index {
   rtgk::QueryGrid* grids = nullptr;  // device [k]
   std::vector<void*> blocks;         // arena blocks the index owns
   // Kept where memory allows and given back when an allocation would fail
-  // otherwise (Ctx::dalloc): the points' coordinates in grid order and the
-  // first positions by top cell bits (see rtgk::QueryArgs).
+  // otherwise (Ctx::dalloc) or a plan asks what is free: the points'
+  // coordinates in grid order and the first positions by top cell bits (see
+  // rtgk::QueryArgs).  Set and cleared under the context's amu.
   float* rows = nullptr;
   uint32_t* tab = nullptr;
   int tab_bits = 0;
