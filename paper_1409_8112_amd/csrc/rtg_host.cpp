@@ -316,21 +316,22 @@ size_t Ctx::pass_bytes_bound(int64_t n, int32_t d, int32_t k, double alpha, uint
 
 // Hashed keys: from six radix passes on (clustered d12: 64 bits, eight passes
 // with values beside the keys), three passes of plain keys instead, or four
-// where the largest instance has more than 2^20 points.  A hash of h bits adds
+// where the largest instance has more than 2^21 points.  A hash of h bits adds
 // about n^2 / 2^(h + 1) tests per grid, and for points that mostly have a cell
-// to themselves as many units, so instances of up to 2^(h - 4) points take h
-// bits (under 3% of their points then collide in a grid): 4e6 such points, d =
-// 9, k = 8, took 4.89 ms with 24 bits, 2.60 with 26, 1.86 with 28 and 1.66 with
-// 32 (3.51 with their exact keys), 1e6 0.72 with 24 (0.86).  Where cells are
-// full the fourth pass shows: clustered d12, 4e6 points, 11.14 / 11.31 / 11.30 /
-// 11.50 ms (12.25 with exact keys).  The check of the accepted
+// to themselves as many units.  4e6 such points, d = 9, k = 8, took 4.89 ms
+// with 24 bits, 2.60 with 26, 1.86 with 28 and 1.66 with 32 (3.51 with their
+// exact keys), 2e6 1.69 with 24 and 0.94 with 28 (1.82), 1e6 0.72 and 0.52 with
+// 32 (0.86).  Where cells are full the fourth pass shows: clustered d12, 4e6
+// points, 11.14 / 11.31 / 11.30 / 11.50 ms (12.25 with exact keys), 2e6 5.74 with
+// 24 and 5.92 with 28 (8.32).  So 24 bits while they cost nobody more than the
+// exact keys did.  The check of the accepted
 // pairs' cells costs the pair kernel 5%.  At five passes hashed and exact keys
 // are even (uniform d12 requests).  Below 2^20 keys a pass is its launches'
 // time and the exact keys stay, with their band per cell.
 constexpr int kHashAbove = 40;
 constexpr int64_t kHashKeys = int64_t(1) << 20;
 constexpr int hash_bits(int64_t nmax) {
-  return nmax <= (int64_t(1) << 20) ? 24 : nmax <= (int64_t(1) << 24) ? 28 : 32;
+  return nmax <= (int64_t(1) << 21) ? 24 : nmax <= (int64_t(1) << 24) ? 28 : 32;
 }
 
 int plan_batch(int d, uint32_t m, const int64_t* k, const int64_t* n, const double* R,
@@ -2953,16 +2954,18 @@ constexpr int64_t kQueryOrderMin = 65536;
 constexpr int kQueryOrderBits = 24;
 // Members of a cell that a query's few lanes test; a wave takes the rest
 // (k_query_long).  Up to d = 6 cells are of a size and those few lanes are
-// the better way up to the longest ordinary ones: 1e6 queries of 1e6 points,
-// d = 6, 4.75 / 5.51 / 6.22 ms with 256 / 128 / 64, 5003 of 50021 points 141 /
-// 165 / 184 us.  Above, cells of a few points lie beside those of hundreds and
-// a wave's queries wait for its longest: 70000 queries of 20000 points, d = 9,
-// 806 / 662 / 621 us, 20000 of 1e5 points 357 / 336 / 357.  Few queries, with
-// more lanes each, test 16 members a lane: another launch and the wait before
-// it cost them more (5003 of 50021 points, d = 6, in a fresh index: 360 us with
-// 256 members, 344 with 1024).
+// the better way up to the longest ordinary ones: 1e6 queries of 1e6 points
+// take 17.65 ms with 512 and 20.6 with 256 at d = 4 (r = 0.07), 14.8 and 16.4 at
+// d = 5 (r = 0.1), 7.4 and 7.55 at d = 6 (r = 0.13), of clustered points at d = 6
+// 14.2 and 11.2 (18.1 without a limit).  Above, cells of a few points lie
+// beside those of hundreds and a wave's queries wait for its longest: 70000
+// queries of 20000 points, d = 9, 806 / 662 / 621 us with 256 / 128 / 64, 20000
+// of 1e5 points 357 / 336 / 357.  Few queries, with more lanes each, test 64
+// members a lane: another launch and the wait before it cost them more (5003
+// of 50021 points, d = 6, in a fresh index: 360 us with 256 members, 344 with
+// 1024; 137 of 2318, d = 12: 163 with 1024, 148 with all).
 uint32_t query_walk(int d, uint32_t lanes) {
-  return lanes > 16 ? 16 * lanes : d <= 6 ? 256 : 128;
+  return lanes > 16 ? 64 * lanes : d <= 6 ? 512 : 128;
 }
 
 // lean: in the least memory, without what a call only has for speed (the

@@ -2493,7 +2493,7 @@ __device__ __forceinline__ PairsArgs query_output(const QueryArgs& A) {
 // first position while the keys' prefix is the cell's: most cells are short
 // (some tens of points), so a whole wave per query idled most of its lanes
 // and waited on every cell's chain of loads.  Few queries get more lanes
-// each, many get four (16 above d = 6), which is what fills the chip (see
+// each, many get four (8 above d = 6), which is what fills the chip (see
 // launch_query_pairs; 1e6 queries of 1e6 points, d = 3, took 6.9 ms, now
 // 0.9).  Members from A.walk on are left to k_query_long: the cell is marked
 // (kQueryLong in qlo, and *A.long_cells).  Without that limit a few lanes
@@ -4429,14 +4429,15 @@ static void query_dispatch(const QueryArgs& a, unsigned blocks, bool long_cells,
 
 // Lanes per query: 1e6 queries (n = 1e6, d = 3, about 29 points a cell) took
 // 1.28 / 1.06 / 1.00 / 1.12 ms with 1 / 2 / 4 / 8; above d = 6, where cells are
-// longer and uneven, 16 (1e5 queries of 1e5 points, d = 9: 1252 us with 4,
-// 1133 with 16; 70000 of 1e5, d = 12: 1893 and 1743); few queries get as many
-// as give the chip 2^18 lanes.  At d = 5 and 6 (cells of about a hundred
+// longer and uneven, 8 (1e5 queries of 1e5 points, d = 9: 1252 / 1119 / 1102 us
+// with 4 / 8 / 16; 1e6 of 1000 points, cells of a few, 1280 with 8 and 1495 with
+// 16), above d = 12 16 (300000 of 20000, d = 13: 7325 us with 8, 6792 with 16);
+// few queries get as many as give the chip 2^18 lanes.  At d = 5 and 6 (cells of about a hundred
 // points) queries that are not in order get 32: each cell then comes from HBM
 // in a few wide steps (50000 queries of 1e6 points, d = 6: 1212 us with 8,
 // 1021 with 32; 33000: 720 and 718).
 uint32_t query_lanes(int d, int64_t m) {
-  uint32_t lanes = d > 6 ? 16 : d > 4 && m < 65536 ? 32 : 4;
+  uint32_t lanes = d > 12 ? 16 : d > 6 ? 8 : d > 4 && m < 65536 ? 32 : 4;
   while (lanes < 64 && (uint64_t)m * lanes < (1u << 18)) lanes *= 2;
   return lanes;
 }

@@ -14,13 +14,13 @@ def _dev(p):
     return torch.from_numpy(p).cuda()
 
 
-@pytest.mark.parametrize("n,passes", [(1 << 20, 3), ((1 << 20) + 1, 4)])
+@pytest.mark.parametrize("n,passes", [(1 << 21, 3), ((1 << 21) + 1, 4)])
 def test_hash_is_wider_for_more_points(n, passes):
-    """More points than 2^20 take more than 24 bits (which would put unrelated
+    """More points than 2^21 take more than 24 bits (which would put unrelated
     points of sparse sets into one run); the lists are those of the exact keys, which
     the sort-unique rule keeps."""
     from paper_1409_8112_amd import rtg
-    pts = _dev(workloads.clustered_points(n, 12, seed=2, n_clusters=8000, sigma=0.01))
+    pts = _dev(workloads.clustered_points(n, 12, seed=2, n_clusters=16000, sigma=0.01))
     with rtg.Context(0, arena_bytes=4 << 30) as ctx:
         got = ctx.all_pairs(pts, 0.028, 2, 2.0, 3)
         assert ctx.stats()["key_passes"] == passes

@@ -98,7 +98,7 @@ def test_many_pairs_of_few_queries_run_once(m, runs):
 
 @pytest.mark.parametrize("d", [1, 3, 6, 13])
 @pytest.mark.parametrize("m", [1, 70, 5000, 70000])
-@pytest.mark.parametrize("crowd", [128, 256, 257, 1025, 3000])
+@pytest.mark.parametrize("crowd", [128, 256, 257, 1025, 3000, 9000])
 def test_crowded_cells(d, m, crowd):
     """Cells of as many points as a query's own lanes test, and of more, which
     a wave finishes: with and without tables, in order and as given."""
@@ -112,7 +112,7 @@ def test_crowded_cells(d, m, crowd):
     qs = rng.random((m, d)).astype(np.float32)
     near = rng.permutation(m)[:min(m, 60)]
     qs[near] = pts[rng.integers(0, crowd, len(near))] + 0.001
-    with rtg.Context(0, arena_bytes=1 << 30) as ctx:
+    with rtg.Context(0, arena_bytes=4 << 30) as ctx:
         index = ctx.index_build(torch.from_numpy(pts).cuda(), r, k, alpha, seed)
         rp, col = _query(ctx, index, qs)
     rows = np.union1d(near, rng.permutation(m)[:100])
